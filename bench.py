@@ -39,6 +39,7 @@ METRIC = "CG iters/s + achieved HBM GB/s, 256^3 Poisson; mixed-prec vs FP64 at 1
 # tied to their hash)
 KERNEL_SOURCES = ["paper_2305_05988_amd/csrc/common.hpp", "paper_2305_05988_amd/csrc/rowops.hpp",
                   "paper_2305_05988_amd/csrc/csr.hpp", "paper_2305_05988_amd/csrc/sell.hpp",
+                  "paper_2305_05988_amd/csrc/pattern.hpp",
                   "paper_2305_05988_amd/csrc/kernels_cg.hpp"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cg_pass1_poisson256_traffic.txt")
 # Inside the timed region every PROFILE_EVERY-th launch of each kernel is
@@ -65,17 +66,11 @@ def csr_bytes(n, nnz, val_bytes=8):
     return val_bytes * nnz + 4 * nnz + 4 * (n + 1)
 
 
-def packed_matrix_bytes(A, n):
-    """Bytes of the matrix representation one SpMV pass reads: for the packed
-    layout the padded value slots (8 B), the column indices of the slices
-    that keep them (4 B), the per-position offset (4 B) and lane mask (8 B)
-    of the offset slices and the int64 slice offsets -- no row pointers; for
-    an unpacked matrix the CSR arrays."""
-    slots, col_slots = A.packed_slots, A.packed_column_slots
-    if not slots:
-        return csr_bytes(n, A.nnz)
-    return (8 * slots + 4 * col_slots + 12 * ((slots - col_slots) // 64)
-            + 8 * ((n + 63) // 64 + 1))
+def packed_matrix_bytes(A, n, dtype="f64"):
+    """Bytes of the matrix representation one SpMV pass reads: what the
+    library says of its packed layout (its_csr_packed_bytes), or the CSR
+    arrays of an unpacked matrix."""
+    return A.packed_bytes(dtype) if A.packed_slots else csr_bytes(n, A.nnz)
 
 
 def host_cpu():
@@ -559,10 +554,6 @@ def kernel_suite(its, inputs, iters=10):
         its.solve(A, b, **kw)
         torch.cuda.synchronize()
 
-    def packed_lowp_bytes(A, n, vb):
-        slots, cs = A.packed_slots, A.packed_column_slots
-        return vb * slots + 4 * cs + 12 * ((slots - cs) // 64) + 8 * ((n + 63) // 64 + 1)
-
     # 256^3 Poisson, packed CSR with FP32 and FP16 value copies
     N = 256
     rp, col, val = inputs.poisson7_csr(N)
@@ -571,7 +562,7 @@ def kernel_suite(its, inputs, iters=10):
     del rp, col, val
     b = its.spmv(A, torch.from_numpy(inputs.uniform_vector(n, 1)).cuda())
     V, V32 = 8 * n, 4 * n
-    M, M32, M16 = packed_matrix_bytes(A, n), packed_lowp_bytes(A, n, 4), packed_lowp_bytes(A, n, 2)
+    M, M32, M16 = packed_matrix_bytes(A, n), packed_matrix_bytes(A, n, "f32"), packed_matrix_bytes(A, n, "f16")
     log(f"kernels: cg 256^3 ({iters} iterations)")
     run(A, b, method="cg", rtol=0.0, max_iter=iters)
     log(f"kernels: jacobi 256^3 ({iters} sweeps)")
@@ -626,8 +617,8 @@ def kernel_suite(its, inputs, iters=10):
     out["stencil27_192_packed"] = {
         "n": n2, "k_cg_pass1<SellOp<double": packed_matrix_bytes(A3, n2) + 3 * V3,
         "k_cg_pass2<double, true": 6 * V3,
-        "k_cg_pass1_pairs<SellOp<float": packed_lowp_bytes(A3, n2, 4) + 3 * V3_32,
-        "k_cg_pass1_pairs<SellOp<__half": packed_lowp_bytes(A3, n2, 2) + 3 * V3_32,
+        "k_cg_pass1_pairs<SellOp<float": packed_matrix_bytes(A3, n2, "f32") + 3 * V3_32,
+        "k_cg_pass1_pairs<SellOp<__half": packed_matrix_bytes(A3, n2, "f16") + 3 * V3_32,
         "k_cg_pass2_f32x2": 6 * V3_32}
     del A3, b3
     torch.cuda.empty_cache()

@@ -167,7 +167,12 @@ its_status its_csr_set_lowp(its_matrix *A, const void *val_lo, int32_t dtype);
    all: one offset and one 64-lane mask per entry position replace them, and
    each row's entries sit at the positions of their offsets.  Matrices from
    structured grids (stencils written as CSR) pack entirely this way, which
-   cuts the bytes per FP64 entry from 12 to 8.
+   cuts the bytes per FP64 entry from 12 to 8.  Where in every slice the rows
+   draw their offsets from one list and all entries of an offset hold the same
+   value (in every precision packed), the layout keeps no entries at all: a
+   pattern (offsets, lane masks, values) is stored once however many slices
+   have it, and each slice stores its pattern's number.  Constant-coefficient
+   operators on structured grids pack this way, whatever their sides.
    The packed copy (col, val and any low-precision values attached with
    its_csr_set_lowp, which must come first) is allocated and owned by the
    handle and freed by its_matrix_destroy or the next its_csr_pack; it is a
@@ -205,13 +210,20 @@ its_status its_csr_transpose(its_matrix *A, void *stream);
 its_status its_csr_value_grad(const its_matrix *A, const double *x, const double *lam, double *dval,
                               void *stream);
 
-/* Slots of the packed layout (entries plus padding), 0 if not packed. */
+/* Slots of the packed layout (entries plus padding; those that the pattern
+   form stands for, where it is used), 0 if not packed. */
 int64_t its_csr_packed_slots(const its_matrix *A);
 
 /* Slots of the packed layout that store a column index (those of the slices
    that are not offset slices, see its_csr_pack); 0 if not packed or if
    every slice is an offset slice. */
 int64_t its_csr_packed_column_slots(const its_matrix *A);
+
+/* Bytes of the matrix that one pass over the packed layout reads with values
+   of `dtype` (ITS_F64, ITS_F32, ITS_F16): values, columns, slice descriptors
+   and offsets, or the pattern numbers and the pattern table; 0 if not packed.
+   (A pass of the methods of Section 3.1 reads the matrix once.) */
+int64_t its_csr_packed_bytes(const its_matrix *A, int32_t dtype);
 
 /* Point colouring for symmetric Gauss-Seidel on a CSR matrix (Section 3.4:
    colours, red-black without rotation).  color: n uint8 (device) with values

@@ -127,6 +127,11 @@ class CSRMatrix(_Matrix):
         """Packed slots that still store a column index (0: all offset slices)."""
         return int(L.lib().its_csr_packed_column_slots(self._h))
 
+    def packed_bytes(self, dtype="f64") -> int:
+        """Bytes of the matrix one pass over the packed layout reads with
+        values of ``dtype``."""
+        return int(L.lib().its_csr_packed_bytes(self._h, _DTYPES[dtype]))
+
     def build_transpose(self):
         """Builds A^T (device memory owned by the handle) for transposed
         solves; solve(..., transpose=True) calls it on first use."""

@@ -25,6 +25,25 @@ using namespace its;
 
 enum MatKind { kCsr = 0, kSten7 = 1, kSten27 = 2, kVar7 = 3 };
 
+// The pattern table of a packed layout and its slices' pattern numbers
+// (pattern.hpp), owned by whoever holds it; pid is null where the layout has
+// no patterns and keeps values (and columns) per entry.
+struct PatArrays {
+  int32_t *pid = nullptr;
+  PatHead *head = nullptr;
+  int32_t *off = nullptr;
+  uint64_t *mask = nullptr;
+  double *val = nullptr;
+  float *val32 = nullptr, *val16 = nullptr;
+  int32_t count = 0;
+  void release() {
+    void *all[] = {pid, head, off, mask, val, val32, val16};
+    for (void *p : all)
+      if (p) (void)hipFree(p);
+    *this = PatArrays();
+  }
+};
+
 struct its_matrix {
   int kind = kCsr;
   int64_t n = 0, nnz = 0;
@@ -55,7 +74,9 @@ struct its_matrix {
   int64_t sell_entries = 0;
   int64_t sell_col_slots = 0;  // slots of the slices that store columns
   int32_t sell_wmax = 0;       // widest slice
+  PatArrays pat;               // instead of all of these where every slice has a pattern
   double pack_fill = 0.0;  // max_fill of the last its_csr_pack (0: not packed)
+  bool packed() const { return sp || pat.pid; }
   // Gauss-Seidel: each colour's rows packed the same way, in colour order
   struct ColorPack {
     int64_t *sp = nullptr;
@@ -63,6 +84,7 @@ struct its_matrix {
     double *val = nullptr;
     int32_t *soff = nullptr;
     uint64_t *smask = nullptr;
+    PatArrays pat;
   };
   std::vector<ColorPack> cpack;
   // A^T (its_csr_transpose): a CSR handle that owns its arrays (own_*)
@@ -91,6 +113,7 @@ static void free_color_packs(its_matrix *A) {
     if (c.val) (void)hipFree(c.val);
     if (c.soff) (void)hipFree(c.soff);
     if (c.smask) (void)hipFree(c.smask);
+    c.pat.release();
   }
   A->cpack.clear();
 }
@@ -105,6 +128,7 @@ static void free_packed(its_matrix *A) {
   if (A->sval16) (void)hipFree(A->sval16);
   if (A->soff) (void)hipFree(A->soff);
   if (A->smask) (void)hipFree(A->smask);
+  A->pat.release();
   A->sp = nullptr;
   A->scol = nullptr;
   A->sval = nullptr;
@@ -334,6 +358,8 @@ template <class F>
 its_status with_op64(const its_matrix *A, F &&f) {
   switch (A->kind) {
     case kCsr:
+      if (A->pat.pid)
+        return f(PatOp<double>{A->pat.pid, A->pat.head, A->pat.off, A->pat.mask, A->pat.val, int32_t(A->n), nullptr});
       if (A->sp && !A->scol)
         return f(SellOp<double, double, true>{A->sp, A->scol, A->sval, int32_t(A->n), A->soff, A->smask, nullptr});
       if (A->sp) return f(SellOp<double, double>{A->sp, A->scol, A->sval, int32_t(A->n), A->soff, A->smask, nullptr});
@@ -363,6 +389,9 @@ its_status with_op32(const its_matrix *A, int dtype, F &&f) {
   switch (A->kind) {
     case kVar7: return fail(ITS_E_UNSUPPORTED, "mixed precision is not available for variable coefficients");
     case kCsr:
+      if (A->pat.pid)
+        return f(PatOp<float>{A->pat.pid, A->pat.head, A->pat.off, A->pat.mask,
+                              dtype == ITS_F32 ? A->pat.val32 : A->pat.val16, int32_t(A->n), nullptr});
       if (dtype == ITS_F32) {
         if (A->sp && !A->scol)
           return f(SellOp<float, float, true>{A->sp, A->scol, A->sval32, int32_t(A->n), A->soff, A->smask, nullptr});
@@ -500,9 +529,11 @@ int64_t steps_for(int64_t max_iter) {
 }
 
 // Common prologue: zero the States, b.b, r0 = b - A x0 (stored in r if
-// non-null) and r0.r0.  Returns bb and rr0 through `host`.
+// non-null; Pairs: as the first members of pairs, the second ones 0) and
+// r0.r0.  Returns bb and rr0 through `host`.
+template <bool Pairs>
 its_status prologue(Run &run, const its_matrix *A, const WS &w, const double *b, const double *x,
-                    double *r, int rstride, State *host, double &bb, double &rr) {
+                    double *r, State *host, double &bb, double &rr) {
   const int32_t n = int32_t(A->n);
   const int G = grid_for(n);
   LAUNCH(run, kClassOther, k_reset, 1, w.st, 2, w.R);
@@ -510,7 +541,7 @@ its_status prologue(Run &run, const its_matrix *A, const WS &w, const double *b,
   FINISH(run, 1, w.R, G, (FinDot{w.st, 0}));
   its_status s = with_op64(A, [&](auto op) -> its_status {
     const int GA = op.grid();
-    LAUNCH(run, kClassOther, k_residual<decltype(op)>, GA, op, b, x, r, rstride, w.R);
+    LAUNCH(run, kClassOther, (k_residual<decltype(op), Pairs>), GA, op, b, x, r, w.R);
     FINISH(run, 1, w.R, GA, (FinDot{w.st, 1}));
     return ITS_OK;
   });
@@ -531,7 +562,7 @@ its_status true_residual(Run &run, const its_matrix *A, const WS &w, const doubl
                          const double *x, State *host, double bb, its_result *res) {
   its_status s = with_op64(A, [&](auto op) -> its_status {
     const int GA = op.grid();
-    LAUNCH(run, kClassOther, k_residual<decltype(op)>, GA, op, b, x, (double *)nullptr, 1, w.R);
+    LAUNCH(run, kClassOther, (k_residual<decltype(op), false>), GA, op, b, x, (double *)nullptr, w.R);
     FINISH(run, 1, w.R, GA, (FinDot{w.st2, 2}));
     return ITS_OK;
   });
@@ -604,7 +635,7 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
   double2_t *rp = w.reg<double2_t>(0);  // {r, p} pairs
   double *q = w.v64(1);
   double bb, rr;
-  its_status s = prologue(run, A, w, b, x, reinterpret_cast<double *>(rp), 2, h, bb, rr);
+  its_status s = prologue<true>(run, A, w, b, x, reinterpret_cast<double *>(rp), h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -676,7 +707,7 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
   double2_t *ra = w.reg<double2_t>(0);  // {r, Ap} pairs
   double *p = w.v64(1), *wv = w.v64(2);
   double bb, rr;
-  its_status s = prologue(run, A, w, b, x, reinterpret_cast<double *>(ra), 2, h, bb, rr);
+  its_status s = prologue<true>(run, A, w, b, x, reinterpret_cast<double *>(ra), h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -739,7 +770,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
   float2_t *rhp = w.reg<float2_t>(1) + kGuardPairs;
   float *q = w.reg<float>(2), *d = w.reg<float>(3);
   double bb, rr;
-  its_status s = prologue(run, A, w, b, x, r, 1, h, bb, rr);
+  its_status s = prologue<false>(run, A, w, b, x, r, h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -755,7 +786,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
     if (outer > 0) {  // r = b - A x of the refined iterate
       s = with_op64(A, [&](auto op) -> its_status {
         const int GA = op.grid();
-        LAUNCH(run, 2, k_residual<decltype(op)>, GA, op, b, (const double *)x, r, 1, w.R);
+        LAUNCH(run, 2, (k_residual<decltype(op), false>), GA, op, b, (const double *)x, r, w.R);
         FINISH(run, 1, w.R, GA, (FinDot{w.st, 1}));
         return ITS_OK;
       });
@@ -768,7 +799,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
     if (!std::isfinite(rr)) { res->status = ITS_BREAKDOWN; break; }
     if (outer == o->max_outer || inner_total >= o->max_iter) { res->status = ITS_NOT_CONVERGED; break; }
     const double rn = std::sqrt(rr);
-    LAUNCH(run, 3, k_ir_scale, G, n, (const double *)r, reinterpret_cast<float *>(rhp), d, w.R, rn);
+    LAUNCH(run, 3, k_ir_scale, G, n, (const double *)r, rhp, d, w.R, rn);
     FINISH(run, 1, w.R, G, (FinDot{w.st2, 1}));
     s = poll(run, w.st2, h);
     if (s != ITS_OK) return s;
@@ -829,7 +860,7 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
   double2_t *ru = w.reg<double2_t>(0), *rv = w.reg<double2_t>(3);
   double *rs = w.v64(1), *p = w.v64(2), *t = w.v64(4);
   double bb, rr;
-  its_status s = prologue(run, A, w, b, x, reinterpret_cast<double *>(ru), 2, h, bb, rr);
+  its_status s = prologue<true>(run, A, w, b, x, reinterpret_cast<double *>(ru), h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -898,7 +929,7 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
   const int G = grid_for(n);
   double *X[2] = {x, w.v64(0)};
   double bb, rr;
-  its_status s = prologue(run, A, w, b, x, nullptr, 1, h, bb, rr);
+  its_status s = prologue<false>(run, A, w, b, x, nullptr, h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -940,7 +971,7 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
   if (A->kind == kVar7) return fail(ITS_E_UNSUPPORTED, "Gauss-Seidel is not available for variable coefficients");
   const int nc = A->kind == kCsr ? A->ncolors : (A->kind == kSten7 ? 2 : 8);
   double bb, rr;
-  its_status s = prologue(run, A, w, b, x, nullptr, 1, h, bb, rr);
+  its_status s = prologue<false>(run, A, w, b, x, nullptr, h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -975,7 +1006,13 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
       if (!A->cpack.empty()) {
         const auto &cp = A->cpack[size_t(c)];
         const int32_t *rows = A->color_rows + beg;
-        if (!cp.col) {  // every slice an offset slice
+        if (cp.pat.pid) {
+          const PatOp<double> op{cp.pat.pid, cp.pat.head, cp.pat.off, cp.pat.mask, cp.pat.val, cnt, rows};
+          if (nc == 2 && c == 0)
+            LAUNCH(run, 0, (k_gs_rows_packed<M, Backwards<PatOp<double>>>), Gc, Backwards<PatOp<double>>{op}, rows, b, x, xs, (const State *)w.st, w.R);
+          else
+            LAUNCH(run, 0, (k_gs_rows_packed<M, PatOp<double>>), Gc, op, rows, b, x, xs, (const State *)w.st, w.R);
+        } else if (!cp.col) {  // every slice an offset slice
           // with two colours the red half-sweeps run backwards: each starts on the rows
           // the black one before it wrote last
           const SellOp<double, double, true> op{cp.sp, cp.col, cp.val, cnt, cp.soff, cp.smask, rows};
@@ -1413,7 +1450,7 @@ its_status its_csr_value_grad(const its_matrix *A, const double *x, const double
 its_status its_csr_set_lowp(its_matrix *A, const void *val_lo, int32_t dtype) {
   if (!A || A->kind != kCsr) return fail(ITS_E_INVALID, "not a CSR matrix");
   drop_graph(A);
-  if (A->sp) return fail(ITS_E_INVALID, "set low-precision values before its_csr_pack");
+  if (A->packed()) return fail(ITS_E_INVALID, "set low-precision values before its_csr_pack");
   if (!val_lo && A->nnz > 0) return fail(ITS_E_INVALID, "null values");
   if (reinterpret_cast<uintptr_t>(val_lo) % 16)
     return fail(ITS_E_INVALID, "low-precision values must be 16-byte aligned");
@@ -1443,10 +1480,12 @@ struct PackOut {
   __half *val16 = nullptr;
   int32_t *soff = nullptr;
   uint64_t *smask = nullptr;
+  PatArrays pat;  // instead of all of these where every slice has a pattern
   int64_t slots = 0;
   int32_t wmax = 0;
   int64_t col_slots = 0;
   void release() {
+    pat.release();
     if (sp) (void)hipFree(sp);
     if (col) (void)hipFree(col);
     if (val) (void)hipFree(val);
@@ -1457,6 +1496,94 @@ struct PackOut {
     *this = PackOut();
   }
 };
+
+// Looks at every slice of the layout: the offset slices get their descriptors
+// and flags (P.sp, P.soff, P.smask; P.col_slots the slots of the others), and
+// if every slice has a pattern and there are at most kPatLimit of them, P.pat
+// is the layout.
+static hipError_t scan_slices(const its_matrix *A, const int32_t *rows, int32_t count, const float *v32,
+                              const __half *v16, hipStream_t s, PackOut &P) {
+  const int64_t ns = (int64_t(count) + kSlice - 1) / kSlice;
+  const int grid = int(std::min<int64_t>((ns + kWaves - 1) / kWaves, 65536));
+  struct Found {
+    unsigned long long key[kPatTable];
+    unsigned int rep[kPatTable];
+    unsigned long long col_slots, odd;
+  };
+  DevTmp tmp, rep, number;
+  PatArrays T;
+  hipError_t e = hipMalloc(&tmp.p, sizeof(Found));
+  if (e == hipSuccess) e = hipMalloc(&T.pid, size_t(ns) * sizeof(int32_t));
+  if (e != hipSuccess) {
+    T.release();
+    return e;
+  }
+  Found *F = static_cast<Found *>(tmp.p);
+  std::vector<char> raw(sizeof(Found));
+  Found *H = reinterpret_cast<Found *>(raw.data());
+  e = hipMemsetAsync(F, 0, sizeof(Found), s);
+  if (e == hipSuccess) e = hipMemsetAsync(F->rep, 0xff, sizeof(F->rep), s);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_slice_scan, dim3(grid), dim3(kBlock), 0, s, count, A->rp, rows, A->col, A->val, v32, v16,
+                       P.sp, P.soff, P.smask, T.pid, F->key, F->rep, &F->col_slots, &F->odd);
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(H, F, sizeof(Found), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) {
+    T.release();
+    return e;
+  }
+  P.col_slots = int64_t(H->col_slots);
+  // patterns numbered in the order of their first slices
+  std::vector<std::pair<uint32_t, int32_t>> found;
+  if (H->odd == 0)
+    for (int32_t q = 0; q < kPatTable; ++q)
+      if (H->key[q]) found.emplace_back(H->rep[q], q);
+  if (found.empty() || found.size() > size_t(kPatLimit)) {
+    T.release();
+    return hipSuccess;
+  }
+  std::sort(found.begin(), found.end());
+  std::vector<int32_t> hrep(found.size()), hnumber(kPatTable, 0);
+  for (size_t q = 0; q < found.size(); ++q) {
+    hrep[q] = int32_t(found[q].first);
+    hnumber[size_t(found[q].second)] = int32_t(q);
+  }
+  T.count = int32_t(found.size());
+  const size_t at = found.size() * kPatMax;
+  if (e == hipSuccess) e = hipMalloc(&rep.p, hrep.size() * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMalloc(&number.p, hnumber.size() * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMalloc(&T.head, found.size() * sizeof(PatHead));
+  if (e == hipSuccess) e = hipMalloc(&T.off, at * sizeof(int32_t));
+  if (e == hipSuccess) e = hipMalloc(&T.mask, at * sizeof(uint64_t));
+  if (e == hipSuccess) e = hipMalloc(&T.val, at * sizeof(double));
+  if (e == hipSuccess && v32) e = hipMalloc(&T.val32, at * sizeof(float));
+  if (e == hipSuccess && v16) e = hipMalloc(&T.val16, at * sizeof(float));
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(rep.p, hrep.data(), hrep.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess)
+    e = hipMemcpyAsync(number.p, hnumber.data(), hnumber.size() * sizeof(int32_t), hipMemcpyHostToDevice, s);
+  if (e == hipSuccess) {
+    hipLaunchKernelGGL(k_pattern_emit, dim3((T.count + kWaves - 1) / kWaves), dim3(kBlock), 0, s, T.count, count,
+                       A->rp, rows, A->col, A->val, v32, v16, static_cast<const int32_t *>(rep.p), T.head, T.off,
+                       T.mask, T.val, T.val32, T.val16);
+    hipLaunchKernelGGL(k_pattern_check, dim3(grid), dim3(kBlock), 0, s, count, A->rp, rows, A->col, A->val, v32, v16,
+                       static_cast<const int32_t *>(number.p), (const PatHead *)T.head, (const int32_t *)T.off,
+                       (const uint64_t *)T.mask, (const double *)T.val, (const float *)T.val32,
+                       (const float *)T.val16, T.pid, &F->odd);
+    e = hipGetLastError();
+  }
+  unsigned long long odd = 0;
+  if (e == hipSuccess) e = hipMemcpyAsync(&odd, &F->odd, sizeof(odd), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess || odd) {
+    T.release();
+    return e;
+  }
+  P.pat = T;
+  return hipSuccess;
+}
 
 static its_status pack_rows(const its_matrix *A, const int32_t *rows, int64_t count, double max_fill,
                             bool lowp, hipStream_t s, PackOut &out) {
@@ -1502,31 +1629,29 @@ static its_status pack_rows(const its_matrix *A, const int32_t *rows, int64_t co
   const int64_t cols = total / kSlice;  // entry positions over all slices
   if (e == hipSuccess && total > 0) e = hipMalloc(&P.soff, size_t(cols) * sizeof(int32_t));
   if (e == hipSuccess && total > 0) e = hipMalloc(&P.smask, size_t(cols) * sizeof(uint64_t));
-  if (e == hipSuccess && total > 0) e = hipMalloc(&P.val, size_t(total) * sizeof(double));
-  if (e == hipSuccess && total > 0 && lowp && A->val32) e = hipMalloc(&P.val32, size_t(total) * sizeof(float));
-  if (e == hipSuccess && total > 0 && lowp && A->val16) e = hipMalloc(&P.val16, size_t(total) * sizeof(__half));
   if (e == hipSuccess)
     e = hipMemcpyAsync(P.sp, hsp.data(), size_t(ns + 1) * sizeof(int64_t), hipMemcpyHostToDevice, s);
   const int32_t ci = int32_t(count);
+  const float *v32 = lowp ? A->val32 : nullptr;
+  const __half *v16 = lowp ? A->val16 : nullptr;
   if (e == hipSuccess && total > 0) {
-    // offset slices, then columns for the slices that keep them
-    DevTmp nslots;
-    unsigned long long hslots = 0;
-    e = hipMalloc(&nslots.p, sizeof(unsigned long long));
-    if (e == hipSuccess) e = hipMemsetAsync(nslots.p, 0, sizeof(unsigned long long), s);
-    if (e == hipSuccess) {
-      hipLaunchKernelGGL(k_sell_offsets, dim3(gw), dim3(kBlock), 0, s, ci, A->rp, rows, A->col, P.sp,
-                         P.soff, P.smask, static_cast<unsigned long long *>(nslots.p));
-      e = hipGetLastError();
+    e = scan_slices(A, rows, ci, v32, v16, s, P);
+    if (e == hipSuccess && P.pat.pid) {  // nothing is kept per entry
+      (void)hipFree(P.sp);
+      (void)hipFree(P.soff);
+      (void)hipFree(P.smask);
+      P.sp = nullptr;
+      P.soff = nullptr;
+      P.smask = nullptr;
+    } else {
+      if (e == hipSuccess) e = hipMalloc(&P.val, size_t(total) * sizeof(double));
+      if (e == hipSuccess && v32) e = hipMalloc(&P.val32, size_t(total) * sizeof(float));
+      if (e == hipSuccess && v16) e = hipMalloc(&P.val16, size_t(total) * sizeof(__half));
+      // columns are addressed by slot, so any explicit slice needs the full array
+      if (e == hipSuccess && P.col_slots > 0) e = hipMalloc(&P.col, size_t(total) * sizeof(int32_t));
     }
-    if (e == hipSuccess)
-      e = hipMemcpyAsync(&hslots, nslots.p, sizeof(hslots), hipMemcpyDeviceToHost, s);
-    if (e == hipSuccess) e = hipStreamSynchronize(s);
-    P.col_slots = int64_t(hslots);
-    // columns are addressed by slot, so any explicit slice needs the full array
-    if (e == hipSuccess && P.col_slots > 0) e = hipMalloc(&P.col, size_t(total) * sizeof(int32_t));
   }
-  if (e == hipSuccess && total > 0) {
+  if (e == hipSuccess && total > 0 && !P.pat.pid) {
     const int gs = int(std::min<int64_t>((ns * kSlice + kBlock - 1) / kBlock, 65536));
     hipLaunchKernelGGL(k_sell_scatter<double>, dim3(gs), dim3(kBlock), 0, s, ci, A->rp, rows, A->col,
                        A->val, (const int64_t *)P.sp, (const int32_t *)P.soff, P.col, P.val);
@@ -1569,6 +1694,7 @@ static its_status pack_colors(its_matrix *A, hipStream_t s) {
         if (q.val) (void)hipFree(q.val);
         if (q.soff) (void)hipFree(q.soff);
         if (q.smask) (void)hipFree(q.smask);
+        q.pat.release();
       }
       if (st == ITS_E_UNSUPPORTED) {
         g_err.clear();
@@ -1582,6 +1708,7 @@ static its_status pack_colors(its_matrix *A, hipStream_t s) {
     cp.val = P.val;
     cp.soff = P.soff;
     cp.smask = P.smask;
+    cp.pat = P.pat;
     packs.push_back(cp);
   }
   A->cpack = packs;
@@ -1605,6 +1732,7 @@ its_status its_csr_pack(its_matrix *A, double max_fill, void *stream) {
   A->sval16 = P.val16;
   A->soff = P.soff;
   A->smask = P.smask;
+  A->pat = P.pat;
   A->sell_entries = P.slots;
   A->sell_col_slots = P.col_slots;
   A->sell_wmax = P.wmax;
@@ -1614,10 +1742,20 @@ its_status its_csr_pack(its_matrix *A, double max_fill, void *stream) {
   return pack_colors(A, s);
 }
 
-int64_t its_csr_packed_slots(const its_matrix *A) { return A && A->sp ? A->sell_entries : 0; }
+int64_t its_csr_packed_slots(const its_matrix *A) { return A && A->packed() ? A->sell_entries : 0; }
 
 int64_t its_csr_packed_column_slots(const its_matrix *A) {
-  return A && A->sp ? A->sell_col_slots : 0;
+  return A && A->packed() ? A->sell_col_slots : 0;
+}
+
+int64_t its_csr_packed_bytes(const its_matrix *A, int32_t dtype) {
+  if (!A || !A->packed() || dtype < ITS_F64 || dtype > ITS_F16) return 0;
+  const int64_t ns = (A->n + kSlice - 1) / kSlice;
+  if (A->pat.pid)
+    return 4 * ns + int64_t(A->pat.count) * (int64_t(sizeof(PatHead)) + kPatMax * (12 + (dtype == ITS_F64 ? 8 : 4)));
+  const int64_t vb = dtype == ITS_F64 ? 8 : dtype == ITS_F32 ? 4 : 2;
+  return vb * A->sell_entries + 4 * A->sell_col_slots + 12 * ((A->sell_entries - A->sell_col_slots) / kSlice) +
+         8 * (ns + 1);
 }
 
 its_status its_csr_set_colors(its_matrix *A, const uint8_t *color, int32_t ncolors, void *stream) {
@@ -1847,7 +1985,8 @@ static its_status solve_impl(const its_matrix *Ac, const its_options *o, const d
     std::memcpy(&rt, &o->restart_tol, sizeof(rt));
     run.key = {uint64_t(o->method), uint64_t(o->inner_dtype), uint64_t(o->restart_mode), rt,
                uint64_t(o->transpose), uint64_t(reinterpret_cast<uintptr_t>(Ac)),
-               uint64_t(reinterpret_cast<uintptr_t>(A->sp)), uint64_t(A->cpack.size()),
+               uint64_t(reinterpret_cast<uintptr_t>(A->sp)), uint64_t(reinterpret_cast<uintptr_t>(A->pat.pid)),
+               uint64_t(A->cpack.size()),
                uint64_t(reinterpret_cast<uintptr_t>(A->color_rows)), uint64_t(A->kind),
                uint64_t(reinterpret_cast<uintptr_t>(b)), uint64_t(reinterpret_cast<uintptr_t>(x)),
                uint64_t(reinterpret_cast<uintptr_t>(workspace)), uint64_t(A->n),

@@ -13,6 +13,7 @@
 #include "kernels_persist.hpp"
 #include "kernels_relax.hpp"
 #include "kernels_util.hpp"
+#include "pattern.hpp"
 #include "sell.hpp"
 #include "stencil.hpp"
 #include "varcoef.hpp"

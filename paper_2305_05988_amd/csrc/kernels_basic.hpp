@@ -61,31 +61,40 @@ template <class Op>
 __global__ void __launch_bounds__(kBlock) k_spmv(Op A, const double *__restrict__ x,
                                                  double *__restrict__ y) {
   __shared__ typename Op::Smem sm;
-  auto xj = [&](int32_t j) { return x[j]; };
+  const Gather<double> xj{x};
   auto same = [](double v) { return v; };
   A.rows(sm, xj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
     double acc = 0.0;
-    entries([&](int32_t, double a, double v) { acc = fma(a, v, acc); });
+    entries([&](int32_t, double a, double v, bool has = true) { acc = has ? fma(a, v, acc) : acc; });
     if (valid) st_nt(y + i, acc);
   });
 }
 
-// r = b - A x (r may be null; entry i stored at r[i * rstride]) and r.r
-// (finished by FinDot).
-template <class Op>
+// r = b - A x and r.r (finished by FinDot).  r may be null; with Pairs it holds
+// pairs, whose second members become 0.
+template <class Op, bool Pairs>
 __global__ void __launch_bounds__(kBlock) k_residual(Op A, const double *__restrict__ b,
                                                      const double *__restrict__ x, double *r,
-                                                     int rstride, Reduce *R) {
+                                                     Reduce *R) {
   __shared__ typename Op::Smem sm;
-  auto xj = [&](int32_t j) { return x[j]; };
+  const Gather<double> xj{x};
   auto same = [](double v) { return v; };
   Dot2 a;
   A.rows(sm, xj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
     double acc = 0.0;
-    entries([&](int32_t, double av, double v) { acc = fma(av, v, acc); });
+    entries([&](int32_t, double av, double v, bool has = true) { acc = has ? fma(av, v, acc) : acc; });
     if (valid) {
       const double ri = ld_nt(b + i) - acc;
-      if (r) st_nt(r + int64_t(i) * rstride, ri);
+      if (r) {
+        if constexpr (Pairs) {
+          double2_t o;
+          o.x = ri;
+          o.y = 0.0;
+          st_nt(reinterpret_cast<double2_t *>(r) + i, o);
+        } else {
+          st_nt(r + i, ri);
+        }
+      }
       a.add(ri, ri);
     }
   });

@@ -51,18 +51,17 @@ __global__ void __launch_bounds__(kBlock) k_bicg_a(Op A, const double2_t *__rest
   const bool restart = st->restart;
   const double bet = st->beta;
   const double rn = restart ? __builtin_sqrt(st->rho) : 1.0;
-  auto load = [&](int32_t j) -> double2_t { return ru[j]; };
+  const Gather<double2_t> load{ru};
   auto pv = [&](const double2_t &e) -> double { return plain ? e.x : fma(bet, e.y, e.x); };
   Dot2 a;
   A.rows(sm, load, pv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
     double acc = 0.0, pi = 0.0;
     bool have = false;  // p_i taken from the row's diagonal entry
-    entries([&](int32_t j, double av, double pj) {
-      acc = fma(av, pj, acc);
-      if (j == i) {
-        pi = pj;
-        have = true;
-      }
+    entries([&](int32_t j, double av, double pj, bool has = true) {
+      acc = has ? fma(av, pj, acc) : acc;
+      const bool own_entry = has && j == i;
+      pi = own_entry ? pj : pi;
+      have = have || own_entry;
     });
     if (valid) {
       if (!have) pi = own();
@@ -109,18 +108,17 @@ __global__ void __launch_bounds__(kBlock) k_bicg_b(Op A, const double2_t *__rest
   __shared__ typename Op::Smem sm;
   if (st->flag != kRunning) return;
   const double alpha = st->alpha;
-  auto load = [&](int32_t j) -> double2_t { return rv[j]; };
+  const Gather<double2_t> load{rv};
   auto sv = [&](const double2_t &e) -> double { return fma(-alpha, e.y, e.x); };
   Dot2 a0, a1;
   A.rows(sm, load, sv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
     double acc = 0.0, si = 0.0;
     bool have = false;  // s_i taken from the row's diagonal entry
-    entries([&](int32_t j, double av, double sv_j) {
-      acc = fma(av, sv_j, acc);
-      if (j == i) {
-        si = sv_j;
-        have = true;
-      }
+    entries([&](int32_t j, double av, double sv_j, bool has = true) {
+      acc = has ? fma(av, sv_j, acc) : acc;
+      const bool own_entry = has && j == i;
+      si = own_entry ? sv_j : si;
+      have = have || own_entry;
     });
     if (valid) {
       if (!have) si = own();

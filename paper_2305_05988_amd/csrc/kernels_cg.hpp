@@ -13,7 +13,8 @@ namespace its {
 //           q = A p, alpha = rho / (p.q)
 //   pass 2: p = r + beta p stored, x += alpha p, r -= alpha q, rho' = r.r,
 //           convergence test, beta = rho'/rho
-// At the first iteration p = r.  r and p are stored interleaved as pairs
+// At the first iteration p = r: the prologue stores p = 0 beside r and beta is
+// 0, so the same expression gives it.  r and p are stored interleaved as pairs
 // {r_i, p_i}, so pass 1 gathers both with one access per column.
 //
 // x is read and written every other iteration (both pass 2 kernels): an even
@@ -32,20 +33,18 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass1(Op A,
   __shared__ typename Op::Smem sm;
   if (st->flag != kRunning) return;
   using P2 = typename Pair<T>::type;
-  const bool first = st->k == 0;
   const T beta = T(st->beta);
-  auto load = [&](int32_t j) -> P2 { return rp[j]; };
-  auto pv = [&](const P2 &v) -> T { return first ? v.x : fmaT(beta, v.y, v.x); };
+  const Gather<P2> load{rp};
+  auto pv = [&](const P2 &v) -> T { return fmaT(beta, v.y, v.x); };
   Dot2 a;
   A.rows(sm, load, pv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
     T acc = T(0), pi = T(0);
     bool have = false;  // p_i taken from the row's diagonal entry
-    entries([&](int32_t j, T av, T pj) {
-      acc = fmaT(av, pj, acc);
-      if (j == i) {
-        pi = pj;
-        have = true;
-      }
+    entries([&](int32_t j, T av, T pj, bool has = true) {
+      acc = has ? fmaT(av, pj, acc) : acc;
+      const bool own_entry = has && j == i;
+      pi = own_entry ? pj : pi;
+      have = have || own_entry;
     });
     if (valid) {
       st_nt(q + i, acc);
@@ -64,9 +63,8 @@ template <class Op>
 __global__ void __launch_bounds__(kBlock) k_cg_pass1_pairs(Op A, const float2_t *rp, float *q,
                                                            const State *st, Reduce *R) {
   if (st->flag != kRunning) return;
-  const bool first = st->k == 0;
   const float beta = float(st->beta);
-  auto pv = [&](const float2_t &v) -> float { return first ? v.x : fmaT(beta, v.y, v.x); };
+  auto pv = [&](const float2_t &v) -> float { return fmaT(beta, v.y, v.x); };
   Dot2 a;
   A.walk_pairs(rp, [&](int32_t i0, int32_t i1, bool valid0, bool valid1, auto &&entries) {
     float acc0 = 0.0f, acc1 = 0.0f, p0 = 0.0f, p1 = 0.0f;
@@ -153,7 +151,6 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass2(int32_t n, T *__restrict__ 
   } else {
     alpha = T(st->alpha);
   }
-  const bool first = st->k == 0;
   const bool defer = (st->k & 1) == 0;  // x waits for the next iteration
   const T beta = T(st->beta), alpha_x = T(st->alpha_x);
   Dot2 a;
@@ -185,7 +182,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass2(int32_t n, T *__restrict__ 
     for (int h = 0; h < 2; ++h) {
       if (i[h] >= n) continue;
       const T r0 = v[h].x;
-      const T pi = first ? r0 : fmaT(beta, v[h].y, r0);
+      const T pi = fmaT(beta, v[h].y, r0);
       // on odd iterations v.y is p of the deferred even iteration
       if (!defer) st_nt(x + i[h], fmaT(alpha, pi, fmaT(alpha_x, v[h].y, xi[h])));
       const T ri = fmaT(-alpha, qi[h], r0);
@@ -232,14 +229,13 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass2_f32x2(int32_t n, float *__r
                                                            const float *__restrict__ q,
                                                            const State *st, Reduce *R) {
   if (st->flag != kRunning) return;
-  const bool first = st->k == 0;
   const bool defer = (st->k & 1) == 0;  // x waits for the next iteration, as in k_cg_pass2
   const float beta = float(st->beta), alpha = float(st->alpha), alpha_x = float(st->alpha_x);
   Dot2 a;
   // row with r_i, the old p_i, x_i, q_i: returns the new {r_i, p_i}, updates x_i
   // (on odd iterations, with the deferred step of the even one first)
   auto row = [&](float r0, float pold, float &xi, float qi) -> float2_t {
-    const float pi = first ? r0 : fmaT(beta, pold, r0);
+    const float pi = fmaT(beta, pold, r0);
     if (!defer) xi = fmaT(alpha, pi, fmaT(alpha_x, pold, xi));
     float2_t o;
     o.x = fmaT(-alpha, qi, r0);

@@ -31,7 +31,7 @@ __global__ void __launch_bounds__(kBlock) k_cgnb_init(Op A, double2_t *__restric
   Dot2 a;
   A.rows(sm, rj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
     double acc = 0.0;
-    entries([&](int32_t, double av, double v) { acc = fma(av, v, acc); });
+    entries([&](int32_t, double av, double v, bool has = true) { acc = has ? fma(av, v, acc) : acc; });
     if (valid) {
       const double ri = ra[i].x;
       st_nt(p + i, ri);
@@ -65,18 +65,17 @@ __global__ void __launch_bounds__(kBlock) k_cgnb_x(Op A, const double2_t *__rest
   __shared__ typename Op::Smem sm;
   if (st->flag != kRunning) return;
   const double alpha = st->alpha;
-  auto load = [&](int32_t j) -> double2_t { return ra[j]; };
+  const Gather<double2_t> load{ra};
   auto rv = [&](const double2_t &v) -> double { return fma(-alpha, v.y, v.x); };
   Dot2 a;
   A.rows(sm, load, rv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
     double acc = 0.0, ri = 0.0;
     bool have = false;  // r_i taken from the row's diagonal entry
-    entries([&](int32_t j, double av, double rj) {
-      acc = fma(av, rj, acc);
-      if (j == i) {
-        ri = rj;
-        have = true;
-      }
+    entries([&](int32_t j, double av, double rj, bool has = true) {
+      acc = has ? fma(av, rj, acc) : acc;
+      const bool own_entry = has && j == i;
+      ri = own_entry ? rj : ri;
+      have = have || own_entry;
     });
     if (valid) {
       st_nt(w + i, acc);

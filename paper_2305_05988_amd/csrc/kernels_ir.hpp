@@ -9,14 +9,17 @@ namespace its {
 // Outer step: rh = (float)(r/rn), d = 0, rh.rh; then (after the inner CG)
 // x += rn * d in double.
 
-// rh is the first member of the inner {r, p} pairs (stride 2).
+// rh is the first member of the inner {r, p} pairs; p starts as 0.
 __global__ void __launch_bounds__(kBlock) k_ir_scale(int32_t n, const double *__restrict__ r,
-                                                     float *__restrict__ rh, float *__restrict__ d,
+                                                     float2_t *__restrict__ rh, float *__restrict__ d,
                                                      Reduce *R, double rn) {
   Dot2 a;
   for_rows(n, [&](int32_t i) {
     const float v = float(r[i] / rn);
-    rh[2 * int64_t(i)] = v;
+    float2_t o;
+    o.x = v;
+    o.y = 0.0f;
+    rh[i] = o;
     d[i] = 0.0f;
     a.add(double(v), double(v));
   });

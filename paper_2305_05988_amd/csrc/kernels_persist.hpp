@@ -62,12 +62,12 @@ __device__ __forceinline__ void persist_epilogue(const Op &A, typename Op::Smem 
                                                  const GridSync &gs, SyncState &ss, int &buf) {
   grid_arrive(gs, ss);
   if (!grid_wait(gs, ss)) return;
-  auto xj = [&](int32_t j) { return x[j]; };
+  const Gather<double> xj{x};
   auto same = [](double v) { return v; };
   Dot2 a;
   A.rows(sm, xj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
     double acc = 0.0;
-    entries([&](int32_t, double av, double v) { acc = fma(av, v, acc); });
+    entries([&](int32_t, double av, double v, bool has = true) { acc = has ? fma(av, v, acc) : acc; });
     if (valid) {
       const double ri = b[i] - acc;
       a.add(ri, ri);
@@ -99,20 +99,18 @@ __global__ void __launch_bounds__(kBlock) k_cg_persist(Op A, double *x,
   while (ls.flag == kRunning) {
     // SpMV pass: p = r + beta p on the fly, q = A p, p.q
     {
-      const bool first = ls.k == 0;
       const double beta = ls.beta;
-      auto load = [&](int32_t j) -> double2_t { return rp[j]; };
-      auto pv = [&](const double2_t &v) -> double { return first ? v.x : fma(beta, v.y, v.x); };
+      const Gather<double2_t> load{rp};
+      auto pv = [&](const double2_t &v) -> double { return fma(beta, v.y, v.x); };
       Dot2 a;
       A.rows(sm, load, pv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
         double acc = 0.0, pi = 0.0;
         bool have = false;
-        entries([&](int32_t j, double av, double pj) {
-          acc = fma(av, pj, acc);
-          if (j == i) {
-            pi = pj;
-            have = true;
-          }
+        entries([&](int32_t j, double av, double pj, bool has = true) {
+          acc = has ? fma(av, pj, acc) : acc;
+          const bool own_entry = has && j == i;
+          pi = own_entry ? pj : pi;
+          have = have || own_entry;
         });
         if (valid) {
           q[i] = acc;
@@ -129,13 +127,12 @@ __global__ void __launch_bounds__(kBlock) k_cg_persist(Op A, double *x,
     buf ^= 1;
     if (ls.flag != kRunning) break;
     // update pass (own rows): p = r + beta p, r -= alpha q, r.r
-    const bool first = ls.k == 0;
     const double beta = ls.beta, alpha = ls.alpha;
     {
       Dot2 a;
       A.own_rows([&](int32_t i) {
         const double2_t v = rp[i];
-        const double pi = first ? v.x : fma(beta, v.y, v.x);
+        const double pi = fma(beta, v.y, v.x);
         const double ri = fma(-alpha, q[i], v.x);
         double2_t o;
         o.x = ri;
@@ -192,11 +189,11 @@ __global__ void __launch_bounds__(kBlock) k_cgnb_persist(Op A, double *x,
     // split phase: the SpMV on r_j (r_j formed on the fly for every gathered
     // column) overlaps the alpha_n reduction
     {
-      auto load = [&](int32_t j) -> double2_t { return cur[j]; };
+      const Gather<double2_t> load{cur};
       auto rv = [&](const double2_t &v) -> double { return fma(-alpha, v.y, v.x); };
       A.rows(sm, load, rv, [&](int32_t i, bool valid, auto &&entries, auto &&) {
         double acc = 0.0;
-        entries([&](int32_t, double av, double rj) { acc = fma(av, rj, acc); });
+        entries([&](int32_t, double av, double rj, bool has = true) { acc = has ? fma(av, rj, acc) : acc; });
         if (valid) w[i] = acc;
       });
     }
@@ -261,18 +258,17 @@ __global__ void __launch_bounds__(kBlock) k_bicg_persist(Op A, double *x,
       const bool restart = ls.restart;
       const double bet = ls.beta;
       const double rn = restart ? __builtin_sqrt(ls.rho) : 1.0;
-      auto load = [&](int32_t j) -> double2_t { return ru[j]; };
+      const Gather<double2_t> load{ru};
       auto pv = [&](const double2_t &e) -> double { return plain ? e.x : fma(bet, e.y, e.x); };
       Dot2 a;
       A.rows(sm, load, pv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
         double acc = 0.0, pi = 0.0;
         bool have = false;
-        entries([&](int32_t j, double av, double pj) {
-          acc = fma(av, pj, acc);
-          if (j == i) {
-            pi = pj;
-            have = true;
-          }
+        entries([&](int32_t j, double av, double pj, bool has = true) {
+          acc = has ? fma(av, pj, acc) : acc;
+          const bool own_entry = has && j == i;
+          pi = own_entry ? pj : pi;
+          have = have || own_entry;
         });
         if (valid) {
           if (!have) pi = own();
@@ -303,18 +299,17 @@ __global__ void __launch_bounds__(kBlock) k_bicg_persist(Op A, double *x,
     const double alpha = ls.alpha;
     // pass B: s = r - alpha v on the fly, t = A s, t.s and t.t
     {
-      auto load = [&](int32_t j) -> double2_t { return rv[j]; };
+      const Gather<double2_t> load{rv};
       auto sv = [&](const double2_t &e) -> double { return fma(-alpha, e.y, e.x); };
       Dot2 a0, a1;
       A.rows(sm, load, sv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
         double acc = 0.0, si = 0.0;
         bool have = false;
-        entries([&](int32_t j, double av, double sj) {
-          acc = fma(av, sj, acc);
-          if (j == i) {
-            si = sj;
-            have = true;
-          }
+        entries([&](int32_t j, double av, double sj, bool has = true) {
+          acc = has ? fma(av, sj, acc) : acc;
+          const bool own_entry = has && j == i;
+          si = own_entry ? sj : si;
+          have = have || own_entry;
         });
         if (valid) {
           if (!have) si = own();

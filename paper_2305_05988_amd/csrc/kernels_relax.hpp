@@ -18,17 +18,15 @@ __global__ void __launch_bounds__(kBlock) k_jacobi(Op A, const double *__restric
                                                    Reduce *R) {
   __shared__ typename Op::Smem sm;
   if (st->flag != kRunning) return;
-  auto xj = [&](int32_t j) { return xo[j]; };
+  const Gather<double> xj{xo};
   auto same = [](double v) { return v; };
   Dot2 a;
   A.rows(sm, xj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
     double full = 0.0, off = 0.0, diag = 0.0;
-    entries([&](int32_t j, double av, double v) {
-      full = fma(av, v, full);
-      if (j == i)
-        diag = av;
-      else
-        off = fma(av, v, off);
+    entries([&](int32_t j, double av, double v, bool has = true) {
+      full = has ? fma(av, v, full) : full;
+      diag = has && j == i ? av : diag;
+      off = has && j != i ? fma(av, v, off) : off;
     });
     if (valid) {
       const double bi = ld_nt(b + i);
@@ -126,20 +124,18 @@ __global__ void __launch_bounds__(kBlock) k_gs_rows_packed(Op A, const int32_t *
                                                            const State *st, Reduce *R) {
   __shared__ typename Op::Smem sm;
   if (st->flag != kRunning) return;
-  auto xj = [&](int32_t j) { return x[j]; };
+  const Gather<double> xj{x};
   Dot2 a;
   for_tiles(A.n, [&](int32_t r0, int32_t r1) {
     const int32_t p = r0 + int32_t(threadIdx.x);
     const int32_t i = p < r1 ? rows[p] : -1;
     double full = 0.0, off = 0.0, diag = 0.0, xi = 0.0;
-    A.tile_entries(r0, r1, sm, xj, [&](int32_t j, double av, double v) {
-      if (Mode == kGsLagged) full = fma(av, v, full);
-      if (j != i) {
-        off = fma(av, v, off);
-      } else {
-        diag = av;
-        xi = v;
-      }
+    A.tile_entries(r0, r1, sm, xj, [&](int32_t j, double av, double v, bool has = true) {
+      if (Mode == kGsLagged) full = has ? fma(av, v, full) : full;
+      const bool own_entry = has && j == i;
+      off = has && j != i ? fma(av, v, off) : off;
+      diag = own_entry ? av : diag;
+      xi = own_entry ? v : xi;
     });
     const double bi = p < r1 ? b[i] : 0.0;
     if (p < r1) {
@@ -152,7 +148,9 @@ __global__ void __launch_bounds__(kBlock) k_gs_rows_packed(Op A, const int32_t *
     }
     if (Mode == kGsFinal) {
       double f2 = 0.0;
-      A.tile_entries(r0, r1, sm, xj, [&](int32_t, double av, double v) { f2 = fma(av, v, f2); });
+      A.tile_entries(r0, r1, sm, xj, [&](int32_t, double av, double v, bool has = true) {
+        f2 = has ? fma(av, v, f2) : f2;
+      });
       if (p < r1) {
         const double ri = bi - f2;
         a.add(ri, ri);
@@ -238,12 +236,12 @@ __global__ void __launch_bounds__(kBlock) k_gs_check(Op A, const double *__restr
                                                      Reduce *R) {
   __shared__ typename Op::Smem sm;
   if (st->flag != kRunning) return;
-  auto xj = [&](int32_t j) { return x[j]; };
+  const Gather<double> xj{x};
   auto same = [](double v) { return v; };
   Dot2 a;
   A.rows(sm, xj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
     double acc = 0.0;
-    entries([&](int32_t, double av, double v) { acc = fma(av, v, acc); });
+    entries([&](int32_t, double av, double v, bool has = true) { acc = has ? fma(av, v, acc) : acc; });
     if (valid) {
       const double ri = b[i] - acc;
       a.add(ri, ri);

@@ -22,8 +22,11 @@
 // body(i, valid, entries, own) is called by every thread of the block for
 // each row it owns (valid = false for slots past the last row); inside it,
 // entries(consume) calls consume(j, a_ij, x_j) for the row's entries in
-// stored order with x_j = value(load(j)), and own() returns x_i.  entries
-// must be called once per body call, by every thread (the CSR operator
+// stored order with x_j = value(load(j)), and own() returns x_i.  consume
+// takes a fourth argument, true by default: false says that the lane's row
+// lacks the entry, and consume must leave its results as they are by selecting
+// (a branch would let the compiler move the entry's gather behind it).
+// entries must be called once per body call, by every thread (the CSR operator
 // synchronises the block inside it).  The CSR operators walk 1-D tiles; the
 // stencil operator marches 2-D tiles along z with the vector staged in LDS.
 #pragma once
@@ -50,6 +53,15 @@ __host__ __device__ constexpr bool rev_of(const Backwards<Op> &) {
   return true;
 }
 
+// The plain gather of a vector: element j, or element ub + lane with ub
+// wave-uniform (the base then stays in scalar registers).
+template <class P>
+struct Gather {
+  const P *p;
+  __device__ __forceinline__ P operator()(int32_t j) const { return p[j]; }
+  __device__ __forceinline__ P at(int64_t ub, uint32_t lane) const { return (p + ub)[lane]; }
+};
+
 // rows() for the operators that walk 1-D tiles of kBlock rows.
 template <class Op, class Load, class Value, class Body>
 __device__ __forceinline__ void tiled_rows(const Op &A, typename Op::Smem &sm, Load &&load,
@@ -57,8 +69,8 @@ __device__ __forceinline__ void tiled_rows(const Op &A, typename Op::Smem &sm, L
   for_tiles(A.n, [&](int32_t r0, int32_t r1) {
     const int32_t i = r0 + int32_t(threadIdx.x);
     auto entries = [&](auto &&consume) {
-      A.tile_entries(r0, r1, sm, load, [&](int32_t j, auto av, const auto &raw) {
-        consume(j, av, value(raw));
+      A.tile_entries(r0, r1, sm, load, [&](int32_t j, auto av, const auto &raw, bool has = true) {
+        consume(j, av, value(raw), has);
       });
     };
     auto own = [&]() { return value(load(i)); };

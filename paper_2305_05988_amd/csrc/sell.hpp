@@ -454,73 +454,6 @@ __global__ void __launch_bounds__(kBlock) k_sell_width(int32_t count, int32_t nn
   }
 }
 
-// Decides which slices become offset slices (one thread per slice): builds
-// the sorted list of the column offsets of the slice's rows, and if every
-// row is strictly ascending and the list holds exactly w offsets, writes the
-// offsets and lane masks at (sp[s] >> 6) + j and sets the slice's flag in
-// sp[s].  The slots of the slices that keep explicit columns are added to
-// *col_slots.  sp must hold the unflagged slot bases on entry.
-__global__ void __launch_bounds__(kBlock) k_sell_offsets(int32_t count, const int32_t *__restrict__ rp,
-                                                         const int32_t *__restrict__ rows,
-                                                         const int32_t *__restrict__ col, int64_t *sp,
-                                                         int32_t *__restrict__ soff,
-                                                         uint64_t *__restrict__ smask,
-                                                         unsigned long long *col_slots) {
-  const int64_t ns = (int64_t(count) + kSlice - 1) / kSlice;
-  for (int64_t s = int64_t(blockIdx.x) * kBlock + threadIdx.x; s < ns;
-       s += int64_t(gridDim.x) * kBlock) {
-    const int64_t base = sp[s];
-    const int32_t w = int32_t((slice_base(sp[s + 1]) - base) >> 6);
-    if (w == 0) continue;
-    bool ok = w <= kMaxOffsetWidth;
-    int32_t d[kMaxOffsetWidth];
-    int32_t u = 0;
-    const int32_t p0 = int32_t(s * kSlice);
-    const int32_t p1 = int32_t(min(int64_t(count), (s + 1) * kSlice));
-    for (int32_t p = p0; ok && p < p1; ++p) {
-      const int32_t i = rows ? rows[p] : p;
-      for (int32_t e = rp[i]; ok && e < rp[i + 1]; ++e) {
-        if (e > rp[i] && col[e] <= col[e - 1]) {
-          ok = false;
-          break;
-        }
-        const int32_t o = col[e] - i;
-        int32_t at = 0;  // insertion point in the sorted list
-        while (at < u && d[at] < o) ++at;
-        if (at < u && d[at] == o) continue;
-        if (u == w) {
-          ok = false;
-          break;
-        }
-        for (int32_t q = u; q > at; --q) d[q] = d[q - 1];
-        d[at] = o;
-        ++u;
-      }
-    }
-    if (!ok || u != w) {
-      atomicAdd(col_slots, static_cast<unsigned long long>(kSlice) * unsigned(w));
-      continue;
-    }
-    uint64_t m[kMaxOffsetWidth];
-    for (int32_t j = 0; j < w; ++j) m[j] = 0;
-    for (int32_t p = p0; p < p1; ++p) {
-      const int32_t i = rows ? rows[p] : p;
-      int32_t j = 0;
-      for (int32_t e = rp[i]; e < rp[i + 1]; ++e) {
-        // the row's offsets are in the list, in ascending order
-        while (j < w && d[j] != col[e] - i) ++j;
-        if (j < w) m[j] |= uint64_t(1) << (p - p0);
-      }
-    }
-    const int64_t k = base >> 6;
-    for (int32_t j = 0; j < w; ++j) {
-      soff[k + j] = d[j];
-      smask[k + j] = m[j];
-    }
-    sp[s] = base | kOffsetSlice;
-  }
-}
-
 // Scatters the entries of every row (and the padding of every slot past a
 // row's end, including the rows of the last slice beyond n) into the
 // sliced layout; in an offset slice a row's entries go to the positions of
