@@ -267,6 +267,34 @@ __device__ __forceinline__ void block_partial(DD (&v)[ND], Reduce *R, bool rev =
   }
 }
 
+// ------------------------------------------------------- pass to pass
+// A pass of an iteration ends with one partial per block; the scalars that
+// the next pass needs (alpha, beta, the stopping test) are a fixed-order sum
+// of those partials away.  On small grids every block of the next pass forms
+// that sum itself and applies the scalar update to its own copy of the State,
+// so no finishing kernel runs between the passes.  The copies are the same bit
+// for bit; block 0 stores its copy for the pass after.  It stores to another
+// State than the one the blocks read (`out` is never `in`), and the pass's own
+// partials go to other slots than the ones it reads, so a block that starts
+// late finds what the first found.
+struct Pass {
+  const State *in;
+  State *out;                // where the State goes when partials are pending
+  const DD *src[kMaxDots];   // the partials of the pass before
+  int32_t count;             // how many (0: none pending, the State stays where it is)
+  DD *dst[kMaxDots];         // slots of this pass's partials
+};
+
+template <int ND>
+__device__ __forceinline__ void block_partial_to(DD (&v)[ND], DD *const (&dst)[kMaxDots], bool rev = false) {
+  block_reduce<ND>(v);
+  if (threadIdx.x == 0) {
+    const int at = sched_place(rev);
+#pragma unroll
+    for (int d = 0; d < ND; ++d) dst[d][at] = v[d];
+  }
+}
+
 // The partials of a pass with G blocks are finished by one kernel when
 // G <= kFinishOne, else by two: k_finish_group (block b sums first-level
 // partials kGroup*b .. kGroup*b+kGroup-1 into p2[b]) and k_finish_final over
@@ -277,12 +305,16 @@ __device__ __forceinline__ void block_partial(DD (&v)[ND], Reduce *R, bool rev =
 // and cost more than the extra launch.)
 constexpr int kFinishOne = 16 * kBlock;
 
+struct PartialSlots {  // the partials of dot d are at src[d]
+  const DD *src[kMaxDots];
+};
+
 template <int ND>
-__global__ void __launch_bounds__(kBlock) k_finish_group(Reduce *R, int G) {
+__global__ void __launch_bounds__(kBlock) k_finish_group(PartialSlots from, Reduce *R, int G) {
   DD v[ND];
   const int j = blockIdx.x * kGroup + int(threadIdx.x);
 #pragma unroll
-  for (int d = 0; d < ND; ++d) v[d] = (j < G) ? R->p1[d][j] : DD{0.0, 0.0};
+  for (int d = 0; d < ND; ++d) v[d] = (j < G) ? from.src[d][j] : DD{0.0, 0.0};
   block_reduce<ND>(v);
   if (threadIdx.x == 0) {
 #pragma unroll
@@ -291,15 +323,14 @@ __global__ void __launch_bounds__(kBlock) k_finish_group(Reduce *R, int G) {
 }
 
 // One block reduces `count` partials src[d][0 .. count) (thread t adds
-// partials t, t + kBlock, ... in that order), then thread 0 applies Fin (the
-// pass's scalar update) to the totals.  Every thread of the block calls it.
-template <int ND, class Fin>
-__device__ __forceinline__ void finish_in_block(const DD *const (&src)[ND], int count, Fin fin) {
-  DD v[ND];
+// partials t, t + kBlock, ... in that order); the totals are valid in thread
+// 0.  Every thread of the block calls it.
+template <int ND>
+__device__ __forceinline__ void sum_in_block(const DD *const *src, int count, DD (&v)[ND]) {
 #pragma unroll
   for (int d = 0; d < ND; ++d) v[d] = DD{0.0, 0.0};
-  // eight partials per thread in flight at a time, added in the same order
-  constexpr int kU = 8;
+  // four partials per thread in flight at a time, added in the same order
+  constexpr int kU = 4;
   for (int j0 = int(threadIdx.x); j0 < count; j0 += kU * kBlock) {
     DD t[kU][ND];
 #pragma unroll
@@ -311,21 +342,71 @@ __device__ __forceinline__ void finish_in_block(const DD *const (&src)[ND], int 
 #pragma unroll
     for (int u = 0; u < kU; ++u)
 #pragma unroll
-      for (int d = 0; d < ND; ++d) v[d] = dd_add(v[d], t[u][d]);
+      for (int d = 0; d < ND; ++d) v[d] = dd_cascade(v[d], t[u][d]);
   }
   block_reduce<ND>(v);
+}
+
+// Then thread 0 applies Fin (the pass's scalar update) to the totals.
+template <int ND, class Fin>
+__device__ __forceinline__ void finish_in_block(const DD *const (&src)[ND], int count, Fin fin) {
+  DD v[ND];
+  sum_in_block<ND>(src, count, v);
   if (threadIdx.x == 0) fin(v);
 }
 
-// Single block: reduce `count` partials (from p1 if `level` is 1, else p2)
-// and apply Fin to the totals.
+// The same for a pass with nothing pending.  A type of its own, so that the
+// kernels of large grids do not carry the sum (registers and code that cost the
+// packed CG pass on 1.7e6 rows 6 %).
+struct PassPlain {
+  const State *in;
+  DD *dst[kMaxDots];
+};
+
+// Start of a pass: the State it works with into s -- the stored one, or where
+// partials are pending the block's own after Fin.  False: the solve has
+// stopped and the pass does nothing.  Every thread of the block calls it.
 template <int ND, class Fin>
-__global__ void __launch_bounds__(kBlock) k_finish_final(Reduce *R, int count, int level, Fin fin) {
+__device__ __forceinline__ bool pass_begin(const PassPlain &p, State &s, Fin) {
+  s = *p.in;
+  return s.flag == kRunning;
+}
+template <int ND, class Fin>
+__device__ __forceinline__ bool pass_begin(const Pass &p, State &s, Fin fin) {
+  __shared__ State ls;
+  static_assert(sizeof(State) % 4 == 0 && sizeof(State) / 4 <= kBlock, "one word per thread");
+  constexpr int kWords = int(sizeof(State) / 4);
+  const int t = threadIdx.x;
+  if (t < kWords) reinterpret_cast<uint32_t *>(&ls)[t] = reinterpret_cast<const uint32_t *>(p.in)[t];
+  DD v[ND];
+  sum_in_block<ND>(p.src, p.count, v);  // synchronises the block
+  fin.st = &ls;
+  if (t == 0 && fin.active()) fin(v);
+  __syncthreads();
+  if (blockIdx.x == 0 && t < kWords)
+    reinterpret_cast<uint32_t *>(p.out)[t] = reinterpret_cast<const uint32_t *>(&ls)[t];
+  s = ls;
+  return s.flag == kRunning;
+}
+
+// What is pending, applied by one block: before the host reads the State.
+template <int ND, class Fin>
+__global__ void __launch_bounds__(kBlock) k_pass_end(Pass p, Fin fin) {
+  State s;
+  if (p.count > 0) {
+    pass_begin<ND>(p, s, fin);
+  } else if (threadIdx.x < sizeof(State) / 4) {
+    reinterpret_cast<uint32_t *>(p.out)[threadIdx.x] = reinterpret_cast<const uint32_t *>(p.in)[threadIdx.x];
+  }
+}
+
+// Single block: reduce `count` partials and apply Fin to the totals.
+template <int ND, class Fin>
+__global__ void __launch_bounds__(kBlock) k_finish_final(PartialSlots from, int count, Fin fin) {
   if (!fin.active()) return;
-  const DD *src[ND];
-#pragma unroll
-  for (int d = 0; d < ND; ++d) src[d] = level == 1 ? R->p1[d] : R->p2[d];
-  finish_in_block<ND>(src, count, fin);
+  DD v[ND];
+  sum_in_block<ND>(from.src, count, v);
+  if (threadIdx.x == 0) fin(v);
 }
 
 // Blocks of the first finishing level (0 when one kernel finishes).

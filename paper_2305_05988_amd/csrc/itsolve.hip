@@ -229,11 +229,12 @@ struct Run {
   // The finishing kernel(s) of a reducing pass that ran with G blocks.
   template <int ND, class Fin>
   hipError_t finish(Reduce *R, int G, Fin fin) {
+    const PartialSlots p1{{R->p1[0], R->p1[1]}}, p2{{R->p2[0], R->p2[1]}};
     const int nb = finish_grid(G);
-    if (nb == 0) return launch(kClassFinish, k_finish_final<ND, Fin>, 1, R, G, 1, fin);
-    hipError_t e = launch(kClassFinish, k_finish_group<ND>, nb, R, G);
+    if (nb == 0) return launch(kClassFinish, k_finish_final<ND, Fin>, 1, p1, G, fin);
+    hipError_t e = launch(kClassFinish, k_finish_group<ND>, nb, p1, R, G);
     if (e != hipSuccess) return e;
-    return launch(kClassFinish, k_finish_final<ND, Fin>, 1, R, nb, 2, fin);
+    return launch(kClassFinish, k_finish_final<ND, Fin>, 1, p2, nb, fin);
   }
 };
 
@@ -342,16 +343,16 @@ constexpr int kUpdateGrid = 1024;
 
 // A CSR operator's launch that sweeps its tiles backwards (Backwards); the
 // matrix-free operators are launched as they are.
-#define LAUNCH_OP(run, cls, K, rev, grid, op, ...)                                              \
+#define LAUNCH_OP(run, cls, K, rev, grid, pass, op, ...)                                        \
   do {                                                                                        \
     using Op_ = decltype(op);                                                                 \
     if constexpr (GathersPairs<Op_>::value) {                                                 \
       if (rev) {                                                                              \
-        LAUNCH(run, cls, K<Backwards<Op_>>, grid, Backwards<Op_>{op}, __VA_ARGS__);           \
+        LAUNCH_PASS(run, cls, K, (Backwards<Op_>), grid, pass, Backwards<Op_>{op}, __VA_ARGS__); \
         break;                                                                                \
       }                                                                                       \
     }                                                                                         \
-    LAUNCH(run, cls, K<Op_>, grid, op, __VA_ARGS__);                                          \
+    LAUNCH_PASS(run, cls, K, (Op_), grid, pass, op, __VA_ARGS__);                             \
   } while (0)
 
 template <class F>
@@ -419,6 +420,116 @@ its_status with_op32(const its_matrix *A, int dtype, F &&f) {
   }
 }
 
+// ------------------------------------------------------- pass to pass
+
+#define TRY(expr)                      \
+  do {                                 \
+    its_status t_ = (expr);            \
+    if (t_ != ITS_OK) return t_;       \
+  } while (0)
+
+// Most blocks of a pass, and most partials of the pass before it, for which
+// every block of the pass sums the partials itself (Pass, common.hpp) instead of
+// a finishing kernel between the two.  Per iteration, both ways: packed CG 40^3
+// 15.6 -> 12.3 us, 64^3 (1024 blocks) 16.5 -> 13.8; packed BiCGStab 64^3 29.7 ->
+// 25.9, Jacobi 9.4 -> 8.9.  With 2048 blocks and more the sum at the start of
+// every block costs what the kernel did or more (Jacobi 96^3 16.0 -> 21.3).
+constexpr int kFuseBlocks = 1024;
+
+// The passes of one batch of iterations, handing State and partials on.  The
+// batch starts and ends with the State in `base` (where the host reads it);
+// between them it alternates over two States kept in the grid-barrier words,
+// which the launch-per-pass schedule does not use otherwise.
+struct Flow {
+  Run *run;
+  Reduce *R;
+  State *base, *alt[2];
+  State *cur = nullptr;
+  const DD *src[kMaxDots] = {};
+  int32_t count = 0;  // pending partials
+
+  Flow(Run &r, const WS &w, State *at) : run(&r), R(w.R), base(at) {
+    static_assert(2 * sizeof(State) <= sizeof(unsigned long long) * kSyncWords, "two States in the barrier words");
+    alt[0] = reinterpret_cast<State *>(w.sync);
+    alt[1] = alt[0] + 1;
+  }
+  void start() {
+    cur = base;
+    count = 0;
+  }
+  State *other() const { return cur == alt[0] ? alt[1] : alt[0]; }
+  DD *slots(int d, int region) const { return R->p1[d] + region * kFinishOne; }
+
+  // A finishing kernel applies what is pending to the State where it is.
+  template <int ND, class Fin>
+  its_status apply(Fin fin) {
+    fin.st = cur;
+    LAUNCH(*run, kClassFinish, (k_finish_final<ND, Fin>), 1, (PartialSlots{{src[0], src[1]}}), count, fin);
+    count = 0;
+    return ITS_OK;
+  }
+  // The Pass of a kernel of G blocks that applies Fin to ND pending totals;
+  // its partials go to `region` (0 .. 15; a pass never reads the region it
+  // writes).  A grid of more than kFinishOne blocks takes the slots from
+  // region 0 on, and finds nothing pending.
+  template <int ND, class Fin>
+  its_status enter(int G, Fin fin, int region, Pass &p) {
+    if (count > 0 && std::max(G, int(count)) > kFuseBlocks) TRY(apply<ND>(fin));
+    if (G > kFinishOne) region = 0;
+    p = Pass{cur, count > 0 ? other() : nullptr, {src[0], src[1]}, count, {slots(0, region), slots(1, region)}};
+    if (p.out) cur = p.out;
+    count = 0;
+    return ITS_OK;
+  }
+  // That kernel's ND partials are pending from here on.
+  template <int ND>
+  its_status leave(int G, const Pass &p) {
+    return pend<ND>(G, p.dst[0], p.dst[1]);
+  }
+  // Two passes of G blocks each made dot 0's and dot 1's partials, in two
+  // regions: both are pending.
+  its_status join(int G, int region0, int region1) {
+    if (G > kFinishOne) region0 = region1 = 0;
+    return pend<2>(G, slots(0, region0), slots(1, region1));
+  }
+  template <int ND>
+  its_status pend(int G, const DD *p0, const DD *p1) {
+    src[0] = p0;
+    src[1] = p1;
+    count = G;
+    const int nb = finish_grid(G);
+    if (nb == 0) return ITS_OK;
+    LAUNCH(*run, kClassFinish, k_finish_group<ND>, nb, (PartialSlots{{p0, p1}}), R, G);
+    src[0] = R->p2[0];
+    src[1] = R->p2[1];
+    count = nb;
+    return ITS_OK;
+  }
+  // End of the batch: what is pending is applied and the State is back in base.
+  template <int ND, class Fin>
+  its_status end(Fin fin) {
+    if (cur == base) return count > 0 ? apply<ND>(fin) : ITS_OK;
+    LAUNCH(*run, kClassFinish, (k_pass_end<ND, Fin>), 1, (Pass{cur, base, {src[0], src[1]}, count, {nullptr, nullptr}}), fin);
+    start();
+    return ITS_OK;
+  }
+};
+
+// f with the Pass, or with the PassPlain where nothing is pending.
+template <class F>
+its_status with_pass(const Pass &p, F &&f) {
+  if (p.count > 0) return f(p);
+  return f(PassPlain{p.in, {p.dst[0], p.dst[1]}});
+}
+
+// Launches K<template arguments..., type of the pass>(arguments..., pass).
+#define PARENS(...) __VA_ARGS__
+#define LAUNCH_PASS(run, cls, K, targs, grid, pass, ...)                                        \
+  TRY(with_pass(pass, [&](auto ps_) -> its_status {                                             \
+    LAUNCH(run, cls, (K<PARENS targs, decltype(ps_)>), grid, __VA_ARGS__, ps_);                 \
+    return ITS_OK;                                                                              \
+  }))
+
 // ------------------------------------------------------------- polling
 
 its_status poll(Run &run, const State *dev, State *host) {
@@ -442,7 +553,8 @@ int batch_size(const its_options *o, int64_t n) {
 }
 
 // Runs iterations j = j0, j0+1, ... until the device flag leaves kRunning or
-// max_iter iterations were launched; `step(j)` launches iteration j.
+// max_iter iterations were launched; `step(j, first, last)` launches iteration
+// j, the first or last of its batch (the State is read after the last).
 // Graph form of the loop: iterations 0..m-1 (or 1..m with the first run
 // eagerly, for a step whose first iteration differs) are captured once on
 // the handle's stream and replayed, with one poll of the State per replay.
@@ -460,7 +572,7 @@ its_status iterate_graph(Run &run, const State *dev, State *host, int64_t max_it
   }
   int64_t j = 0;
   if (eager_first) {
-    its_status st = step(0);
+    its_status st = step(0, true, true);
     if (st != ITS_OK) return st;
     j = 1;
   }
@@ -478,7 +590,7 @@ its_status iterate_graph(Run &run, const State *dev, State *host, int64_t max_it
     run.s = G.s;
     HIP_TRY(hipStreamBeginCapture(G.s, hipStreamCaptureModeThreadLocal));
     its_status st = ITS_OK;
-    for (int t = 0; t < m && st == ITS_OK; ++t) st = step(j + t);
+    for (int t = 0; t < m && st == ITS_OK; ++t) st = step(j + t, t == 0, t == m - 1);
     hipGraph_t g = nullptr;
     hipError_t e = hipStreamEndCapture(G.s, &g);
     run.s = saved;
@@ -513,7 +625,7 @@ its_status iterate(Run &run, const State *dev, State *host, int64_t max_iter, in
   for (;;) {
     const int64_t todo = std::min<int64_t>(m, max_iter - j);
     for (int64_t t = 0; t < todo; ++t, ++j) {
-      its_status st = step(j);
+      its_status st = step(j, t == 0, t == todo - 1);
       if (st != ITS_OK) return st;
     }
     its_status st = poll(run, dev, host);
@@ -664,25 +776,17 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
   if (flag == kRunning) {
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t) -> its_status {
-        LAUNCH(run, 0, (k_cg_pass1<decltype(op), double>), GA, op, (const double2_t *)rp, q, (const State *)w.st, w.R);
-        // p.q: with two reduction levels the update pass sums the group sums
-        // (at most kGroup) itself instead of a finishing kernel.  It never
-        // reads first-level partials: its own blocks overwrite those with
-        // their r.r partials while others may still be starting.
-        const DD *pq = nullptr;
-        int32_t pqn = 0;
-        if (GA > kFinishOne) {
-          const int nb = finish_grid(GA);
-          LAUNCH(run, kClassFinish, k_finish_group<1>, nb, w.R, GA);
-          pq = reinterpret_cast<const DD *>(reinterpret_cast<const char *>(w.R) + offsetof(Reduce, p2));
-          pqn = nb;
-        } else {
-          FINISH(run, 1, w.R, GA, (FinCg1{w.st}));
-        }
-        LAUNCH(run, 1, (k_cg_pass2<double, GathersPairs<decltype(op)>::value>), G2, n, x, rp, (const double *)q, w.st, w.R, pq, pqn);
-        FINISH(run, 1, w.R, G2, (FinCg2{w.st}));
-        return ITS_OK;
+      Flow f(run, w, w.st);
+      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+        Pass p;
+        if (first) f.start();
+        TRY(f.enter<1>(GA, FinCg2{}, 0, p));
+        LAUNCH_PASS(run, 0, k_cg_pass1, (decltype(op), double), GA, p, op, (const double2_t *)rp, q);
+        TRY(f.leave<1>(GA, p));
+        TRY(f.enter<1>(G2, FinCg1{}, 1, p));
+        LAUNCH_PASS(run, 1, k_cg_pass2, (double, GathersPairs<decltype(op)>::value), G2, p, n, x, rp, (const double *)q);
+        TRY(f.leave<1>(G2, p));
+        return last ? f.end<1>(FinCg2{}) : ITS_OK;
       });
     });
     if (s != ITS_OK) return s;
@@ -730,12 +834,17 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
       if (o->persistent)
         return persist_launch(run, h, k_cgnb_persist<decltype(op)>, GA, w, op, x, ra, w.reg<double2_t>(3), p, wv, b,
                               w.st, w.R);
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t) -> its_status {
-        LAUNCH(run, 0, k_cgnb_x<decltype(op)>, GA, op, (const double2_t *)ra, wv, (const State *)w.st, w.R);
-        FINISH(run, 1, w.R, GA, (FinCgnbX{w.st}));
-        LAUNCH(run, 1, k_cgnb_y<GathersPairs<decltype(op)>::value>, G, n, x, ra, p, (const double *)wv, (const State *)w.st, w.R);
-        FINISH(run, 1, w.R, G, (FinCgnbY{w.st}));
-        return ITS_OK;
+      Flow f(run, w, w.st);
+      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+        Pass ps;
+        if (first) f.start();
+        TRY(f.enter<1>(GA, FinCgnbY{}, 0, ps));
+        LAUNCH_PASS(run, 0, k_cgnb_x, (decltype(op)), GA, ps, op, (const double2_t *)ra, wv);
+        TRY(f.leave<1>(GA, ps));
+        TRY(f.enter<1>(G, FinCgnbX{}, 1, ps));
+        LAUNCH_PASS(run, 1, k_cgnb_y, (GathersPairs<decltype(op)>::value), G, ps, n, x, ra, p, (const double *)wv);
+        TRY(f.leave<1>(G, ps));
+        return last ? f.end<1>(FinCgnbY{}) : ITS_OK;
       });
     });
     if (s != ITS_OK) return s;
@@ -817,20 +926,23 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
         int GA = op.grid();
         if constexpr (PairWalk<decltype(op)>::value)
           if (pairs) GA = op.grid_pairs(A->sell_wmax > 7);
-        return iterate(run, w.st2, h, budget, batch_size(o, n), [&](int64_t) -> its_status {
+        Flow f(run, w, w.st2);
+        return iterate(run, w.st2, h, budget, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+          Pass p;
+          if (first) f.start();
+          TRY(f.enter<1>(GA, FinCg2{}, 0, p));
+          bool done = false;
           if constexpr (PairWalk<decltype(op)>::value)
             if (pairs) {
-              LAUNCH(run, 0, (k_cg_pass1_pairs<decltype(op)>), GA, op, (const float2_t *)rhp, q, (const State *)w.st2, w.R);
-              FINISH(run, 1, w.R, GA, (FinCg1{w.st2}));
-              LAUNCH(run, 1, k_cg_pass2_f32x2<GathersPairs<decltype(op)>::value>, G2, n, d, rhp, (const float *)q, (const State *)w.st2, w.R);
-              FINISH(run, 1, w.R, G2, (FinCg2{w.st2}));
-              return ITS_OK;
+              LAUNCH_PASS(run, 0, k_cg_pass1_pairs, (decltype(op)), GA, p, op, (const float2_t *)rhp, q);
+              done = true;
             }
-          LAUNCH(run, 0, (k_cg_pass1<decltype(op), float>), GA, op, (const float2_t *)rhp, q, (const State *)w.st2, w.R);
-          FINISH(run, 1, w.R, GA, (FinCg1{w.st2}));
-          LAUNCH(run, 1, k_cg_pass2_f32x2<GathersPairs<decltype(op)>::value>, G2, n, d, rhp, (const float *)q, (const State *)w.st2, w.R);
-          FINISH(run, 1, w.R, G2, (FinCg2{w.st2}));
-          return ITS_OK;
+          if (!done) LAUNCH_PASS(run, 0, k_cg_pass1, (decltype(op), float), GA, p, op, (const float2_t *)rhp, q);
+          TRY(f.leave<1>(GA, p));
+          TRY(f.enter<1>(G2, FinCg1{}, 1, p));
+          LAUNCH_PASS(run, 1, k_cg_pass2_f32x2, (GathersPairs<decltype(op)>::value), G2, p, n, d, rhp, (const float *)q);
+          TRY(f.leave<1>(G2, p));
+          return last ? f.end<1>(FinCg2{}) : ITS_OK;
         });
       });
       if (s != ITS_OK) return s;
@@ -891,15 +1003,22 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
         return persist_launch(run, h, k_bicg_persist<decltype(op), false>, GA, w, op, x, ru, rs, p, rv, t, b,
                               w.st, w.R, rt2, paper);
       }
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t) -> its_status {
-        LAUNCH(run, 0, k_bicg_a<decltype(op)>, GA, op, (const double2_t *)ru, rs, p, rv, (const State *)w.st, w.R);
-        FINISH(run, 1, w.R, GA, (FinBicgA{w.st}));
+      Flow f(run, w, w.st);
+      const FinBicgC fc{nullptr, rt2, paper};
+      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+        Pass ps;
+        if (first) f.start();
+        TRY(f.enter<2>(GA, fc, 0, ps));
+        LAUNCH_PASS(run, 0, k_bicg_a, (decltype(op)), GA, ps, op, (const double2_t *)ru, rs, p, rv, fc);
+        TRY(f.leave<1>(GA, ps));
+        TRY(f.enter<1>(GA, FinBicgA{}, 1, ps));
         // backwards: it starts on the {r, v} pairs pass A wrote last
-        LAUNCH_OP(run, 1, k_bicg_b, true, GA, op, (const double2_t *)rv, t, (const State *)w.st, w.R);
-        FINISH(run, 2, w.R, GA, (FinBicgB{w.st}));
-        LAUNCH(run, 2, k_bicg_c<GathersPairs<decltype(op)>::value>, GC, n, x, ru, (const double *)rs, (const double *)p, (const double2_t *)rv, (const double *)t, (const State *)w.st, w.R);
-        FINISH(run, 2, w.R, GC, (FinBicgC{w.st, rt2, paper}));
-        return ITS_OK;
+        LAUNCH_OP(run, 1, k_bicg_b, true, GA, ps, op, (const double2_t *)rv, t);
+        TRY(f.leave<2>(GA, ps));
+        TRY(f.enter<2>(GC, FinBicgB{}, 2, ps));
+        LAUNCH_PASS(run, 2, k_bicg_c, (GathersPairs<decltype(op)>::value), GC, ps, n, x, ru, (const double *)rs, (const double *)p, (const double2_t *)rv, (const double *)t);
+        TRY(f.leave<2>(GC, ps));
+        return last ? f.end<2>(fc) : ITS_OK;
       });
     });
     if (s != ITS_OK) return s;
@@ -943,12 +1062,16 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
   // sweep j tests x_j and forms x_{j+1}: max_iter + 1 launches at most
   s = with_op64(A, [&](auto op) -> its_status {
     const int GA = op.grid();
-    return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j) -> its_status {
+    Flow f(run, w, w.st);
+    return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
       const int a = int(j & 1);
+      Pass p;
+      if (first) f.start();
+      TRY(f.enter<1>(GA, FinJacobi{}, a, p));
       // odd sweeps run backwards: each starts on the x values the previous one wrote last
-      LAUNCH_OP(run, 0, k_jacobi, a == 1, GA, op, b, (const double *)X[a], X[a ^ 1], (const State *)w.st, w.R);
-      FINISH(run, 1, w.R, GA, (FinJacobi{w.st}));
-      return ITS_OK;
+      LAUNCH_OP(run, 0, k_jacobi, a == 1, GA, p, op, b, (const double *)X[a], X[a ^ 1]);
+      TRY(f.leave<1>(GA, p));
+      return last ? f.end<1>(FinJacobi{}) : ITS_OK;
     });
   });
   if (s != ITS_OK) return s;
@@ -997,43 +1120,56 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
     for (int c = 0; c < 2 && c < nc; ++c) count[c] = A->color_off[c + 1] - A->color_off[c];
   // with two colours both half-sweeps' residual partials line up on one grid
   const int G2 = grid_for(std::max(count[0], count[1]));
-  auto sweep = [&](int c, auto mode_tag) -> its_status {
+  Flow f(run, w, w.st);
+  // enters a half-sweep's launch on Gc blocks: with two colours on CSR the red
+  // (final) sweep applies the pending test, elsewhere the first sweep does
+  auto enter = [&](int Gc, bool two, int region, Pass &p) -> its_status {
+    return two ? f.enter<2>(Gc, FinGs2{}, region, p) : f.enter<1>(Gc, FinGs{}, region, p);
+  };
+  auto sweep = [&](int c, int region, auto mode_tag) -> its_status {
     constexpr int M = decltype(mode_tag)::value;
+    Pass p;
     if (A->kind == kCsr) {
       const int32_t beg = A->color_off[c], cnt = A->color_off[c + 1] - beg;
       const int Gc = M == kGsPlain ? grid_for(cnt) : G2;
       if (cnt == 0 && M == kGsPlain) return ITS_OK;
+      TRY(enter(Gc, M != kGsPlain, region, p));
+      if (M == kGsLagged) p.dst[0] = p.dst[1];  // the black partials are the test's dot 1
       if (!A->cpack.empty()) {
         const auto &cp = A->cpack[size_t(c)];
         const int32_t *rows = A->color_rows + beg;
         if (cp.pat.pid) {
           const PatOp<double> op{cp.pat.pid, cp.pat.head, cp.pat.off, cp.pat.mask, cp.pat.val, cnt, rows};
           if (nc == 2 && c == 0)
-            LAUNCH(run, 0, (k_gs_rows_packed<M, Backwards<PatOp<double>>>), Gc, Backwards<PatOp<double>>{op}, rows, b, x, xs, (const State *)w.st, w.R);
+            LAUNCH_PASS(run, 0, k_gs_rows_packed, (M, Backwards<PatOp<double>>), Gc, p, (Backwards<PatOp<double>>{op}), rows, b, x, xs);
           else
-            LAUNCH(run, 0, (k_gs_rows_packed<M, PatOp<double>>), Gc, op, rows, b, x, xs, (const State *)w.st, w.R);
+            LAUNCH_PASS(run, 0, k_gs_rows_packed, (M, PatOp<double>), Gc, p, (op), rows, b, x, xs);
         } else if (!cp.col) {  // every slice an offset slice
           // with two colours the red half-sweeps run backwards: each starts on the rows
           // the black one before it wrote last
           const SellOp<double, double, true> op{cp.sp, cp.col, cp.val, cnt, cp.soff, cp.smask, rows};
           if (nc == 2 && c == 0)
-            LAUNCH(run, 0, (k_gs_rows_packed<M, Backwards<SellOp<double, double, true>>>), Gc, Backwards<SellOp<double, double, true>>{op}, rows, b, x, xs, (const State *)w.st, w.R);
+            LAUNCH_PASS(run, 0, k_gs_rows_packed, (M, Backwards<SellOp<double, double, true>>), Gc, p, (Backwards<SellOp<double, double, true>>{op}), rows, b, x, xs);
           else
-            LAUNCH(run, 0, (k_gs_rows_packed<M, SellOp<double, double, true>>), Gc, op, rows, b, x, xs, (const State *)w.st, w.R);
+            LAUNCH_PASS(run, 0, k_gs_rows_packed, (M, SellOp<double, double, true>), Gc, p, (op), rows, b, x, xs);
         } else {
-          LAUNCH(run, 0, (k_gs_rows_packed<M, SellOp<double, double>>), Gc, SellOp<double, double>{cp.sp, cp.col, cp.val, cnt, cp.soff, cp.smask, rows}, rows, b, x, xs, (const State *)w.st, w.R);
+          LAUNCH_PASS(run, 0, k_gs_rows_packed, (M, SellOp<double, double>), Gc, p, (SellOp<double, double>{cp.sp, cp.col, cp.val, cnt, cp.soff, cp.smask, rows}), rows, b, x, xs);
         }
         return ITS_OK;
       }
-      LAUNCH(run, 0, k_gs_rows_csr<M>, Gc, CsrOp<double, double>{A->rp, A->col, A->val, n}, (const int32_t *)(A->color_rows + beg), cnt, b, x, xs, (const State *)w.st, w.R);
+      LAUNCH_PASS(run, 0, k_gs_rows_csr, (M), Gc, p, (CsrOp<double, double>{A->rp, A->col, A->val, n}), (const int32_t *)(A->color_rows + beg), cnt, b, x, xs);
     } else if (A->kind == kSten7) {
       StencilOp<7, double> op{A->nx, A->ny, A->nz, n, {}};
       for (int q = 0; q < 7; ++q) op.c[q] = A->coef[q];
-      LAUNCH(run, 0, k_gs_stencil<7>, grid_for(gs_colour_cells<7>(A->nx, A->ny, A->nz)), op, (int32_t)c, b, x, (const State *)w.st);
+      const int Gc = grid_for(gs_colour_cells<7>(A->nx, A->ny, A->nz));
+      TRY(enter(Gc, false, region, p));
+      LAUNCH_PASS(run, 0, k_gs_stencil, (7), Gc, p, op, (int32_t)c, b, x);
     } else {
       StencilOp<27, double> op{A->nx, A->ny, A->nz, n, {}};
       for (int q = 0; q < 27; ++q) op.c[q] = A->coef[q];
-      LAUNCH(run, 0, k_gs_stencil<27>, grid_for(gs_colour_cells<27>(A->nx, A->ny, A->nz)), op, (int32_t)c, b, x, (const State *)w.st);
+      const int Gc = grid_for(gs_colour_cells<27>(A->nx, A->ny, A->nz));
+      TRY(enter(Gc, false, region, p));
+      LAUNCH_PASS(run, 0, k_gs_stencil, (27), Gc, p, op, (int32_t)c, b, x);
     }
     return ITS_OK;
   };
@@ -1047,16 +1183,21 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
     // sweep, after which the test runs; so step j (0-based) finishes
     // iterate j's test before making iterate j + 1, and max_iter + 1 steps
     // cover max_iter tests.
-    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j) -> its_status {
-      its_status e;
+    // The red partials (dot 0) of iteration j - 1 and the black ones (dot 1)
+    // of iteration j make the test that iteration j's red sweep applies before
+    // it writes its own red partials: those alternate between two regions.
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+      if (first) f.start();
+      const int red = int(j & 1);
       if (j == 0) {
-        if ((e = sweep(0, Plain{})) != ITS_OK) return e;
-        if ((e = sweep(1, Plain{})) != ITS_OK) return e;
+        TRY(sweep(0, 0, Plain{}));
+        TRY(sweep(1, 0, Plain{}));
       } else {
-        if ((e = sweep(1, Lagged{})) != ITS_OK) return e;
-        FINISH(run, 2, w.R, G2, (FinGs2{w.st}));
+        TRY(sweep(1, 2, Lagged{}));
+        TRY(f.join(G2, red ^ 1, 2));
       }
-      return sweep(0, Final{});
+      TRY(sweep(0, red, Final{}));
+      return last ? f.end<2>(FinGs2{}) : ITS_OK;
     }, /*eager_first=*/true);
     if (s != ITS_OK) return s;
     // the stopping test ran after a black sweep: put the tested black rows back
@@ -1065,18 +1206,15 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
   } else if (flag == kRunning) {
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j) -> its_status {
-        for (int c = (j == 0 ? 0 : 1); c < nc; ++c) {
-          its_status e = sweep(c, Plain{});
-          if (e != ITS_OK) return e;
-        }
-        for (int c = nc - 2; c >= 0; --c) {
-          its_status e = sweep(c, Plain{});
-          if (e != ITS_OK) return e;
-        }
-        LAUNCH(run, 1, k_gs_check<decltype(op)>, GA, op, b, (const double *)x, (const State *)w.st, w.R);
-        FINISH(run, 1, w.R, GA, (FinGs{w.st}));
-        return ITS_OK;
+      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+        if (first) f.start();
+        for (int c = (j == 0 ? 0 : 1); c < nc; ++c) TRY(sweep(c, 2, Plain{}));
+        for (int c = nc - 2; c >= 0; --c) TRY(sweep(c, 2, Plain{}));
+        Pass p;
+        TRY(f.enter<1>(GA, FinGs{}, int(j & 1), p));
+        LAUNCH_PASS(run, 1, k_gs_check, (decltype(op)), GA, p, op, b, (const double *)x);
+        TRY(f.leave<1>(GA, p));
+        return last ? f.end<1>(FinGs{}) : ITS_OK;
       }, /*eager_first=*/true);
     });
     if (s != ITS_OK) return s;
@@ -1838,12 +1976,13 @@ its_status its_dot(int64_t n, const double *x, const double *y, double *result, 
   hipLaunchKernelGGL(k_reset, dim3(1), dim3(kBlock), 0, s, st, 1, R);
   const int G = grid_for(n);
   hipLaunchKernelGGL(k_dot, dim3(G), dim3(kBlock), 0, s, int32_t(n), x, y, R);
+  const PartialSlots p1{{R->p1[0], R->p1[1]}}, p2{{R->p2[0], R->p2[1]}};
   const int nb = finish_grid(G);
   if (nb == 0) {
-    hipLaunchKernelGGL((k_finish_final<1, FinDot>), dim3(1), dim3(kBlock), 0, s, R, G, 1, FinDot{st, 0});
+    hipLaunchKernelGGL((k_finish_final<1, FinDot>), dim3(1), dim3(kBlock), 0, s, p1, G, FinDot{st, 0});
   } else {
-    hipLaunchKernelGGL(k_finish_group<1>, dim3(nb), dim3(kBlock), 0, s, R, G);
-    hipLaunchKernelGGL((k_finish_final<1, FinDot>), dim3(1), dim3(kBlock), 0, s, R, nb, 2, FinDot{st, 0});
+    hipLaunchKernelGGL(k_finish_group<1>, dim3(nb), dim3(kBlock), 0, s, p1, R, G);
+    hipLaunchKernelGGL((k_finish_final<1, FinDot>), dim3(1), dim3(kBlock), 0, s, p2, nb, FinDot{st, 0});
   }
   HIP_TRY(hipGetLastError());
   double v = 0.0;

@@ -40,17 +40,84 @@ struct FinBicgInit {  // alpha_n = r.r'
   __device__ void operator()(DD (&v)[1]) const { st->alpha_n = dd_round(v[0]); }
 };
 
-template <class Op>
+// alpha_d = v.r', alpha = alpha_n / alpha_d; the restart (if any) is consumed.
+struct FinBicgA {
+  State *st;
+  __device__ bool active() const { return st->flag == kRunning; }
+  __device__ void operator()(DD (&v)[1]) const {
+    const double ad = dd_round(v[0]);
+    st->restart = 0;
+    if (ad == 0.0 || !finite(ad)) {
+      st->flag = kBreakdown;
+    } else {
+      st->alpha_d = ad;
+      st->alpha = st->alpha_n / ad;
+    }
+  }
+};
+
+// omega = (t.s) / (t.t), 0 if t.t = 0.
+struct FinBicgB {
+  State *st;
+  __device__ bool active() const { return st->flag == kRunning; }
+  __device__ void operator()(DD (&d)[2]) const {
+    const double ts = dd_round(d[0]), tt = dd_round(d[1]);
+    st->ts = ts;
+    st->tt = tt;
+    st->omega = (tt == 0.0) ? 0.0 : ts / tt;
+  }
+};
+
+// alpha_n' = r.r', beta = r.r; the restart test, then the convergence test
+// (in that order, as the restart count of the returned iterate includes a
+// restart decided in its last iteration).
+struct FinBicgC {
+  State *st;
+  double restart_tol2;
+  int32_t paper_mode;
+  __device__ bool active() const { return st->flag == kRunning; }
+  __device__ void operator()(DD (&d)[2]) const {
+    const double om = st->omega;
+    const bool half = (om == 0.0);
+    const double an = dd_round(d[0]), beta = dd_round(d[1]);
+    const int64_t k = st->k + 1;
+    st->k = k;
+    st->rho = beta;
+    if (half) {
+      st->flag = (beta <= st->thr2) ? kConverged : kBreakdown;
+      return;
+    }
+    const bool want = paper_mode ? (__builtin_fabs(an) < restart_tol2)
+                                 : (an * an < restart_tol2 * beta);
+    if (want && beta > 0.0 && finite(beta)) {
+      st->restart = 1;
+      st->alpha_n = __builtin_sqrt(beta);
+      st->restarts += 1;
+    } else {
+      st->beta = an / (st->alpha_d * om);
+      st->alpha_n = an;
+    }
+    if (beta <= st->thr2)
+      st->flag = kConverged;
+    else if (!finite(beta))
+      st->flag = kBreakdown;
+    else if (k >= st->max_iter)
+      st->flag = kMaxIter;
+  }
+};
+
+template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_bicg_a(Op A, const double2_t *__restrict__ ru,
                                                    double *__restrict__ rs, double *__restrict__ p,
-                                                   double2_t *__restrict__ rv, const State *st,
-                                                   Reduce *R) {
+                                                   double2_t *__restrict__ rv, FinBicgC fin,
+                                                   P ps) {
   __shared__ typename Op::Smem sm;
-  if (st->flag != kRunning) return;
-  const bool plain = st->k == 0 || st->restart;
-  const bool restart = st->restart;
-  const double bet = st->beta;
-  const double rn = restart ? __builtin_sqrt(st->rho) : 1.0;
+  State ls;
+  if (!pass_begin<2>(ps, ls, fin)) return;
+  const bool plain = ls.k == 0 || ls.restart;
+  const bool restart = ls.restart;
+  const double bet = ls.beta;
+  const double rn = restart ? __builtin_sqrt(ls.rho) : 1.0;
   const Gather<double2_t> load{ru};
   auto pv = [&](const double2_t &e) -> double { return plain ? e.x : fma(bet, e.y, e.x); };
   Dot2 a;
@@ -82,32 +149,16 @@ __global__ void __launch_bounds__(kBlock) k_bicg_a(Op A, const double2_t *__rest
     }
   });
   DD v[1] = {a.get()};
-  block_partial<1>(v, R, rev_of(A));
+  block_partial_to<1>(v, ps.dst, rev_of(A));
 }
 
-// alpha_d = v.r', alpha = alpha_n / alpha_d; the restart (if any) is consumed.
-struct FinBicgA {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double ad = dd_round(v[0]);
-    st->restart = 0;
-    if (ad == 0.0 || !finite(ad)) {
-      st->flag = kBreakdown;
-    } else {
-      st->alpha_d = ad;
-      st->alpha = st->alpha_n / ad;
-    }
-  }
-};
-
-template <class Op>
+template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_bicg_b(Op A, const double2_t *__restrict__ rv,
-                                                   double *__restrict__ t, const State *st,
-                                                   Reduce *R) {
+                                                   double *__restrict__ t, P ps) {
   __shared__ typename Op::Smem sm;
-  if (st->flag != kRunning) return;
-  const double alpha = st->alpha;
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinBicgA{})) return;
+  const double alpha = ls.alpha;
   const Gather<double2_t> load{rv};
   auto sv = [&](const double2_t &e) -> double { return fma(-alpha, e.y, e.x); };
   Dot2 a0, a1;
@@ -128,31 +179,19 @@ __global__ void __launch_bounds__(kBlock) k_bicg_b(Op A, const double2_t *__rest
     }
   });
   DD d[2] = {a0.get(), a1.get()};
-  block_partial<2>(d, R, rev_of(A));
+  block_partial_to<2>(d, ps.dst, rev_of(A));
 }
 
-// omega = (t.s) / (t.t), 0 if t.t = 0.
-struct FinBicgB {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&d)[2]) const {
-    const double ts = dd_round(d[0]), tt = dd_round(d[1]);
-    st->ts = ts;
-    st->tt = tt;
-    st->omega = (tt == 0.0) ? 0.0 : ts / tt;
-  }
-};
-
-template <bool Keep>
+template <bool Keep, class P>
 __global__ void __launch_bounds__(kBlock) k_bicg_c(int32_t n, double *__restrict__ x,
                                                    double2_t *__restrict__ ru,
                                                    const double *__restrict__ rs,
                                                    const double *__restrict__ p,
                                                    const double2_t *__restrict__ rv,
-                                                   const double *__restrict__ t, const State *st,
-                                                   Reduce *R) {
-  if (st->flag != kRunning) return;
-  const double alpha = st->alpha, om = st->omega;
+                                                   const double *__restrict__ t, P ps) {
+  State ls;
+  if (!pass_begin<2>(ps, ls, FinBicgB{})) return;
+  const double alpha = ls.alpha, om = ls.omega;
   const bool half = (om == 0.0);
   Dot2 a0, a1;
   // rows i and i + kBlock of each tile of 2 kBlock rows, the loads of both in
@@ -195,45 +234,7 @@ __global__ void __launch_bounds__(kBlock) k_bicg_c(int32_t n, double *__restrict
     }
   }
   DD d[2] = {a0.get(), a1.get()};
-  block_partial<2>(d, R);
+  block_partial_to<2>(d, ps.dst);
 }
-
-// alpha_n' = r.r', beta = r.r; the restart test, then the convergence test
-// (in that order, as the restart count of the returned iterate includes a
-// restart decided in its last iteration).
-struct FinBicgC {
-  State *st;
-  double restart_tol2;
-  int32_t paper_mode;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&d)[2]) const {
-    const double om = st->omega;
-    const bool half = (om == 0.0);
-    const double an = dd_round(d[0]), beta = dd_round(d[1]);
-    const int64_t k = st->k + 1;
-    st->k = k;
-    st->rho = beta;
-    if (half) {
-      st->flag = (beta <= st->thr2) ? kConverged : kBreakdown;
-      return;
-    }
-    const bool want = paper_mode ? (__builtin_fabs(an) < restart_tol2)
-                                 : (an * an < restart_tol2 * beta);
-    if (want && beta > 0.0 && finite(beta)) {
-      st->restart = 1;
-      st->alpha_n = __builtin_sqrt(beta);
-      st->restarts += 1;
-    } else {
-      st->beta = an / (st->alpha_d * om);
-      st->alpha_n = an;
-    }
-    if (beta <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(beta))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
-};
 
 }  // namespace its

@@ -25,15 +25,48 @@ namespace its {
 // stops after an even iteration applies the pending update with k_cg_flush_x
 // (k_cg_flush_x32 for the FP32 inner solve).
 
-template <class Op, class T>
+// alpha = rho / (p.q); p.q = 0 or non-finite is a breakdown.
+struct FinCg1 {
+  State *st;
+  __device__ bool active() const { return st->flag == kRunning; }
+  __device__ void operator()(DD (&v)[1]) const {
+    const double pq = dd_round(v[0]);
+    if (pq == 0.0 || !finite(pq))
+      st->flag = kBreakdown;
+    else
+      st->alpha = st->rho / pq;
+  }
+};
+
+// rho' = r.r, one more iteration, beta = rho'/rho, convergence test.
+struct FinCg2 {
+  State *st;
+  __device__ bool active() const { return st->flag == kRunning; }
+  __device__ void operator()(DD (&v)[1]) const {
+    const double rho_new = dd_round(v[0]);
+    const int64_t k = st->k + 1;
+    if (k & 1) st->alpha_x = st->alpha;  // iteration k - 1 (even) deferred its x update
+    st->k = k;
+    st->beta = rho_new / st->rho;
+    st->rho = rho_new;
+    if (rho_new <= st->thr2)
+      st->flag = kConverged;
+    else if (!finite(rho_new))
+      st->flag = kBreakdown;
+    else if (k >= st->max_iter)
+      st->flag = kMaxIter;
+  }
+};
+
+template <class Op, class T, class P>
 __global__ void __launch_bounds__(kBlock) k_cg_pass1(Op A,
                                                      const typename Pair<T>::type *__restrict__ rp,
-                                                     T *__restrict__ q, const State *st,
-                                                     Reduce *R) {
+                                                     T *__restrict__ q, P ps) {
   __shared__ typename Op::Smem sm;
-  if (st->flag != kRunning) return;
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinCg2{})) return;
   using P2 = typename Pair<T>::type;
-  const T beta = T(st->beta);
+  const T beta = T(ls.beta);
   const Gather<P2> load{rp};
   auto pv = [&](const P2 &v) -> T { return fmaT(beta, v.y, v.x); };
   Dot2 a;
@@ -53,17 +86,18 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass1(Op A,
     }
   });
   DD v[1] = {a.get()};
-  block_partial<1>(v, R, rev_of(A));
+  block_partial_to<1>(v, ps.dst, rev_of(A));
 }
 
 // Pass 1 of the refinement's FP32 inner CG on an FP32/FP16 offset-slice
 // layout, two rows per lane (SellOp::walk_pairs): for each row the
 // arithmetic of k_cg_pass1.  rp must be readable at indices -1 and n.
-template <class Op>
+template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_cg_pass1_pairs(Op A, const float2_t *rp, float *q,
-                                                           const State *st, Reduce *R) {
-  if (st->flag != kRunning) return;
-  const float beta = float(st->beta);
+                                                           P ps) {
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinCg2{})) return;
+  const float beta = float(ls.beta);
   auto pv = [&](const float2_t &v) -> float { return fmaT(beta, v.y, v.x); };
   Dot2 a;
   A.walk_pairs(rp, [&](int32_t i0, int32_t i1, bool valid0, bool valid1, auto &&entries) {
@@ -98,61 +132,19 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass1_pairs(Op A, const float2_t 
     }
   });
   DD v[1] = {a.get()};
-  block_partial<1>(v, R);
+  block_partial_to<1>(v, ps.dst);
 }
 
-// alpha = rho / (p.q); p.q = 0 or non-finite is a breakdown.
-struct FinCg1 {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double pq = dd_round(v[0]);
-    if (pq == 0.0 || !finite(pq))
-      st->flag = kBreakdown;
-    else
-      st->alpha = st->rho / pq;
-  }
-};
-
-// pq, pq_count: when pq is not null, the SpMV pass's p.q as second-level
-// (group) sums, at most kGroup, which every block reduces itself in the
-// finishing kernel's order (finish_in_block) and turns into alpha as FinCg1
-// does -- block 0 records alpha, or the breakdown, in the State -- so no
-// finishing kernel runs between the two passes.  They must not be
-// first-level partials: this pass writes its own partials there.
-template <class T, bool Keep>
+template <class T, bool Keep, class P>
 __global__ void __launch_bounds__(kBlock) k_cg_pass2(int32_t n, T *__restrict__ x,
                                                      typename Pair<T>::type *__restrict__ rp,
-                                                     const T *__restrict__ q, State *st,
-                                                     Reduce *R, const DD *pq, int32_t pq_count) {
+                                                     const T *__restrict__ q, P ps) {
   using P2 = typename Pair<T>::type;
-  if (st->flag != kRunning) return;
-  T alpha;
-  if (pq) {
-    __shared__ double s_alpha;
-    __shared__ int s_ok;
-    const double rho = st->rho;
-    const DD *src[1] = {pq};
-    finish_in_block<1>(src, pq_count, [&](DD (&v)[1]) {
-      const double pqv = dd_round(v[0]);
-      const bool ok = pqv != 0.0 && finite(pqv);
-      s_ok = ok;
-      s_alpha = ok ? rho / pqv : 0.0;
-      if (blockIdx.x == 0) {
-        if (ok)
-          st->alpha = s_alpha;
-        else
-          st->flag = kBreakdown;
-      }
-    });
-    __syncthreads();
-    if (!s_ok) return;  // block-uniform
-    alpha = T(s_alpha);
-  } else {
-    alpha = T(st->alpha);
-  }
-  const bool defer = (st->k & 1) == 0;  // x waits for the next iteration
-  const T beta = T(st->beta), alpha_x = T(st->alpha_x);
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinCg1{})) return;
+  const T alpha = T(ls.alpha);
+  const bool defer = (ls.k & 1) == 0;  // x waits for the next iteration
+  const T beta = T(ls.beta), alpha_x = T(ls.alpha_x);
   Dot2 a;
   // rows i and i + kBlock of each tile of 2 kBlock rows, the loads of both in
   // flight together (a row past n re-reads row n - 1 and stores nothing)
@@ -194,7 +186,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass2(int32_t n, T *__restrict__ 
     }
   }
   DD v[1] = {a.get()};
-  block_partial<1>(v, R);
+  block_partial_to<1>(v, ps.dst);
 }
 
 // After the iterations of an FP64 CG solve: an odd count of completed
@@ -223,14 +215,14 @@ __global__ void __launch_bounds__(kBlock) k_cg_flush_x32(int32_t n, float *__res
 // would halve that and leave the pass instruction-bound).  Row arithmetic is
 // that of k_cg_pass2<float>; the dot partial is exact before its final
 // rounding, so the pairing of rows does not change it.
-template <bool Keep>
+template <bool Keep, class P>
 __global__ void __launch_bounds__(kBlock) k_cg_pass2_f32x2(int32_t n, float *__restrict__ x,
                                                            float2_t *__restrict__ rp,
-                                                           const float *__restrict__ q,
-                                                           const State *st, Reduce *R) {
-  if (st->flag != kRunning) return;
-  const bool defer = (st->k & 1) == 0;  // x waits for the next iteration, as in k_cg_pass2
-  const float beta = float(st->beta), alpha = float(st->alpha), alpha_x = float(st->alpha_x);
+                                                           const float *__restrict__ q, P ps) {
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinCg1{})) return;
+  const bool defer = (ls.k & 1) == 0;  // x waits for the next iteration, as in k_cg_pass2
+  const float beta = float(ls.beta), alpha = float(ls.alpha), alpha_x = float(ls.alpha_x);
   Dot2 a;
   // row with r_i, the old p_i, x_i, q_i: returns the new {r_i, p_i}, updates x_i
   // (on odd iterations, with the deferred step of the even one first)
@@ -271,27 +263,7 @@ __global__ void __launch_bounds__(kBlock) k_cg_pass2_f32x2(int32_t n, float *__r
     rp[i] = o;
   }
   DD v[1] = {a.get()};
-  block_partial<1>(v, R);
+  block_partial_to<1>(v, ps.dst);
 }
-
-// rho' = r.r, one more iteration, beta = rho'/rho, convergence test.
-struct FinCg2 {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double rho_new = dd_round(v[0]);
-    const int64_t k = st->k + 1;
-    if (k & 1) st->alpha_x = st->alpha;  // iteration k - 1 (even) deferred its x update
-    st->k = k;
-    st->beta = rho_new / st->rho;
-    st->rho = rho_new;
-    if (rho_new <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(rho_new))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
-};
 
 }  // namespace its

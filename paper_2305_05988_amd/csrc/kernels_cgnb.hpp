@@ -58,35 +58,6 @@ struct FinCgnbInit {  // alpha_d,0 and alpha_0
   }
 };
 
-template <class Op>
-__global__ void __launch_bounds__(kBlock) k_cgnb_x(Op A, const double2_t *__restrict__ ra,
-                                                   double *__restrict__ w, const State *st,
-                                                   Reduce *R) {
-  __shared__ typename Op::Smem sm;
-  if (st->flag != kRunning) return;
-  const double alpha = st->alpha;
-  const Gather<double2_t> load{ra};
-  auto rv = [&](const double2_t &v) -> double { return fma(-alpha, v.y, v.x); };
-  Dot2 a;
-  A.rows(sm, load, rv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
-    double acc = 0.0, ri = 0.0;
-    bool have = false;  // r_i taken from the row's diagonal entry
-    entries([&](int32_t j, double av, double rj, bool has = true) {
-      acc = has ? fma(av, rj, acc) : acc;
-      const bool own_entry = has && j == i;
-      ri = own_entry ? rj : ri;
-      have = have || own_entry;
-    });
-    if (valid) {
-      st_nt(w + i, acc);
-      if (!have) ri = own();
-      a.add(ri, ri);
-    }
-  });
-  DD v[1] = {a.get()};
-  block_partial<1>(v, R, rev_of(A));
-}
-
 // alpha_n,j; beta and gamma for pass Y.
 struct FinCgnbX {
   State *st;
@@ -98,35 +69,6 @@ struct FinCgnbX {
     st->gamma = (an * an) / (st->alpha_d * an_new);
   }
 };
-
-template <bool Keep>
-__global__ void __launch_bounds__(kBlock) k_cgnb_y(int32_t n, double *__restrict__ x,
-                                                   double2_t *__restrict__ ra,
-                                                   double *__restrict__ p,
-                                                   const double *__restrict__ w, const State *st,
-                                                   Reduce *R) {
-  if (st->flag != kRunning) return;
-  const double alpha = st->alpha, beta = st->beta, gamma = st->gamma;
-  const bool exact = st->alpha_n == 0.0;  // gamma = 1/0: use the limit alpha p_{j-1}
-  Dot2 a;
-  for_rows(n, [&](int32_t i) {
-    const double2_t v = ld_nt(ra + i);
-    const double ri = fma(-alpha, v.y, v.x);
-    const double api = fma(beta, v.y, ld_nt(w + i));
-    const double p_old = ld_nt(p + i);
-    const double pi = fma(beta, p_old, ri);
-    const double xi = ld_nt(x + i);
-    st_nt(x + i, exact ? fma(alpha, p_old, xi) : fma(gamma, pi, fma(-gamma, ri, xi)));
-    st_nt(p + i, pi);
-    double2_t o;
-    o.x = ri;
-    o.y = api;
-    st_pairs<Keep>(ra + i, o);
-    a.add(api, pi);
-  }, Keep);  // backwards with kept pairs: k_cgnb_x starts where this ends
-  DD v[1] = {a.get()};
-  block_partial<1>(v, R, Keep);
-}
 
 // alpha_d,j; one more iteration; the test on alpha_n,j (the residual of the
 // x_j just formed); alpha_j for the next pass X.
@@ -152,5 +94,63 @@ struct FinCgnbY {
     }
   }
 };
+
+template <class Op, class P>
+__global__ void __launch_bounds__(kBlock) k_cgnb_x(Op A, const double2_t *__restrict__ ra,
+                                                   double *__restrict__ w, P ps) {
+  __shared__ typename Op::Smem sm;
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinCgnbY{})) return;
+  const double alpha = ls.alpha;
+  const Gather<double2_t> load{ra};
+  auto rv = [&](const double2_t &v) -> double { return fma(-alpha, v.y, v.x); };
+  Dot2 a;
+  A.rows(sm, load, rv, [&](int32_t i, bool valid, auto &&entries, auto &&own) {
+    double acc = 0.0, ri = 0.0;
+    bool have = false;  // r_i taken from the row's diagonal entry
+    entries([&](int32_t j, double av, double rj, bool has = true) {
+      acc = has ? fma(av, rj, acc) : acc;
+      const bool own_entry = has && j == i;
+      ri = own_entry ? rj : ri;
+      have = have || own_entry;
+    });
+    if (valid) {
+      st_nt(w + i, acc);
+      if (!have) ri = own();
+      a.add(ri, ri);
+    }
+  });
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst, rev_of(A));
+}
+
+template <bool Keep, class P>
+__global__ void __launch_bounds__(kBlock) k_cgnb_y(int32_t n, double *__restrict__ x,
+                                                   double2_t *__restrict__ ra,
+                                                   double *__restrict__ p,
+                                                   const double *__restrict__ w, P ps) {
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinCgnbX{})) return;
+  const double alpha = ls.alpha, beta = ls.beta, gamma = ls.gamma;
+  const bool exact = ls.alpha_n == 0.0;  // gamma = 1/0: use the limit alpha p_{j-1}
+  Dot2 a;
+  for_rows(n, [&](int32_t i) {
+    const double2_t v = ld_nt(ra + i);
+    const double ri = fma(-alpha, v.y, v.x);
+    const double api = fma(beta, v.y, ld_nt(w + i));
+    const double p_old = ld_nt(p + i);
+    const double pi = fma(beta, p_old, ri);
+    const double xi = ld_nt(x + i);
+    st_nt(x + i, exact ? fma(alpha, p_old, xi) : fma(gamma, pi, fma(-gamma, ri, xi)));
+    st_nt(p + i, pi);
+    double2_t o;
+    o.x = ri;
+    o.y = api;
+    st_pairs<Keep>(ra + i, o);
+    a.add(api, pi);
+  }, Keep);  // backwards with kept pairs: k_cgnb_x starts where this ends
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst, Keep);
+}
 
 }  // namespace its

@@ -11,34 +11,6 @@ namespace its {
 // ------------------------------------------------------------------ Jacobi
 // One fused sweep: the residual of x_k (full chain) and x_{k+1} = (b - off)/d.
 // The test applies to x_k, so a converged solve returns x_k from xo.
-template <class Op>
-__global__ void __launch_bounds__(kBlock) k_jacobi(Op A, const double *__restrict__ b,
-                                                   const double *__restrict__ xo,
-                                                   double *__restrict__ xn, const State *st,
-                                                   Reduce *R) {
-  __shared__ typename Op::Smem sm;
-  if (st->flag != kRunning) return;
-  const Gather<double> xj{xo};
-  auto same = [](double v) { return v; };
-  Dot2 a;
-  A.rows(sm, xj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
-    double full = 0.0, off = 0.0, diag = 0.0;
-    entries([&](int32_t j, double av, double v, bool has = true) {
-      full = has ? fma(av, v, full) : full;
-      diag = has && j == i ? av : diag;
-      off = has && j != i ? fma(av, v, off) : off;
-    });
-    if (valid) {
-      const double bi = ld_nt(b + i);
-      const double ri = bi - full;
-      a.add(ri, ri);
-      st_pairs<GathersPairs<Op>::value>(xn + i, (bi - off) / diag);
-    }
-  });
-  DD v[1] = {a.get()};
-  block_partial<1>(v, R, rev_of(A));
-}
-
 // The sweep's residual belongs to x_k: test it; if it fails, x_{k+1} is the
 // new iterate.
 struct FinJacobi {
@@ -59,6 +31,34 @@ struct FinJacobi {
   }
 };
 
+template <class Op, class P>
+__global__ void __launch_bounds__(kBlock) k_jacobi(Op A, const double *__restrict__ b,
+                                                   const double *__restrict__ xo,
+                                                   double *__restrict__ xn, P ps) {
+  __shared__ typename Op::Smem sm;
+  State ls;
+  if (!pass_begin<1>(ps, ls, FinJacobi{})) return;
+  const Gather<double> xj{xo};
+  auto same = [](double v) { return v; };
+  Dot2 a;
+  A.rows(sm, xj, same, [&](int32_t i, bool valid, auto &&entries, auto &&) {
+    double full = 0.0, off = 0.0, diag = 0.0;
+    entries([&](int32_t j, double av, double v, bool has = true) {
+      full = has ? fma(av, v, full) : full;
+      diag = has && j == i ? av : diag;
+      off = has && j != i ? fma(av, v, off) : off;
+    });
+    if (valid) {
+      const double bi = ld_nt(b + i);
+      const double ri = bi - full;
+      a.add(ri, ri);
+      st_pairs<GathersPairs<Op>::value>(xn + i, (bi - off) / diag);
+    }
+  });
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst, rev_of(A));
+}
+
 // ------------------------------------------------------------ Gauss-Seidel
 // Half-sweep over the rows of one colour, in place.  Rows of one colour do
 // not couple, so their updates are independent and the order within the
@@ -68,10 +68,10 @@ struct FinJacobi {
 // first sweeps black then red, and the residual of the iterate it leaves
 // comes from the sweeps themselves instead of a separate SpMV pass:
 //   kGsFinal  (red sweep): after a row's update, its full chain again with
-//             the new value -- the red residual of the new iterate (slot 0);
+//             the new value -- the red residual of the new iterate (dot 0);
 //   kGsLagged (next black sweep): before a row's update, the full chain over
 //             the values it reads anyway -- the black residual of that same
-//             iterate (slot 1) -- and the old value saved to xs, so a solve
+//             iterate (dot 1) -- and the old value saved to xs, so a solve
 //             that stops on this test can put the tested iterate back.
 // Every chain is the SpMV chain (ascending columns, diagonal in place), so
 // r.r equals the separate pass's bit for bit.  (The matrix-free sweeps keep
@@ -79,21 +79,61 @@ struct FinJacobi {
 // chains in the sweeps.)
 enum : int32_t { kGsPlain = 0, kGsFinal = 1, kGsLagged = 2 };
 
-// One dot's block partial into slot d; the other slots are left alone (the
-// red and black residual partials of one test come from two kernels).
-__device__ __forceinline__ void block_partial_at(DD v, int d, Reduce *R, bool rev = false) {
-  DD t[1] = {v};
-  block_reduce<1>(t);
-  if (threadIdx.x == 0) R->p1[d][sched_place(rev)] = t[0];
+// The test after a lagged black sweep: r.r of the iterate = red part (dot 0,
+// from the red sweep that made it) + black part (dot 1).
+struct FinGs2 {
+  State *st;
+  __device__ bool active() const { return st->flag == kRunning; }
+  __device__ void operator()(DD (&v)[2]) const {
+    const double rr = dd_round(dd_add(v[0], v[1]));
+    const int64_t k = st->k + 1;
+    st->k = k;
+    st->rho = rr;
+    if (rr <= st->thr2)
+      st->flag = kConverged;
+    else if (!finite(rr))
+      st->flag = kBreakdown;
+    else if (k >= st->max_iter)
+      st->flag = kMaxIter;
+  }
+};
+
+// Residual of x_{k+1} after a symmetric iteration, and the test.
+struct FinGs {
+  State *st;
+  __device__ bool active() const { return st->flag == kRunning; }
+  __device__ void operator()(DD (&v)[1]) const {
+    const double rr = dd_round(v[0]);
+    const int64_t k = st->k + 1;
+    st->k = k;
+    st->rho = rr;
+    if (rr <= st->thr2)
+      st->flag = kConverged;
+    else if (!finite(rr))
+      st->flag = kBreakdown;
+    else if (k >= st->max_iter)
+      st->flag = kMaxIter;
+  }
+};
+
+// A half-sweep's start: the first of an iteration applies the pending test
+// (FinGs2 with two colours on CSR, FinGs elsewhere), the others have none.
+template <bool Two, class P>
+__device__ __forceinline__ bool gs_begin(const P &ps, State &ls) {
+  if constexpr (Two)
+    return pass_begin<2>(ps, ls, FinGs2{});
+  else
+    return pass_begin<1>(ps, ls, FinGs{});
 }
 
-template <int Mode>
+template <int Mode, class P>
 __global__ void __launch_bounds__(kBlock) k_gs_rows_csr(CsrOp<double, double> A,
                                                         const int32_t *__restrict__ rows,
                                                         int32_t count, const double *__restrict__ b,
                                                         double *x, double *__restrict__ xs,
-                                                        const State *st, Reduce *R) {
-  if (st->flag != kRunning) return;
+                                                        P ps) {
+  State ls;
+  if (!gs_begin<Mode != kGsPlain>(ps, ls)) return;
   Dot2 a;
   for_rows(count, [&](int32_t t) {
     const int32_t i = rows[t];
@@ -112,18 +152,22 @@ __global__ void __launch_bounds__(kBlock) k_gs_rows_csr(CsrOp<double, double> A,
       a.add(ri, ri);
     }
   });
-  if (Mode != kGsPlain) block_partial_at(a.get(), Mode == kGsFinal ? 0 : 1, R);
+  if (Mode != kGsPlain) {
+    DD v[1] = {a.get()};
+    block_partial_to<1>(v, ps.dst);
+  }
 }
 
 // The same half-sweep over a colour's rows in their own packed layout (row p
 // of the layout is rows[p]), so the entries stream coalesced.
-template <int Mode, class Op>
+template <int Mode, class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_gs_rows_packed(Op A, const int32_t *__restrict__ rows,
                                                            const double *__restrict__ b, double *x,
                                                            double *__restrict__ xs,
-                                                           const State *st, Reduce *R) {
+                                                           P ps) {
   __shared__ typename Op::Smem sm;
-  if (st->flag != kRunning) return;
+  State ls;
+  if (!gs_begin<Mode != kGsPlain>(ps, ls)) return;
   const Gather<double> xj{x};
   Dot2 a;
   for_tiles(A.n, [&](int32_t r0, int32_t r1) {
@@ -157,7 +201,10 @@ __global__ void __launch_bounds__(kBlock) k_gs_rows_packed(Op A, const int32_t *
       }
     }
   }, rev_of(A));
-  if (Mode != kGsPlain) block_partial_at(a.get(), Mode == kGsFinal ? 0 : 1, R, rev_of(A));
+  if (Mode != kGsPlain) {
+    DD v[1] = {a.get()};
+    block_partial_to<1>(v, ps.dst, rev_of(A));
+  }
 }
 
 // Matrix-free half-sweep over one colour's cells, walked on a compact index
@@ -170,11 +217,12 @@ __host__ __device__ inline int64_t gs_colour_cells(int32_t nx, int32_t ny, int32
   return NPTS == 7 ? hx * ny * nz : hx * ((ny + 1) / 2) * ((nz + 1) / 2);
 }
 
-template <int NPTS>
+template <int NPTS, class P>
 __global__ void __launch_bounds__(kBlock) k_gs_stencil(StencilOp<NPTS, double> A, int32_t color,
                                                        const double *__restrict__ b, double *x,
-                                                       const State *st) {
-  if (st->flag != kRunning) return;
+                                                       P ps) {
+  State ls;
+  if (!gs_begin<false>(ps, ls)) return;
   const int32_t hx = (A.nx + 1) / 2;
   const int32_t hy = NPTS == 7 ? A.ny : (A.ny + 1) / 2;
   const int32_t cells = int32_t(gs_colour_cells<NPTS>(A.nx, A.ny, A.nz));
@@ -210,32 +258,13 @@ __global__ void __launch_bounds__(kBlock) k_gs_restore_rows(const int32_t *__res
   for_rows(count, [&](int32_t p) { x[rows[p]] = xs[p]; });
 }
 
-// The test after a lagged black sweep: r.r of the iterate = red part (slot 0,
-// from the red sweep that made it) + black part (slot 1).
-struct FinGs2 {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[2]) const {
-    const double rr = dd_round(dd_add(v[0], v[1]));
-    const int64_t k = st->k + 1;
-    st->k = k;
-    st->rho = rr;
-    if (rr <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(rr))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
-};
-
 // Residual of the iterate after a full symmetric iteration, and the test.
-template <class Op>
+template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_gs_check(Op A, const double *__restrict__ b,
-                                                     const double *__restrict__ x, const State *st,
-                                                     Reduce *R) {
+                                                     const double *__restrict__ x, P ps) {
   __shared__ typename Op::Smem sm;
-  if (st->flag != kRunning) return;
+  State ls;
+  if (!gs_begin<false>(ps, ls)) return;
   const Gather<double> xj{x};
   auto same = [](double v) { return v; };
   Dot2 a;
@@ -248,25 +277,7 @@ __global__ void __launch_bounds__(kBlock) k_gs_check(Op A, const double *__restr
     }
   });
   DD v[1] = {a.get()};
-  block_partial<1>(v, R, rev_of(A));
+  block_partial_to<1>(v, ps.dst, rev_of(A));
 }
-
-// Residual of x_{k+1} after a symmetric iteration, and the test.
-struct FinGs {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double rr = dd_round(v[0]);
-    const int64_t k = st->k + 1;
-    st->k = k;
-    st->rho = rr;
-    if (rr <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(rr))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
-};
 
 }  // namespace its
