@@ -40,7 +40,8 @@ METRIC = "CG iters/s + achieved HBM GB/s, 256^3 Poisson; mixed-prec vs FP64 at 1
 KERNEL_SOURCES = ["paper_2305_05988_amd/csrc/common.hpp", "paper_2305_05988_amd/csrc/rowops.hpp",
                   "paper_2305_05988_amd/csrc/csr.hpp", "paper_2305_05988_amd/csrc/sell.hpp",
                   "paper_2305_05988_amd/csrc/pattern.hpp",
-                  "paper_2305_05988_amd/csrc/kernels_cg.hpp"]
+                  "paper_2305_05988_amd/csrc/kernels_cg.hpp",
+                  "paper_2305_05988_amd/csrc/grid.hpp", "paper_2305_05988_amd/csrc/grid.hip"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cg_pass1_poisson256_traffic.txt")
 # Inside the timed region every PROFILE_EVERY-th launch of each kernel is
 # bracketed by HIP events: enough samples for the per-launch average, few
@@ -210,13 +211,19 @@ def main():
     #   pass 2: r, p, q read and r, p written every iteration, x read and
     #           written every other iteration (its update is deferred by one
     #           iteration): 6V on average.
+    # A matrix found to be a stencil on a grid is swept plane by plane with
+    # nothing read but its coefficients:
+    #   pass 1: r, p read, p' written (3V);
+    #   pass 2: p', r read and r written every iteration (A p' is formed
+    #           again), x and p read and x written every other: 4.5V on average.
     # The CSR-equivalent figure (int32 columns and row pointers, as if the CSR
     # arrays were streamed) is kept under its own keys.
     M_csr = csr_bytes(n, nnz)
     M = packed_matrix_bytes(A, n)
     col_slots = A.packed_column_slots
     bytes_pass1 = M + 3 * V
-    bytes_pass2 = 6 * V
+    plane_sweep = bool(slots) and M <= 27 * 8
+    bytes_pass2 = int(4.5 * V) if plane_sweep else 6 * V
     bytes_iter = bytes_pass1 + bytes_pass2
     csr_bytes_iter = M_csr + 10 * V
 
@@ -247,7 +254,8 @@ def main():
     sha = kernel_source_sha()
     traffic = measured_traffic(sha)
     kname = "packed CSR" if slots else "CSR"
-    roof = {"bound": "hbm", "kernel": f"k_cg_pass1 ({kname} SpMV + p.q)",
+    roof = {"bound": "hbm", "kernel": "k_grid_cg_a (plane sweep of the packed CSR, p' and p'.A p')" if plane_sweep
+            else f"k_cg_pass1 ({kname} SpMV + p.q)",
             "achieved": bytes_pass1 / avg1 / 1e9, "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": bytes_pass1 / avg1 / 1e9 / HBM_PEAK_GBS, "traffic": traffic,
             "algorithmic_bytes_per_launch": bytes_pass1, "avg_launch_us": avg1 * 1e6,
@@ -255,7 +263,7 @@ def main():
             "layout_column_slots": col_slots, "layout_slots": slots,
             "csr_equivalent_bytes_per_launch": M_csr + 3 * V,
             "csr_equivalent_gbs": (M_csr + 3 * V) / avg1 / 1e9,
-            "update_pass": {"kernel": "k_cg_pass2", "avg_launch_us": avg2 * 1e6,
+            "update_pass": {"kernel": "k_grid_cg_b" if plane_sweep else "k_cg_pass2", "avg_launch_us": avg2 * 1e6,
                             "bytes_per_launch_avg": bytes_pass2,
                             "achieved": bytes_pass2 / avg2 / 1e9,
                             "frac": bytes_pass2 / avg2 / 1e9 / HBM_PEAK_GBS}}
@@ -268,7 +276,8 @@ def main():
         "config": {"workload": f"poisson7_{N}^3_csr_fp64_cg_rtol{args.rtol:g}", "n": n,
                    "nnz": nnz, "x_star": "U[-1,1) seed 1", "b": "A x*", "x0": 0,
                    "iters_per_solve": info.iters,
-                   "device_layout": ("sliced ELLPACK, 64-row slices (its_csr_pack), "
+                   "device_layout": ("packed (its_csr_pack): found to be a 7-point stencil on a grid"
+                                    if plane_sweep else "sliced ELLPACK, 64-row slices (its_csr_pack), "
                                      f"{slots} slots, {col_slots} of them with column "
                                      "indices" if slots else "CSR")},
         "achieved_gbs": its_per_s * bytes_iter / 1e9,

@@ -172,7 +172,10 @@ its_status its_csr_set_lowp(its_matrix *A, const void *val_lo, int32_t dtype);
    value (in every precision packed), the layout keeps no entries at all: a
    pattern (offsets, lane masks, values) is stored once however many slices
    have it, and each slice stores its pattern's number.  Constant-coefficient
-   operators on structured grids pack this way, whatever their sides.
+   operators on structured grids pack this way, whatever their sides.  A matrix
+   that is exactly a 7- or 27-point stencil with constant finite coefficients on
+   a grid of at least 786,432 points (the neighbours outside it omitted) is
+   then applied as that stencil; the results are the same bit for bit.
    The packed copy (col, val and any low-precision values attached with
    its_csr_set_lowp, which must come first) is allocated and owned by the
    handle and freed by its_matrix_destroy or the next its_csr_pack; it is a
@@ -221,7 +224,8 @@ int64_t its_csr_packed_column_slots(const its_matrix *A);
 
 /* Bytes of the matrix that one pass over the packed layout reads with values
    of `dtype` (ITS_F64, ITS_F32, ITS_F16): values, columns, slice descriptors
-   and offsets, or the pattern numbers and the pattern table; 0 if not packed.
+   and offsets, or the pattern numbers and the pattern table, or the coefficients
+   of the stencil that the matrix was found to be; 0 if not packed.
    (A pass of the methods of Section 3.1 reads the matrix once.) */
 int64_t its_csr_packed_bytes(const its_matrix *A, int32_t dtype);
 
@@ -274,8 +278,10 @@ its_status its_varcoef_grad(const its_matrix *A, const double *x, const double *
 its_status its_matrix_destroy(its_matrix *A);
 int64_t its_matrix_rows(const its_matrix *A);
 
-/* Brick plan of a matrix-free operator's SpMV sweep (the 7- and 27-point
-   stencils of Section 3.1 and the variable-coefficient operator): plan (host,
+/* Brick plan of a matrix-free operator (the 7- and 27-point stencils of Section
+   3.1 and the variable-coefficient operator) for the passes that march bricks:
+   those of small grids and of the persistent kernels (constant stencils on
+   grids of 786,432 points and more are swept in tiles of their own): plan (host,
    4 int32, out) = x tiles of 64 points, y tiles of 4 points, z chunks, and
    the z planes per chunk (the last chunk may hold fewer).  A block marches
    one (x tile, y tile, z chunk) brick plane by plane.  Depends only on the

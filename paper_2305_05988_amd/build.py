@@ -11,11 +11,11 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libitsolve.so")
-SOURCES = [os.path.join(HERE, "csrc", "itsolve.hip"), os.path.join(HERE, "csrc", "batch.hip")]
+SOURCES = [os.path.join(HERE, "csrc", name + ".hip") for name in ("itsolve", "batch", "grid")]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
-    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC", "-shared",
+    "--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
     "-ffp-contract=off", "-fno-fast-math",
     "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
     "-Wall", "-Wno-unused-result",
@@ -24,10 +24,18 @@ FLAGS = [
 
 
 def build(verbose: bool = False) -> str:
-    cmd = [HIPCC] + FLAGS + SOURCES + ["-o", LIB + ".tmp"]
+    """Compiles the sources side by side and links them."""
+    objects = [src[:-len(".hip")] + ".o" for src in SOURCES]
+    compiles = [[HIPCC] + FLAGS + ["-c", src, "-o", obj] for src, obj in zip(SOURCES, objects)]
+    link = [HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared"] + objects + ["-o", LIB + ".tmp"]
     if verbose:
-        print(" ".join(cmd), flush=True)
-    subprocess.run(cmd, check=True)
+        for cmd in compiles + [link]:
+            print(" ".join(cmd), flush=True)
+    running = [subprocess.Popen(cmd) for cmd in compiles]
+    for cmd, status in [(cmd, p.wait()) for cmd, p in zip(compiles, running)]:
+        if status != 0:
+            raise subprocess.CalledProcessError(status, cmd)
+    subprocess.run(link, check=True)
     os.replace(LIB + ".tmp", LIB)
     return LIB
 

@@ -30,7 +30,7 @@ struct alignas(256) State {
   int32_t restart;    // BiCGStab: the next A p pass starts from a restart
   int64_t k;          // completed iterations
   int32_t restarts;   // BiCGStab restarts so far
-  int32_t pad;
+  int32_t plain;      // BiCGStab: this iteration's p is r (first, or after a restart)
   uint32_t counter[8];// flags and counters of the setup checks (counter[7]: rows without a diagonal)
   double rho;         // r.r of the current iterate (CG); beta = r.r (BiCGStab)
   double alpha;       // step length

@@ -1,0 +1,389 @@
+// The passes of constant stencils on large grids: kernels and launches.
+#include <hip/hip_runtime.h>
+
+#include <type_traits>
+
+#include "grid.hpp"
+
+namespace its {
+
+struct None {};
+
+// Accesses to a row's own entries, which no other block wants soon.  Stream:
+// past the caches, for solves whose vectors do not fit the 256 MB memory-side
+// cache (grid_run); the others keep what they store and find it there.
+template <bool Stream, class T>
+__device__ __forceinline__ T ld(const T *p) {
+  if constexpr (Stream)
+    return ld_nt(p);
+  else
+    return *p;
+}
+template <bool Stream, class T>
+__device__ __forceinline__ void st(T *p, T v) {
+  if constexpr (Stream)
+    st_nt(p, v);
+  else
+    *p = v;
+}
+
+// Loads of one vector and of two.
+template <class T>
+struct One {
+  const T *p;
+  __device__ __forceinline__ T at(int64_t ub, uint32_t off) const { return (p + ub)[off]; }
+};
+template <class T>
+struct Two {
+  struct Raw {
+    T a, b;
+  };
+  const T *a, *b;
+  __device__ __forceinline__ Raw at(int64_t ub, uint32_t off) const { return {(a + ub)[off], (b + ub)[off]}; }
+};
+
+struct Same {
+  template <class T>
+  __device__ __forceinline__ T operator()(T v) const { return v; }
+};
+struct KeepValue {
+  template <class Raw, class T>
+  __device__ __forceinline__ T operator()(const Raw &, T v) const { return v; }
+};
+struct KeepNone {
+  template <class Raw, class T>
+  __device__ __forceinline__ None operator()(const Raw &, T) const { return {}; }
+};
+
+// y = A x
+template <class Op>
+__global__ void __launch_bounds__(kBlock) k_grid_spmv(Op A, const double *__restrict__ x, double *__restrict__ y) {
+  __shared__ typename Op::SweepSmem sm;
+  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Same{}, KeepNone{}, [](int32_t) { return None{}; },
+                                     [&](int32_t i, const ChainSum<double> &q, None, None) { st_nt(y + i, q.s); });
+}
+
+// r = b - A x (stored where r is not null, with zeros in `zero`) and r.r
+template <class Op>
+__global__ void __launch_bounds__(kBlock) k_grid_residual(Op A, const double *__restrict__ b,
+                                                          const double *__restrict__ x, double *__restrict__ r,
+                                                          double *__restrict__ zero, DD *dst) {
+  __shared__ typename Op::SweepSmem sm;
+  Dot2 a;
+  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Same{}, KeepNone{}, [&](int32_t i) { return ld_nt(b + i); },
+                                     [&](int32_t i, const ChainSum<double> &q, None, double bi) {
+                                       const double ri = bi - q.s;
+                                       if (r) st_nt(r + i, ri);
+                                       if (zero) st_nt(zero + i, 0.0);
+                                       a.add(ri, ri);
+                                     });
+  DD v[1] = {a.get()};
+  DD *const to[kMaxDots] = {dst, nullptr};
+  block_partial_to<1>(v, to);
+}
+
+// The same without r, for the test after a Gauss-Seidel iteration.
+template <class Op>
+__global__ void __launch_bounds__(kBlock) k_grid_check(Op A, const double *__restrict__ b,
+                                                       const double *__restrict__ x, PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  Dot2 a;
+  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Same{}, KeepNone{}, [&](int32_t i) { return b[i]; },
+                                     [&](int32_t, const ChainSum<double> &q, None, double bi) {
+                                       const double ri = bi - q.s;
+                                       a.add(ri, ri);
+                                     });
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst);
+}
+
+// A Jacobi sweep (k_jacobi): the residual of x, and xn = (b - off) / diag.
+template <class Op, bool S>
+__global__ void __launch_bounds__(kBlock) k_grid_jacobi(Op A, const double *__restrict__ b,
+                                                        const double *__restrict__ x, double *__restrict__ xn,
+                                                        PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  const double diag = A.centre();
+  Dot2 a;
+  A.template sweep<ChainSplit>(sm, One<double>{x}, Same{}, KeepNone{}, [&](int32_t i) { return ld<S>(b + i); },
+                               [&](int32_t i, const ChainSplit &q, None, double bi) {
+                                 const double ri = bi - q.s;
+                                 a.add(ri, ri);
+                                 xn[i] = (bi - q.off) / diag;  // the next sweep's x
+                               });
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst);
+}
+
+// CG in 7.5 vectors an iteration (the pair form of k_cg_pass1 and k_cg_pass2
+// moves 9): with the operator for free, A p costs less to form twice than to
+// store and load.
+//   pass a: p' = r + beta p formed for every point loaded and stored for the
+//           block's own, p'.(A p')
+//   pass b: q = A p' again, r -= alpha q, r.r; every other iteration x with
+//           both iterations' steps
+// p and p' are two buffers: other blocks still load p while p' is stored.  The
+// roundings are k_cg_pass1's and k_cg_pass2's.
+template <class Op, class T, bool S>
+__global__ void __launch_bounds__(kBlock) k_grid_cg_a(Op A, const T *__restrict__ r, const T *__restrict__ p,
+                                                      T *__restrict__ pn, PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  const T beta = T(ps.in->beta);
+  Dot2 a;
+  A.template sweep<ChainSum<T>>(sm, Two<T>{r, p}, [&](const typename Two<T>::Raw &v) { return fmaT(beta, v.b, v.a); },
+                                KeepValue{}, [](int32_t) { return None{}; },
+                                [&](int32_t i, const ChainSum<T> &q, T pi, None) {
+                                  st<S>(pn + i, pi);
+                                  a.add(double(pi), double(q.s));
+                                });
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst);
+}
+
+template <class Op, class T, bool S>
+__global__ void __launch_bounds__(kBlock) k_grid_cg_b(Op A, const T *__restrict__ pn, const T *__restrict__ p,
+                                                      T *__restrict__ r, T *__restrict__ x, PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  const bool defer = (ps.in->k & 1) == 0;  // x waits for the next iteration
+  const T alpha = T(ps.in->alpha), alpha_x = T(ps.in->alpha_x);
+  Dot2 a;
+  struct Own {
+    T r, x, p;
+  };
+  auto run = [&](auto later) {
+    constexpr bool kLater = decltype(later)::value;
+    A.template sweep<ChainSum<T>>(sm, One<T>{pn}, Same{}, KeepValue{},
+                                  [&](int32_t i) {
+                                    if constexpr (kLater)
+                                      return ld<S>(r + i);
+                                    else
+                                      return Own{ld<S>(r + i), ld<S>(x + i), ld<S>(p + i)};
+                                  },
+                                  [&](int32_t i, const ChainSum<T> &q, T pi, const auto &o) {
+                                    T ri;
+                                    if constexpr (kLater) {
+                                      ri = fmaT(-alpha, q.s, o);
+                                    } else {
+                                      st<S>(x + i, fmaT(alpha, pi, fmaT(alpha_x, o.p, o.x)));
+                                      ri = fmaT(-alpha, q.s, o.r);
+                                    }
+                                    st<S>(r + i, ri);
+                                    a.add(double(ri), double(ri));
+                                  });
+  };
+  if (defer)
+    run(std::true_type());
+  else
+    run(std::false_type());
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst);
+}
+
+// Pass X of CG-NB (k_cgnb_x).
+template <class Op>
+__global__ void __launch_bounds__(kBlock) k_grid_cgnb_x(Op A, const double2_t *__restrict__ ra,
+                                                        double *__restrict__ w, PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  const double alpha = ps.in->alpha;
+  Dot2 a;
+  A.template sweep<ChainSum<double>>(sm, One<double2_t>{ra}, [&](const double2_t &v) { return fma(-alpha, v.y, v.x); },
+                                     KeepValue{}, [](int32_t) { return None{}; },
+                                     [&](int32_t i, const ChainSum<double> &q, double ri, None) {
+                                       st_nt(w + i, q.s);
+                                       a.add(ri, ri);
+                                     });
+  DD v[1] = {a.get()};
+  block_partial_to<1>(v, ps.dst);
+}
+
+// BiCGStab in 14 vectors an iteration (the pair form, kernels_bicgstab.hpp,
+// moves 18): t = A s is formed twice instead of stored, and p, which is
+// r + beta u, where it is needed.
+//   pass a: p for every point loaded, v = A p, v.r'
+//   pass b: s = r - alpha v for every point loaded, t = A s, t.s, t.t
+//   pass c: s and t again, x, r, u = p - omega v, r.r', r.r
+// r alternates between two buffers: pass c stores its own rows' new r while
+// other blocks load the old one.  The roundings are the pair form's.
+template <class Op, bool S>
+__global__ void __launch_bounds__(kBlock) k_grid_bicg_a(Op A, const double *__restrict__ r,
+                                                        const double *__restrict__ u, double *__restrict__ rs,
+                                                        double *__restrict__ v, PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  const bool restart = ps.in->restart != 0, plain = ps.in->k == 0 || restart;
+  const double bet = ps.in->beta;
+  const double rn = restart ? __builtin_sqrt(ps.in->rho) : 1.0;
+  using Raw = Two<double>::Raw;
+  Dot2 a;
+  A.template sweep<ChainSum<double>>(sm, Two<double>{r, u},
+                                     [&](const Raw &e) { return plain ? e.a : fma(bet, e.b, e.a); },
+                                     [](const Raw &e, double) { return e.a; }, [&](int32_t i) { return ld<S>(rs + i); },
+                                     [&](int32_t i, const ChainSum<double> &q, double ri, double rsi) {
+                                       st<S>(v + i, q.s);
+                                       if (restart) {
+                                         rsi = ri / rn;
+                                         rs[i] = rsi;
+                                       }
+                                       a.add(q.s, rsi);
+                                     });
+  DD d[1] = {a.get()};
+  block_partial_to<1>(d, ps.dst);
+}
+
+template <class Op>
+__global__ void __launch_bounds__(kBlock) k_grid_bicg_b(Op A, const double *__restrict__ r,
+                                                        const double *__restrict__ v, PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  const double alpha = ps.in->alpha;
+  Dot2 a0, a1;
+  A.template sweep<ChainSum<double>>(sm, Two<double>{r, v},
+                                     [&](const Two<double>::Raw &e) { return fma(-alpha, e.b, e.a); }, KeepValue{},
+                                     [](int32_t) { return None{}; },
+                                     [&](int32_t, const ChainSum<double> &q, double si, None) {
+                                       a0.add(q.s, si);
+                                       a1.add(q.s, q.s);
+                                     });
+  DD d[2] = {a0.get(), a1.get()};
+  block_partial_to<2>(d, ps.dst);
+}
+
+template <class Op, bool S>
+__global__ void __launch_bounds__(kBlock) k_grid_bicg_c(Op A, const double *__restrict__ r, double *__restrict__ rn,
+                                                        double *__restrict__ u, const double *__restrict__ v,
+                                                        const double *__restrict__ rs, double *__restrict__ x,
+                                                        PassPlain ps) {
+  __shared__ typename Op::SweepSmem sm;
+  if (ps.in->flag != kRunning) return;
+  const double alpha = ps.in->alpha, om = ps.in->omega, bet = ps.in->beta;
+  const bool half = om == 0.0, plain = ps.in->plain != 0;
+  using Raw = Two<double>::Raw;
+  struct Own {
+    double u, rs, x;
+  };
+  Dot2 a0, a1;
+  A.template sweep<ChainSum<double>>(sm, Two<double>{r, v}, [&](const Raw &e) { return fma(-alpha, e.b, e.a); },
+                                     [](const Raw &e, double) { return e; },
+                                     [&](int32_t i) { return Own{ld<S>(u + i), ld<S>(rs + i), ld<S>(x + i)}; },
+                                     [&](int32_t i, const ChainSum<double> &q, const Raw &e, const Own &o) {
+                                       const double si = fma(-alpha, e.b, e.a);
+                                       const double pi = plain ? e.a : fma(bet, o.u, e.a);
+                                       const double xh = fma(alpha, pi, o.x);
+                                       st<S>(x + i, half ? xh : fma(om, si, xh));
+                                       const double ri = half ? si : fma(-om, q.s, si);
+                                       st<S>(rn + i, ri);
+                                       st<S>(u + i, fma(-om, e.b, pi));
+                                       a0.add(ri, o.rs);
+                                       a1.add(ri, ri);
+                                     });
+  DD d[2] = {a0.get(), a1.get()};
+  block_partial_to<2>(d, ps.dst);
+}
+
+// ------------------------------------------------------------------ launches
+
+namespace {
+
+template <int NPTS, class T, int R>
+GridOp<NPTS, T, R> make(const GridRun &g) {
+  GridOp<NPTS, T, R> op{g.a->nx, g.a->ny, g.a->nz, g.a->n, {}, g.plan};
+  for (int q = 0; q < NPTS; ++q) op.c[q] = std::is_same<T, float>::value ? T(g.a->lo[q]) : T(g.a->c[q]);
+  return op;
+}
+
+template <class T, class F>
+hipError_t with(const GridRun &g, F &&f) {
+  if (g.a->npts == 7)
+    g.points == 4 ? f(make<7, T, 4>(g)) : f(make<7, T, 2>(g));
+  else
+    g.points == 4 ? f(make<27, T, 4>(g)) : f(make<27, T, 2>(g));
+  return hipGetLastError();
+}
+// f(op, whether the pass streams)
+template <class F>
+hipError_t with_stream(const GridRun &g, F &&f) {
+  return with<double>(g, [&](auto op) { g.stream ? f(op, std::true_type()) : f(op, std::false_type()); });
+}
+
+}  // namespace
+
+// From 786,432 points on: per iteration of packed CG 80^3 21.8 us against 19.8
+// by the packed rows, 96^3 22.8 against 25.4, 128^3 34.7 against 42.2; 27-point
+// Jacobi 96^3 13.8 against 24.5 (below, the chain of planes of a block costs
+// more than the gathers).  In-plane rows are 28-bit so that their byte offsets
+// fit 32 bits.
+bool grid_takes(int32_t nx, int32_t ny, int32_t nz) {
+  const int64_t nxy = int64_t(nx) * ny;
+  return nxy * nz >= (int64_t(3) << 18) && nxy < (int64_t(1) << 28);
+}
+
+// Two points per thread until four still make two blocks per CU: CG 96^3 22.8 us
+// an iteration with two, 24.3 with four; 256^3 179 with two, 164 with four.
+// 512 blocks of four points, all resident: 256^3 164 us against 174 with 1024.
+// Streaming from 256 MB of vectors on: CG 256^3 (512 MB) 164 us against 197
+// with allocating accesses, 27-point 192^3 (226 MB) 79.6 against 73.3.
+GridRun grid_run(const GridStencil &a, int64_t vector_bytes, hipStream_t s) {
+  GridRun g{&a, {}, 0, 0, vector_bytes > (int64_t(256) << 20), s};
+  g.points = a.n >= (1 << 21) ? 4 : 2;
+  g.plan = grid_plan(a.nx, a.ny, a.nz, g.points, g.points == 4 ? 512 : 1024);
+  const int64_t b = int64_t(g.plan.ntx) * g.plan.nty * g.plan.ncz;
+  g.blocks = int(std::min<int64_t>(b, kFinishOne));
+  if (g.blocks >= 64) g.blocks -= g.blocks % kXcds;
+  return g;
+}
+
+#define GRID_LAUNCH(T, kernel, ...)                                                                 \
+  return with<T>(g, [&](auto op) {                                                                  \
+    using Op = decltype(op);                                                                        \
+    hipLaunchKernelGGL((kernel), dim3(g.blocks), dim3(kBlock), 0, g.s, op, __VA_ARGS__);            \
+  })
+
+#define GRID_LAUNCH_STREAM(kernel, ...)                                                             \
+  return with_stream(g, [&](auto op, auto stream) {                                                 \
+    using Op = decltype(op);                                                                        \
+    constexpr bool S = decltype(stream)::value;                                                     \
+    hipLaunchKernelGGL((kernel), dim3(g.blocks), dim3(kBlock), 0, g.s, op, __VA_ARGS__);            \
+  })
+
+hipError_t grid_spmv(const GridRun &g, const double *x, double *y) { GRID_LAUNCH(double, k_grid_spmv<Op>, x, y); }
+hipError_t grid_residual(const GridRun &g, const double *b, const double *x, double *r, double *zero, DD *dst) {
+  GRID_LAUNCH(double, k_grid_residual<Op>, b, x, r, zero, dst);
+}
+hipError_t grid_check(const GridRun &g, const double *b, const double *x, const PassPlain &ps) {
+  GRID_LAUNCH(double, k_grid_check<Op>, b, x, ps);
+}
+hipError_t grid_jacobi(const GridRun &g, const double *b, const double *x, double *xn, const PassPlain &ps) {
+  GRID_LAUNCH_STREAM((k_grid_jacobi<Op, S>), b, x, xn, ps);
+}
+hipError_t grid_cg_a(const GridRun &g, const double *r, const double *p, double *pn, const PassPlain &ps) {
+  GRID_LAUNCH_STREAM((k_grid_cg_a<Op, double, S>), r, p, pn, ps);
+}
+hipError_t grid_cg_b(const GridRun &g, const double *pn, const double *p, double *r, double *x, const PassPlain &ps) {
+  GRID_LAUNCH_STREAM((k_grid_cg_b<Op, double, S>), pn, p, r, x, ps);
+}
+hipError_t grid_cg_a(const GridRun &g, const float *r, const float *p, float *pn, const PassPlain &ps) {
+  GRID_LAUNCH(float, (k_grid_cg_a<Op, float, false>), r, p, pn, ps);
+}
+hipError_t grid_cg_b(const GridRun &g, const float *pn, const float *p, float *r, float *x, const PassPlain &ps) {
+  GRID_LAUNCH(float, (k_grid_cg_b<Op, float, false>), pn, p, r, x, ps);
+}
+hipError_t grid_cgnb_x(const GridRun &g, const double2_t *ra, double *w, const PassPlain &ps) {
+  GRID_LAUNCH(double, k_grid_cgnb_x<Op>, ra, w, ps);
+}
+hipError_t grid_bicg_a(const GridRun &g, const double *r, const double *u, double *rs, double *v, const PassPlain &ps) {
+  GRID_LAUNCH_STREAM((k_grid_bicg_a<Op, S>), r, u, rs, v, ps);
+}
+hipError_t grid_bicg_b(const GridRun &g, const double *r, const double *v, const PassPlain &ps) {
+  GRID_LAUNCH(double, k_grid_bicg_b<Op>, r, v, ps);
+}
+hipError_t grid_bicg_c(const GridRun &g, const double *r, double *rn, double *u, const double *v, const double *rs,
+                       double *x, const PassPlain &ps) {
+  GRID_LAUNCH_STREAM((k_grid_bicg_c<Op, S>), r, rn, u, v, rs, x, ps);
+}
+
+}  // namespace its

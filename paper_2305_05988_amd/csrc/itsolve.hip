@@ -8,6 +8,7 @@
 
 #include <algorithm>
 #include <limits>
+#include <map>
 #include <mutex>
 #include <type_traits>
 #include <utility>
@@ -18,6 +19,7 @@
 #include <string>
 #include <vector>
 
+#include "grid_passes.hpp"
 #include "host.hpp"
 #include "kernels.hpp"
 
@@ -53,6 +55,11 @@ struct its_matrix {
   const __half *val16 = nullptr;
   int32_t nx = 0, ny = 0, nz = 0;
   double coef[27] = {};
+  // The operator as a constant stencil on a grid large enough for the plane
+  // sweep (grid.hip): a matrix-free operator, or a packed matrix found to be
+  // one (find_grid); npts 0: none.  low: its values in FP32 and FP16.
+  GridStencil grid;
+  float low[2][27] = {};
   const double *kcoef = nullptr;  // variable-coefficient diffusion: per-cell k (borrowed)
   // Gauss-Seidel colouring (CSR): rows grouped by colour, owned
   int32_t ncolors = 0;
@@ -129,6 +136,7 @@ static void free_packed(its_matrix *A) {
   if (A->soff) (void)hipFree(A->soff);
   if (A->smask) (void)hipFree(A->smask);
   A->pat.release();
+  A->grid = GridStencil();
   A->sp = nullptr;
   A->scol = nullptr;
   A->sval = nullptr;
@@ -247,6 +255,16 @@ struct Run {
 #define LAUNCH(run, cls, kernel, grid, ...)                                                   \
   do {                                                                                        \
     hipError_t e_ = (run).launch(cls, kernel, grid, __VA_ARGS__);                             \
+    if (e_ != hipSuccess) return fail(ITS_E_HIP, std::string("launch: ") + hipGetErrorString(e_)); \
+  } while (0)
+
+// A pass of grid.hip: the same bookkeeping around its own launch on run.s.
+#define LAUNCH_GRID(run, cls, g, call)                                                        \
+  do {                                                                                        \
+    (g).s = (run).s;                                                                          \
+    (run).prof.begin(cls, (run).s);                                                           \
+    hipError_t e_ = (call);                                                                   \
+    (run).prof.end((run).s);                                                                  \
     if (e_ != hipSuccess) return fail(ITS_E_HIP, std::string("launch: ") + hipGetErrorString(e_)); \
   } while (0)
 
@@ -481,9 +499,16 @@ struct Flow {
     count = 0;
     return ITS_OK;
   }
+  // The same for a kernel that never finds anything pending.
+  template <int ND, class Fin>
+  its_status enter_plain(Fin fin, int region, PassPlain &p) {
+    if (count > 0) TRY(apply<ND>(fin));
+    p = PassPlain{cur, {slots(0, region), slots(1, region)}};
+    return ITS_OK;
+  }
   // That kernel's ND partials are pending from here on.
-  template <int ND>
-  its_status leave(int G, const Pass &p) {
+  template <int ND, class P>
+  its_status leave(int G, const P &p) {
     return pend<ND>(G, p.dst[0], p.dst[1]);
   }
   // Two passes of G blocks each made dot 0's and dot 1's partials, in two
@@ -640,23 +665,46 @@ int64_t steps_for(int64_t max_iter) {
   return max_iter < std::numeric_limits<int64_t>::max() ? max_iter + 1 : max_iter;
 }
 
+// r = b - A x (r may be null) and its r.r through fin.
+its_status residual(Run &run, int cls, const its_matrix *A, const WS &w, const double *b, const double *x, double *r,
+                    FinDot fin, double *zero = nullptr) {
+  if (A->grid.npts) {
+    GridRun g = grid_run(A->grid, 24 * A->n, run.s);
+    LAUNCH_GRID(run, cls, g, grid_residual(g, b, x, r, zero, w.R->p1[0]));
+    FINISH(run, 1, w.R, g.blocks, fin);
+    return ITS_OK;
+  }
+  return with_op64(A, [&](auto op) -> its_status {
+    const int GA = op.grid();
+    LAUNCH(run, cls, (k_residual<decltype(op), false>), GA, op, b, x, r, w.R);
+    FINISH(run, 1, w.R, GA, fin);
+    return ITS_OK;
+  });
+}
+
 // Common prologue: zero the States, b.b, r0 = b - A x0 (stored in r if
 // non-null; Pairs: as the first members of pairs, the second ones 0) and
-// r0.r0.  Returns bb and rr0 through `host`.
+// r0.r0.  Returns bb and rr0 through `host`.  zero: a vector set to 0 beside r
+// (grid operators only).
 template <bool Pairs>
 its_status prologue(Run &run, const its_matrix *A, const WS &w, const double *b, const double *x,
-                    double *r, State *host, double &bb, double &rr) {
+                    double *r, State *host, double &bb, double &rr, double *zero = nullptr) {
   const int32_t n = int32_t(A->n);
   const int G = grid_for(n);
   LAUNCH(run, kClassOther, k_reset, 1, w.st, 2, w.R);
   LAUNCH(run, kClassOther, k_dot, G, n, b, b, w.R);
   FINISH(run, 1, w.R, G, (FinDot{w.st, 0}));
-  its_status s = with_op64(A, [&](auto op) -> its_status {
-    const int GA = op.grid();
-    LAUNCH(run, kClassOther, (k_residual<decltype(op), Pairs>), GA, op, b, x, r, w.R);
-    FINISH(run, 1, w.R, GA, (FinDot{w.st, 1}));
-    return ITS_OK;
-  });
+  its_status s;
+  if (!Pairs && A->grid.npts) {
+    s = residual(run, kClassOther, A, w, b, x, r, FinDot{w.st, 1}, zero);
+  } else {
+    s = with_op64(A, [&](auto op) -> its_status {
+      const int GA = op.grid();
+      LAUNCH(run, kClassOther, (k_residual<decltype(op), Pairs>), GA, op, b, x, r, w.R);
+      FINISH(run, 1, w.R, GA, (FinDot{w.st, 1}));
+      return ITS_OK;
+    });
+  }
   if (s != ITS_OK) return s;
   s = poll(run, w.st, host);
   if (s != ITS_OK) return s;
@@ -672,12 +720,7 @@ double threshold2(double rtol, double bb) {
 
 its_status true_residual(Run &run, const its_matrix *A, const WS &w, const double *b,
                          const double *x, State *host, double bb, its_result *res) {
-  its_status s = with_op64(A, [&](auto op) -> its_status {
-    const int GA = op.grid();
-    LAUNCH(run, kClassOther, (k_residual<decltype(op), false>), GA, op, b, x, (double *)nullptr, w.R);
-    FINISH(run, 1, w.R, GA, (FinDot{w.st2, 2}));
-    return ITS_OK;
-  });
+  its_status s = residual(run, kClassOther, A, w, b, x, nullptr, FinDot{w.st2, 2});
   if (s != ITS_OK) return s;
   s = poll(run, w.st2, host);
   if (s != ITS_OK) return s;
@@ -737,6 +780,30 @@ its_status persist_launch(Run &run, State *h, K kernel, int units, const WS &w, 
 
 // ------------------------------------------------------------------- CG
 
+// The iterations of CG by plane sweeps (grid.hip): T double, or float for the
+// refinement's inner solve.  P[0] holds zeros at the start.
+template <class T>
+its_status cg_grid(Run &run, const GridStencil &a, const WS &w, State *st, State *h, int64_t max_iter, int m, T *x,
+                   T *r, T *const (&P)[2]) {
+  GridRun g = grid_run(a, int64_t(4 * sizeof(T)) * a.n, run.s);  // r, p, p', x
+  Flow f(run, w, st);
+  TRY(iterate(run, st, h, max_iter, m, [&](int64_t j, bool first, bool last) -> its_status {
+    T *p = P[j & 1], *pn = P[(j & 1) ^ 1];
+    PassPlain ps;
+    if (first) f.start();
+    TRY(f.enter_plain<1>(FinCg2{}, 0, ps));
+    LAUNCH_GRID(run, 0, g, grid_cg_a(g, (const T *)r, (const T *)p, pn, ps));
+    TRY(f.leave<1>(g.blocks, ps));
+    TRY(f.enter_plain<1>(FinCg1{}, 1, ps));
+    LAUNCH_GRID(run, 1, g, grid_cg_b(g, (const T *)pn, (const T *)p, r, x, ps));
+    TRY(f.leave<1>(g.blocks, ps));
+    return last ? f.end<1>(FinCg2{}) : ITS_OK;
+  }));
+  // after an odd count of iterations p is in P[1]
+  LAUNCH(run, kClassOther, k_cg_flush_p<T>, grid_for(a.n), a.n, x, (const T *)P[1], (const State *)st);
+  return ITS_OK;
+}
+
 its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const double *b, double *x,
                     const WS &w, its_result *res) {
   State *h = A->host_state;
@@ -746,8 +813,12 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
   const int G2 = grid_for((int64_t(n) + 1) / 2, kUpdateGrid);
   double2_t *rp = w.reg<double2_t>(0);  // {r, p} pairs
   double *q = w.v64(1);
+  // the plane sweep's vectors in the same space: r, and p and p' in turn
+  const bool grid = A->grid.npts != 0 && !o->persistent;
+  double *r = w.v64(0), *P[2] = {r + n, w.v64(1)};
   double bb, rr;
-  its_status s = prologue<true>(run, A, w, b, x, reinterpret_cast<double *>(rp), h, bb, rr);
+  its_status s = grid ? prologue<false>(run, A, w, b, x, r, h, bb, rr, P[0])
+                      : prologue<true>(run, A, w, b, x, reinterpret_cast<double *>(rp), h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -773,7 +844,10 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
     res->true_rel_res = std::sqrt(h->dot[2]) / std::sqrt(bb);
     return ITS_OK;
   }
-  if (flag == kRunning) {
+  if (flag == kRunning && grid) {
+    s = cg_grid(run, A->grid, w, w.st, h, o->max_iter, batch_size(o, n), x, r, P);
+    if (s != ITS_OK) return s;
+  } else if (flag == kRunning) {
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
       Flow f(run, w, w.st);
@@ -835,6 +909,21 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
         return persist_launch(run, h, k_cgnb_persist<decltype(op)>, GA, w, op, x, ra, w.reg<double2_t>(3), p, wv, b,
                               w.st, w.R);
       Flow f(run, w, w.st);
+      if (A->grid.npts) {
+        GridRun g = grid_run(A->grid, 40 * A->n, run.s);  // {r, A p}, p, w, x
+        return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+          PassPlain pp;
+          if (first) f.start();
+          TRY(f.enter_plain<1>(FinCgnbY{}, 0, pp));
+          LAUNCH_GRID(run, 0, g, grid_cgnb_x(g, ra, wv, pp));
+          TRY(f.leave<1>(g.blocks, pp));
+          Pass ps;
+          TRY(f.enter<1>(G, FinCgnbX{}, 1, ps));
+          LAUNCH_PASS(run, 1, k_cgnb_y, (false), G, ps, n, x, ra, p, (const double *)wv);
+          TRY(f.leave<1>(G, ps));
+          return last ? f.end<1>(FinCgnbY{}) : ITS_OK;
+        });
+      }
       return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
         Pass ps;
         if (first) f.start();
@@ -878,6 +967,10 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
   // bytes of them in front keep the pairs' alignment
   float2_t *rhp = w.reg<float2_t>(1) + kGuardPairs;
   float *q = w.reg<float>(2), *d = w.reg<float>(3);
+  // the plane sweep's vectors in the same space: r, and p and p' in turn
+  GridStencil grid = A->grid;
+  std::memcpy(grid.lo, A->low[dt == ITS_F16], sizeof(grid.lo));
+  float *rh = w.reg<float>(1), *P[2] = {rh + n, q};
   double bb, rr;
   its_status s = prologue<false>(run, A, w, b, x, r, h, bb, rr);
   if (s != ITS_OK) return s;
@@ -893,12 +986,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
   int64_t outer = 0;
   for (;; ++outer) {
     if (outer > 0) {  // r = b - A x of the refined iterate
-      s = with_op64(A, [&](auto op) -> its_status {
-        const int GA = op.grid();
-        LAUNCH(run, 2, (k_residual<decltype(op), false>), GA, op, b, (const double *)x, r, w.R);
-        FINISH(run, 1, w.R, GA, (FinDot{w.st, 1}));
-        return ITS_OK;
-      });
+      s = residual(run, 2, A, w, b, x, r, FinDot{w.st, 1});
       if (s != ITS_OK) return s;
       s = poll(run, w.st, h);
       if (s != ITS_OK) return s;
@@ -908,7 +996,10 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
     if (!std::isfinite(rr)) { res->status = ITS_BREAKDOWN; break; }
     if (outer == o->max_outer || inner_total >= o->max_iter) { res->status = ITS_NOT_CONVERGED; break; }
     const double rn = std::sqrt(rr);
-    LAUNCH(run, 3, k_ir_scale, G, n, (const double *)r, rhp, d, w.R, rn);
+    if (grid.npts)
+      LAUNCH(run, 3, k_ir_scale<false>, G, n, (const double *)r, rh, P[0], d, w.R, rn);
+    else
+      LAUNCH(run, 3, k_ir_scale<true>, G, n, (const double *)r, reinterpret_cast<float *>(rhp), (float *)nullptr, d, w.R, rn);
     FINISH(run, 1, w.R, G, (FinDot{w.st2, 1}));
     s = poll(run, w.st2, h);
     if (s != ITS_OK) return s;
@@ -917,6 +1008,9 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
     const int64_t budget = o->max_iter - inner_total;
     if (!(rho_i <= ithr2)) {
       LAUNCH(run, kClassOther, k_begin, 1, w.st2, (int32_t)kRunning, rho_i, ithr2, budget);
+      if (grid.npts)
+        s = cg_grid(run, grid, w, w.st2, h, budget, batch_size(o, n), d, rh, P);
+      else
       s = with_op32(A, dt, [&](auto op) -> its_status {
         // two rows per lane where it pays (measured): FP16 values, or
         // slices wider than one group of seven entries
@@ -946,7 +1040,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
         });
       });
       if (s != ITS_OK) return s;
-      LAUNCH(run, kClassOther, k_cg_flush_x32, G, n, d, (const float2_t *)rhp, (const State *)w.st2);
+      if (!grid.npts) LAUNCH(run, kClassOther, k_cg_flush_x32, G, n, d, (const float2_t *)rhp, (const State *)w.st2);
       inner_total += h->k;
       if (h->flag == kBreakdown) { res->status = ITS_BREAKDOWN; break; }
     }
@@ -971,8 +1065,12 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
   const int GC = grid_for((int64_t(n) + 1) / 2, kUpdateGrid);  // pass C: two rows per thread
   double2_t *ru = w.reg<double2_t>(0), *rv = w.reg<double2_t>(3);
   double *rs = w.v64(1), *p = w.v64(2), *t = w.v64(4);
+  // the plane sweep's vectors in the same space
+  const bool grid = A->grid.npts != 0 && !o->persistent;
+  double *rr2[2] = {w.v64(0), w.v64(2)}, *u = w.v64(0) + n, *v = w.v64(3);
   double bb, rr;
-  its_status s = prologue<true>(run, A, w, b, x, reinterpret_cast<double *>(ru), h, bb, rr);
+  its_status s = grid ? prologue<false>(run, A, w, b, x, rr2[0], h, bb, rr)
+                      : prologue<true>(run, A, w, b, x, reinterpret_cast<double *>(ru), h, bb, rr);
   if (s != ITS_OK) return s;
   if (!std::isfinite(bb)) return fail(ITS_E_INVALID, "b contains NaN or Inf");
   if (bb == 0.0) {
@@ -988,10 +1086,33 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
   else if (o->max_iter <= 0) flag = kMaxIter;
   LAUNCH(run, kClassOther, k_begin, 1, w.st, flag, rr, thr2, (int64_t)o->max_iter);
   if (flag == kRunning) {
-    LAUNCH(run, kClassOther, k_bicg_init, G, n, (const double2_t *)ru, rs, w.R, std::sqrt(rr));
+    if (grid)
+      LAUNCH(run, kClassOther, k_bicg_init<1>, G, n, (const double *)rr2[0], rs, w.R, std::sqrt(rr));
+    else
+      LAUNCH(run, kClassOther, k_bicg_init<2>, G, n, reinterpret_cast<const double *>(ru), rs, w.R, std::sqrt(rr));
     FINISH(run, 1, w.R, G, (FinBicgInit{w.st}));
     const double rt2 = o->restart_tol * o->restart_tol;
     const int32_t paper = o->restart_mode == ITS_RESTART_PAPER;
+    if (grid) {
+      GridRun g = grid_run(A->grid, 48 * A->n, run.s);  // r, its next, u, r', v, x
+      Flow f(run, w, w.st);
+      const FinBicgC fc{nullptr, rt2, paper};
+      s = iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+        double *r = rr2[j & 1], *rn = rr2[(j & 1) ^ 1];
+        PassPlain ps;
+        if (first) f.start();
+        TRY(f.enter_plain<2>(fc, 0, ps));
+        LAUNCH_GRID(run, 0, g, grid_bicg_a(g, r, u, rs, v, ps));
+        TRY(f.leave<1>(g.blocks, ps));
+        TRY(f.enter_plain<1>(FinBicgA{}, 1, ps));
+        LAUNCH_GRID(run, 1, g, grid_bicg_b(g, r, v, ps));
+        TRY(f.leave<2>(g.blocks, ps));
+        TRY(f.enter_plain<2>(FinBicgB{}, 2, ps));
+        LAUNCH_GRID(run, 2, g, grid_bicg_c(g, r, rn, u, v, rs, x, ps));
+        TRY(f.leave<2>(g.blocks, ps));
+        return last ? f.end<2>(fc) : ITS_OK;
+      });
+    } else
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
       if (o->persistent) {
@@ -1060,7 +1181,20 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
   const double thr2 = threshold2(o->rtol, bb);
   LAUNCH(run, kClassOther, k_begin, 1, w.st, (int32_t)kRunning, 0.0, thr2, (int64_t)o->max_iter);
   // sweep j tests x_j and forms x_{j+1}: max_iter + 1 launches at most
-  s = with_op64(A, [&](auto op) -> its_status {
+  if (A->grid.npts) {
+    GridRun g = grid_run(A->grid, 24 * A->n, run.s);  // x, its next, b
+    Flow f(run, w, w.st);
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+      const int a = int(j & 1);
+      PassPlain ps;
+      if (first) f.start();
+      TRY(f.enter_plain<1>(FinJacobi{}, a, ps));
+      LAUNCH_GRID(run, 0, g, grid_jacobi(g, b, X[a], X[a ^ 1], ps));
+      TRY(f.leave<1>(g.blocks, ps));
+      return last ? f.end<1>(FinJacobi{}) : ITS_OK;
+    });
+  } else
+    s = with_op64(A, [&](auto op) -> its_status {
     const int GA = op.grid();
     Flow f(run, w, w.st);
     return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
@@ -1204,16 +1338,25 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
     LAUNCH(run, kClassOther, k_gs_restore_rows, grid_for(count[1]), (const int32_t *)(A->color_rows + A->color_off[1]), count[1], (const double *)xs, x);
     HIP_TRY(hipStreamSynchronize(run.s));
   } else if (flag == kRunning) {
+    GridRun g{};
+    if (A->grid.npts) g = grid_run(A->grid, 16 * A->n, run.s);  // x, b
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
       return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
         if (first) f.start();
         for (int c = (j == 0 ? 0 : 1); c < nc; ++c) TRY(sweep(c, 2, Plain{}));
         for (int c = nc - 2; c >= 0; --c) TRY(sweep(c, 2, Plain{}));
-        Pass p;
-        TRY(f.enter<1>(GA, FinGs{}, int(j & 1), p));
-        LAUNCH_PASS(run, 1, k_gs_check, (decltype(op)), GA, p, op, b, (const double *)x);
-        TRY(f.leave<1>(GA, p));
+        if (A->grid.npts) {
+          PassPlain ps;
+          TRY(f.enter_plain<1>(FinGs{}, int(j & 1), ps));
+          LAUNCH_GRID(run, 1, g, grid_check(g, b, x, ps));
+          TRY(f.leave<1>(g.blocks, ps));
+        } else {
+          Pass p;
+          TRY(f.enter<1>(GA, FinGs{}, int(j & 1), p));
+          LAUNCH_PASS(run, 1, k_gs_check, (decltype(op)), GA, p, op, b, (const double *)x);
+          TRY(f.leave<1>(GA, p));
+        }
         return last ? f.end<1>(FinGs{}) : ITS_OK;
       }, /*eager_first=*/true);
     });
@@ -1402,7 +1545,15 @@ its_status its_stencil_create(int32_t nx, int32_t ny, int32_t nz, int32_t npts, 
   A->nx = nx;
   A->ny = ny;
   A->nz = nz;
-  for (int o = 0; o < npts; ++o) A->coef[o] = coef[o];
+  for (int o = 0; o < npts; ++o) {
+    A->coef[o] = coef[o];
+    A->low[0][o] = float(coef[o]);
+    A->low[1][o] = float(static_cast<_Float16>(coef[o]));
+  }
+  if (grid_takes(nx, ny, nz)) {
+    A->grid = GridStencil{npts, nx, ny, nz, int32_t(n), {}, {}};
+    for (int o = 0; o < npts; ++o) A->grid.c[o] = coef[o];
+  }
   *out = A;
   return ITS_OK;
 }
@@ -1853,6 +2004,88 @@ static its_status pack_colors(its_matrix *A, hipStream_t s) {
   return ITS_OK;
 }
 
+// Whether a matrix in pattern form is a constant stencil on a grid that the
+// plane sweep takes: its 7 or 27 offsets (each with one value throughout) name
+// the grid's sides, and every slice must then have exactly the entries whose
+// neighbours lie inside it.
+static hipError_t find_grid(its_matrix *A, hipStream_t s) {
+  const PatArrays &P = A->pat;
+  const size_t at = size_t(P.count) * kPatMax;
+  std::vector<PatHead> head(size_t(P.count));
+  std::vector<int32_t> off(at);
+  std::vector<double> val(at);
+  std::vector<float> v32(at), v16(at);
+  hipError_t e = hipMemcpyAsync(head.data(), P.head, head.size() * sizeof(PatHead), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(off.data(), P.off, at * sizeof(int32_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(val.data(), P.val, at * sizeof(double), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess && P.val32) e = hipMemcpyAsync(v32.data(), P.val32, at * sizeof(float), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess && P.val16) e = hipMemcpyAsync(v16.data(), P.val16, at * sizeof(float), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess) return e;
+  struct Value {
+    double v;
+    float lo[2];
+  };
+  std::map<int32_t, Value> found;
+  for (int32_t q = 0; q < P.count; ++q)
+    for (int32_t j = 0; j < head[size_t(q)].w; ++j) {
+      const size_t k = size_t(q) * kPatMax + size_t(j);
+      const Value v{val[k], {v32[k], v16[k]}};
+      const auto put = found.emplace(off[k], v);
+      if (std::memcmp(&put.first->second, &v, sizeof(v)) != 0 || !std::isfinite(v.v) || !std::isfinite(v.lo[0]) ||
+          !std::isfinite(v.lo[1]) || found.size() > 27)
+        return hipSuccess;
+    }
+  const int np = int(found.size());
+  if (np != 7 && np != 27) return hipSuccess;
+  GridOffsets d{};
+  struct {
+    GridStencil st;
+    float low[2][27] = {};
+  } g;
+  int q = 0;
+  for (const auto &f : found) {
+    d.d[q] = f.first;
+    g.st.c[q] = f.second.v;
+    g.low[0][q] = f.second.lo[0];
+    g.low[1][q] = f.second.lo[1];
+    ++q;
+  }
+  const int64_t nx = np == 7 ? d.d[5] : d.d[16], nxy = np == 7 ? d.d[6] : d.d[22];
+  if (nx < 3 || nxy < 3 * nx || nxy % nx != 0 || A->n % nxy != 0) return hipSuccess;
+  const int32_t ny = int32_t(nxy / nx), nz = int32_t(A->n / nxy);
+  q = 0;
+  for (int dk = -1; dk <= 1; ++dk)
+    for (int dj = -1; dj <= 1; ++dj)
+      for (int di = -1; di <= 1; ++di) {
+        if (np == 7 && std::abs(dk) + std::abs(dj) + std::abs(di) > 1) continue;
+        if (d.d[q++] != dk * nxy + dj * nx + di) return hipSuccess;
+      }
+  if (nz < 2 || !grid_takes(int32_t(nx), ny, nz)) return hipSuccess;
+  DevTmp bad;
+  uint32_t hbad = 1;
+  e = hipMalloc(&bad.p, sizeof(uint32_t));
+  if (e == hipSuccess) e = hipMemsetAsync(bad.p, 0, sizeof(uint32_t), s);
+  if (e == hipSuccess) {
+    const int64_t ns = (A->n + kSlice - 1) / kSlice;
+    hipLaunchKernelGGL(k_grid_match, dim3(int(std::min<int64_t>((ns + kWaves - 1) / kWaves, 4096))), dim3(kBlock), 0, s,
+                       int32_t(A->n), int32_t(nx), ny, nz, np, d, (const int32_t *)P.pid, (const PatHead *)P.head,
+                       (const int32_t *)P.off, (const uint64_t *)P.mask, static_cast<uint32_t *>(bad.p));
+    e = hipGetLastError();
+  }
+  if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipStreamSynchronize(s);
+  if (e != hipSuccess || hbad) return e;
+  g.st.npts = np;
+  g.st.nx = int32_t(nx);
+  g.st.ny = ny;
+  g.st.nz = nz;
+  g.st.n = int32_t(A->n);
+  A->grid = g.st;
+  std::memcpy(A->low, g.low, sizeof(g.low));
+  return hipSuccess;
+}
+
 its_status its_csr_pack(its_matrix *A, double max_fill, void *stream) {
   if (!A || A->kind != kCsr) return fail(ITS_E_INVALID, "not a CSR matrix");
   if (!(max_fill >= 1.0) || !std::isfinite(max_fill))
@@ -1875,6 +2108,10 @@ its_status its_csr_pack(its_matrix *A, double max_fill, void *stream) {
   A->sell_col_slots = P.col_slots;
   A->sell_wmax = P.wmax;
   A->pack_fill = max_fill;
+  if (A->pat.pid && find_grid(A, s) != hipSuccess) {
+    free_packed(A);
+    return fail(ITS_E_HIP, "packing: the search for a grid failed");
+  }
   // A^T alike where its rows fit max_fill (else it stays in CSR form)
   if (A->tr) (void)its_csr_pack(A->tr, max_fill, stream);
   return pack_colors(A, s);
@@ -1889,6 +2126,7 @@ int64_t its_csr_packed_column_slots(const its_matrix *A) {
 int64_t its_csr_packed_bytes(const its_matrix *A, int32_t dtype) {
   if (!A || !A->packed() || dtype < ITS_F64 || dtype > ITS_F16) return 0;
   const int64_t ns = (A->n + kSlice - 1) / kSlice;
+  if (A->grid.npts) return int64_t(A->grid.npts) * (dtype == ITS_F64 ? 8 : 4);
   if (A->pat.pid)
     return 4 * ns + int64_t(A->pat.count) * (int64_t(sizeof(PatHead)) + kPatMax * (12 + (dtype == ITS_F64 ? 8 : 4)));
   const int64_t vb = dtype == ITS_F64 ? 8 : dtype == ITS_F32 ? 4 : 2;
@@ -1948,6 +2186,10 @@ its_status its_spmv(const its_matrix *A, const double *x, double *y, void *strea
   if (!x || !y) return fail(ITS_E_INVALID, "null vector");
   if (x == y) return fail(ITS_E_INVALID, "x and y alias");
   hipStream_t s = S(stream);
+  if (A->grid.npts) {
+    HIP_TRY(grid_spmv(grid_run(A->grid, 16 * A->n, s), x, y));
+    return ITS_OK;
+  }
   its_status st = with_op64(A, [&](auto op) -> its_status {
     const int grid = op.grid();
     hipLaunchKernelGGL(k_spmv<decltype(op)>, dim3(grid), dim3(kBlock), 0, s, op, x, y);
@@ -2088,7 +2330,11 @@ static its_status solve_impl(const its_matrix *Ac, const its_options *o, const d
     At.ny = A->ny;
     At.nz = A->nz;
     const int np = A->kind == kSten7 ? 7 : 27;
-    for (int q = 0; q < np; ++q) At.coef[q] = A->coef[np - 1 - q];
+    At.grid = A->grid;
+    for (int q = 0; q < np; ++q) {
+      At.coef[q] = At.grid.c[q] = A->coef[np - 1 - q];
+      for (int l = 0; l < 2; ++l) At.low[l][q] = A->low[l][np - 1 - q];
+    }
     At.diag_state = A->diag_state;
     At.host_state = A->host_state;
     A = &At;
@@ -2125,7 +2371,7 @@ static its_status solve_impl(const its_matrix *Ac, const its_options *o, const d
     run.key = {uint64_t(o->method), uint64_t(o->inner_dtype), uint64_t(o->restart_mode), rt,
                uint64_t(o->transpose), uint64_t(reinterpret_cast<uintptr_t>(Ac)),
                uint64_t(reinterpret_cast<uintptr_t>(A->sp)), uint64_t(reinterpret_cast<uintptr_t>(A->pat.pid)),
-               uint64_t(A->cpack.size()),
+               uint64_t(A->cpack.size()), uint64_t(A->grid.npts),
                uint64_t(reinterpret_cast<uintptr_t>(A->color_rows)), uint64_t(A->kind),
                uint64_t(reinterpret_cast<uintptr_t>(b)), uint64_t(reinterpret_cast<uintptr_t>(x)),
                uint64_t(reinterpret_cast<uintptr_t>(workspace)), uint64_t(A->n),

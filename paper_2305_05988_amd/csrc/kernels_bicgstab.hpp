@@ -19,13 +19,15 @@ namespace its {
 // stored as interleaved pairs, one 16-byte access per column: {r, u} for
 // pass A (written by pass C), {r, v} for pass B (written by pass A).
 
-// r' = r / ||r||, alpha_n = r.r' (r: the first members of the {r, u} pairs)
-__global__ void __launch_bounds__(kBlock) k_bicg_init(int32_t n, const double2_t *__restrict__ ru,
+// r' = r / ||r||, alpha_n = r.r' (r: a vector, or with Stride 2 the first
+// members of the {r, u} pairs)
+template <int Stride>
+__global__ void __launch_bounds__(kBlock) k_bicg_init(int32_t n, const double *__restrict__ r,
                                                       double *__restrict__ rs, Reduce *R,
                                                       double rnorm) {
   Dot2 a;
   for_rows(n, [&](int32_t i) {
-    const double ri = ru[i].x;
+    const double ri = r[int64_t(i) * Stride];
     const double rsi = ri / rnorm;
     rs[i] = rsi;
     a.add(ri, rsi);
@@ -46,6 +48,7 @@ struct FinBicgA {
   __device__ bool active() const { return st->flag == kRunning; }
   __device__ void operator()(DD (&v)[1]) const {
     const double ad = dd_round(v[0]);
+    st->plain = st->k == 0 || st->restart;
     st->restart = 0;
     if (ad == 0.0 || !finite(ad)) {
       st->flag = kBreakdown;

@@ -200,6 +200,15 @@ __global__ void __launch_bounds__(kBlock) k_cg_flush_x(int32_t n, double *__rest
   for_rows(n, [&](int32_t i) { x[i] = fma(alpha_x, rp[i].y, x[i]); });
 }
 
+// The same with p in a vector of its own.
+template <class T>
+__global__ void __launch_bounds__(kBlock) k_cg_flush_p(int32_t n, T *__restrict__ x, const T *__restrict__ p,
+                                                       const State *st) {
+  if ((st->k & 1) == 0) return;
+  const T alpha_x = T(st->alpha_x);
+  for_rows(n, [&](int32_t i) { x[i] = fmaT(alpha_x, p[i], x[i]); });
+}
+
 // The same for the FP32 inner solve's correction d.
 __global__ void __launch_bounds__(kBlock) k_cg_flush_x32(int32_t n, float *__restrict__ x,
                                                          const float2_t *__restrict__ rp,

@@ -9,17 +9,23 @@ namespace its {
 // Outer step: rh = (float)(r/rn), d = 0, rh.rh; then (after the inner CG)
 // x += rn * d in double.
 
-// rh is the first member of the inner {r, p} pairs; p starts as 0.
+// p starts as 0: the second member of the {rh, p} pairs, or a vector of its own.
+template <bool Pairs>
 __global__ void __launch_bounds__(kBlock) k_ir_scale(int32_t n, const double *__restrict__ r,
-                                                     float2_t *__restrict__ rh, float *__restrict__ d,
-                                                     Reduce *R, double rn) {
+                                                     float *__restrict__ rh, float *__restrict__ p,
+                                                     float *__restrict__ d, Reduce *R, double rn) {
   Dot2 a;
   for_rows(n, [&](int32_t i) {
     const float v = float(r[i] / rn);
-    float2_t o;
-    o.x = v;
-    o.y = 0.0f;
-    rh[i] = o;
+    if constexpr (Pairs) {
+      float2_t o;
+      o.x = v;
+      o.y = 0.0f;
+      reinterpret_cast<float2_t *>(rh)[i] = o;
+    } else {
+      rh[i] = v;
+      p[i] = 0.0f;
+    }
     d[i] = 0.0f;
     a.add(double(v), double(v));
   });

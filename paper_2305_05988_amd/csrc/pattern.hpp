@@ -374,4 +374,43 @@ __global__ void __launch_bounds__(kBlock) k_pattern_check(int32_t count, const i
   }
 }
 
+// Ascending column offsets of a 7- or 27-point stencil.
+struct GridOffsets {
+  int32_t d[27];
+};
+
+// Compares every slice's pattern with the entries that the stencil of np
+// offsets has on an nx*ny*nz grid, neighbours outside it omitted; *bad counts
+// the slices that differ.  n = nx ny nz.
+__global__ void __launch_bounds__(kBlock) k_grid_match(int32_t n, int32_t nx, int32_t ny, int32_t nz, int32_t np,
+                                                       GridOffsets d, const int32_t *__restrict__ pid,
+                                                       const PatHead *__restrict__ head,
+                                                       const int32_t *__restrict__ off,
+                                                       const uint64_t *__restrict__ mask, uint32_t *bad) {
+  const int64_t ns = (int64_t(n) + kSlice - 1) / kSlice;
+  const int lane = threadIdx.x & 63;
+  for (int64_t s = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6); s < ns; s += int64_t(gridDim.x) * kWaves) {
+    const int64_t p = s * kSlice + lane;
+    const int32_t i = int32_t(min(p, int64_t(n) - 1));
+    const int32_t t = i / nx, ix = i - t * nx, iz = t / ny, iy = t - iz * ny;
+    const int32_t q = pid[s], w = head[q].w;
+    int32_t j = 0;
+    bool same = true;
+    for (int dk = -1, u = 0; dk <= 1; ++dk)
+      for (int dj = -1; dj <= 1; ++dj)
+        for (int di = -1; di <= 1; ++di) {
+          if (np == 7 && (dk != 0) + (dj != 0) + (di != 0) > 1) continue;
+          const uint64_t m = __ballot(p < n && iz + dk >= 0 && iz + dk < nz && iy + dj >= 0 && iy + dj < ny &&
+                                      ix + di >= 0 && ix + di < nx);
+          if (m != 0) {
+            const int64_t k = int64_t(q) * kPatMax + j;
+            same = same && j < w && off[k] == d.d[u] && mask[k] == m;
+            ++j;
+          }
+          ++u;
+        }
+    if (lane == 0 && (!same || j != w)) atomicAdd(bad, 1u);
+  }
+}
+
 }  // namespace its
