@@ -3,6 +3,7 @@
 
 #include <type_traits>
 
+#include "fins.hpp"
 #include "grid.hpp"
 
 namespace its {
@@ -42,6 +43,9 @@ struct Two {
   __device__ __forceinline__ Raw at(int64_t ub, uint32_t off) const { return {(a + ub)[off], (b + ub)[off]}; }
 };
 
+struct Always {
+  __device__ __forceinline__ bool operator()() const { return true; }
+};
 struct Same {
   template <class T>
   __device__ __forceinline__ T operator()(T v) const { return v; }
@@ -59,7 +63,7 @@ struct KeepNone {
 template <class Op>
 __global__ void __launch_bounds__(kBlock) k_grid_spmv(Op A, const double *__restrict__ x, double *__restrict__ y) {
   __shared__ typename Op::SweepSmem sm;
-  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Same{}, KeepNone{}, [](int32_t) { return None{}; },
+  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Always{}, Same{}, KeepNone{}, [](int32_t) { return None{}; },
                                      [&](int32_t i, const ChainSum<double> &q, None, None) { st_nt(y + i, q.s); });
 }
 
@@ -70,7 +74,7 @@ __global__ void __launch_bounds__(kBlock) k_grid_residual(Op A, const double *__
                                                           double *__restrict__ zero, DD *dst) {
   __shared__ typename Op::SweepSmem sm;
   Dot2 a;
-  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Same{}, KeepNone{}, [&](int32_t i) { return ld_nt(b + i); },
+  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Always{}, Same{}, KeepNone{}, [&](int32_t i) { return ld_nt(b + i); },
                                      [&](int32_t i, const ChainSum<double> &q, None, double bi) {
                                        const double ri = bi - q.s;
                                        if (r) st_nt(r + i, ri);
@@ -89,7 +93,7 @@ __global__ void __launch_bounds__(kBlock) k_grid_check(Op A, const double *__res
   __shared__ typename Op::SweepSmem sm;
   if (ps.in->flag != kRunning) return;
   Dot2 a;
-  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Same{}, KeepNone{}, [&](int32_t i) { return b[i]; },
+  A.template sweep<ChainSum<double>>(sm, One<double>{x}, Always{}, Same{}, KeepNone{}, [&](int32_t i) { return b[i]; },
                                      [&](int32_t, const ChainSum<double> &q, None, double bi) {
                                        const double ri = bi - q.s;
                                        a.add(ri, ri);
@@ -99,20 +103,21 @@ __global__ void __launch_bounds__(kBlock) k_grid_check(Op A, const double *__res
 }
 
 // A Jacobi sweep (k_jacobi): the residual of x, and xn = (b - off) / diag.
-template <class Op, bool S>
+template <class Op, bool S, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_jacobi(Op A, const double *__restrict__ b,
-                                                        const double *__restrict__ x, double *__restrict__ xn,
-                                                        PassPlain ps) {
+                                                        const double *__restrict__ x, double *__restrict__ xn, P ps) {
   __shared__ typename Op::SweepSmem sm;
-  if (ps.in->flag != kRunning) return;
   const double diag = A.centre();
+  State s;
   Dot2 a;
-  A.template sweep<ChainSplit>(sm, One<double>{x}, Same{}, KeepNone{}, [&](int32_t i) { return ld<S>(b + i); },
+  const auto begin = [&] { return pass_begin<1>(ps, s, FinJacobi{}); };
+  const bool on = A.template sweep<ChainSplit>(sm, One<double>{x}, begin, Same{}, KeepNone{}, [&](int32_t i) { return ld<S>(b + i); },
                                [&](int32_t i, const ChainSplit &q, None, double bi) {
                                  const double ri = bi - q.s;
                                  a.add(ri, ri);
                                  xn[i] = (bi - q.off) / diag;  // the next sweep's x
                                });
+  if (!on) return;
   DD v[1] = {a.get()};
   block_partial_to<1>(v, ps.dst);
 }
@@ -126,37 +131,49 @@ __global__ void __launch_bounds__(kBlock) k_grid_jacobi(Op A, const double *__re
 //           both iterations' steps
 // p and p' are two buffers: other blocks still load p while p' is stored.  The
 // roundings are k_cg_pass1's and k_cg_pass2's.
-template <class Op, class T, bool S>
+template <class Op, class T, bool S, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_cg_a(Op A, const T *__restrict__ r, const T *__restrict__ p,
-                                                      T *__restrict__ pn, PassPlain ps) {
+                                                      T *__restrict__ pn, P ps) {
   __shared__ typename Op::SweepSmem sm;
-  if (ps.in->flag != kRunning) return;
-  const T beta = T(ps.in->beta);
+  State s;
+  T beta = T(0);
   Dot2 a;
-  A.template sweep<ChainSum<T>>(sm, Two<T>{r, p}, [&](const typename Two<T>::Raw &v) { return fmaT(beta, v.b, v.a); },
+  const auto begin = [&] {
+    const bool on = pass_begin<1>(ps, s, FinCg2{});
+    beta = T(s.beta);
+    return on;
+  };
+  const bool on = A.template sweep<ChainSum<T>>(sm, Two<T>{r, p}, begin, [&](const typename Two<T>::Raw &v) { return fmaT(beta, v.b, v.a); },
                                 KeepValue{}, [](int32_t) { return None{}; },
                                 [&](int32_t i, const ChainSum<T> &q, T pi, None) {
                                   st<S>(pn + i, pi);
                                   a.add(double(pi), double(q.s));
                                 });
+  if (!on) return;
   DD v[1] = {a.get()};
   block_partial_to<1>(v, ps.dst);
 }
 
-template <class Op, class T, bool S>
+template <class Op, class T, bool S, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_cg_b(Op A, const T *__restrict__ pn, const T *__restrict__ p,
-                                                      T *__restrict__ r, T *__restrict__ x, PassPlain ps) {
+                                                      T *__restrict__ r, T *__restrict__ x, bool defer, P ps) {
   __shared__ typename Op::SweepSmem sm;
-  if (ps.in->flag != kRunning) return;
-  const bool defer = (ps.in->k & 1) == 0;  // x waits for the next iteration
-  const T alpha = T(ps.in->alpha), alpha_x = T(ps.in->alpha_x);
+  State s;
+  T alpha = T(0), alpha_x = T(0);
+  bool on = false;
   Dot2 a;
+  const auto begin = [&] {
+    const bool ok = pass_begin<1>(ps, s, FinCg1{});
+    alpha = T(s.alpha);
+    alpha_x = T(s.alpha_x);
+    return ok;
+  };
   struct Own {
     T r, x, p;
   };
   auto run = [&](auto later) {
     constexpr bool kLater = decltype(later)::value;
-    A.template sweep<ChainSum<T>>(sm, One<T>{pn}, Same{}, KeepValue{},
+    on = A.template sweep<ChainSum<T>>(sm, One<T>{pn}, begin, Same{}, KeepValue{},
                                   [&](int32_t i) {
                                     if constexpr (kLater)
                                       return ld<S>(r + i);
@@ -179,24 +196,31 @@ __global__ void __launch_bounds__(kBlock) k_grid_cg_b(Op A, const T *__restrict_
     run(std::true_type());
   else
     run(std::false_type());
+  if (!on) return;
   DD v[1] = {a.get()};
   block_partial_to<1>(v, ps.dst);
 }
 
 // Pass X of CG-NB (k_cgnb_x).
-template <class Op>
+template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_cgnb_x(Op A, const double2_t *__restrict__ ra,
-                                                        double *__restrict__ w, PassPlain ps) {
+                                                        double *__restrict__ w, P ps) {
   __shared__ typename Op::SweepSmem sm;
-  if (ps.in->flag != kRunning) return;
-  const double alpha = ps.in->alpha;
+  State s;
+  double alpha = 0.0;
   Dot2 a;
-  A.template sweep<ChainSum<double>>(sm, One<double2_t>{ra}, [&](const double2_t &v) { return fma(-alpha, v.y, v.x); },
+  const auto begin = [&] {
+    const bool ok = pass_begin<1>(ps, s, FinCgnbY{});
+    alpha = s.alpha;
+    return ok;
+  };
+  const bool on = A.template sweep<ChainSum<double>>(sm, One<double2_t>{ra}, begin, [&](const double2_t &v) { return fma(-alpha, v.y, v.x); },
                                      KeepValue{}, [](int32_t) { return None{}; },
                                      [&](int32_t i, const ChainSum<double> &q, double ri, None) {
                                        st_nt(w + i, q.s);
                                        a.add(ri, ri);
                                      });
+  if (!on) return;
   DD v[1] = {a.get()};
   block_partial_to<1>(v, ps.dst);
 }
@@ -209,18 +233,25 @@ __global__ void __launch_bounds__(kBlock) k_grid_cgnb_x(Op A, const double2_t *_
 //   pass c: s and t again, x, r, u = p - omega v, r.r', r.r
 // r alternates between two buffers: pass c stores its own rows' new r while
 // other blocks load the old one.  The roundings are the pair form's.
-template <class Op, bool S>
+template <class Op, bool S, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_bicg_a(Op A, const double *__restrict__ r,
                                                         const double *__restrict__ u, double *__restrict__ rs,
-                                                        double *__restrict__ v, PassPlain ps) {
+                                                        double *__restrict__ v, FinBicgC fin, P ps) {
   __shared__ typename Op::SweepSmem sm;
-  if (ps.in->flag != kRunning) return;
-  const bool restart = ps.in->restart != 0, plain = ps.in->k == 0 || restart;
-  const double bet = ps.in->beta;
-  const double rn = restart ? __builtin_sqrt(ps.in->rho) : 1.0;
+  State s;
+  bool restart = false, plain = false;
+  double bet = 0.0, rn = 1.0;
   using Raw = Two<double>::Raw;
   Dot2 a;
-  A.template sweep<ChainSum<double>>(sm, Two<double>{r, u},
+  const auto begin = [&] {
+    const bool ok = pass_begin<2>(ps, s, fin);
+    restart = s.restart != 0;
+    plain = s.k == 0 || restart;
+    bet = s.beta;
+    if (restart) rn = __builtin_sqrt(s.rho);
+    return ok;
+  };
+  const bool on = A.template sweep<ChainSum<double>>(sm, Two<double>{r, u}, begin,
                                      [&](const Raw &e) { return plain ? e.a : fma(bet, e.b, e.a); },
                                      [](const Raw &e, double) { return e.a; }, [&](int32_t i) { return ld<S>(rs + i); },
                                      [&](int32_t i, const ChainSum<double> &q, double ri, double rsi) {
@@ -231,43 +262,59 @@ __global__ void __launch_bounds__(kBlock) k_grid_bicg_a(Op A, const double *__re
                                        }
                                        a.add(q.s, rsi);
                                      });
+  if (!on) return;
   DD d[1] = {a.get()};
   block_partial_to<1>(d, ps.dst);
 }
 
-template <class Op>
+template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_bicg_b(Op A, const double *__restrict__ r,
-                                                        const double *__restrict__ v, PassPlain ps) {
+                                                        const double *__restrict__ v, P ps) {
   __shared__ typename Op::SweepSmem sm;
-  if (ps.in->flag != kRunning) return;
-  const double alpha = ps.in->alpha;
+  State s;
+  double alpha = 0.0;
   Dot2 a0, a1;
-  A.template sweep<ChainSum<double>>(sm, Two<double>{r, v},
+  const auto begin = [&] {
+    const bool ok = pass_begin<1>(ps, s, FinBicgA{});
+    alpha = s.alpha;
+    return ok;
+  };
+  const bool on = A.template sweep<ChainSum<double>>(sm, Two<double>{r, v}, begin,
                                      [&](const Two<double>::Raw &e) { return fma(-alpha, e.b, e.a); }, KeepValue{},
                                      [](int32_t) { return None{}; },
                                      [&](int32_t, const ChainSum<double> &q, double si, None) {
                                        a0.add(q.s, si);
                                        a1.add(q.s, q.s);
                                      });
+  if (!on) return;
   DD d[2] = {a0.get(), a1.get()};
   block_partial_to<2>(d, ps.dst);
 }
 
-template <class Op, bool S>
+template <class Op, bool S, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_bicg_c(Op A, const double *__restrict__ r, double *__restrict__ rn,
                                                         double *__restrict__ u, const double *__restrict__ v,
                                                         const double *__restrict__ rs, double *__restrict__ x,
-                                                        PassPlain ps) {
+                                                        P ps) {
   __shared__ typename Op::SweepSmem sm;
-  if (ps.in->flag != kRunning) return;
-  const double alpha = ps.in->alpha, om = ps.in->omega, bet = ps.in->beta;
-  const bool half = om == 0.0, plain = ps.in->plain != 0;
+  State s;
+  double alpha = 0.0, om = 0.0, bet = 0.0;
+  bool half = false, plain = false;
+  const auto begin = [&] {
+    const bool ok = pass_begin<2>(ps, s, FinBicgB{});
+    alpha = s.alpha;
+    om = s.omega;
+    bet = s.beta;
+    half = om == 0.0;
+    plain = s.plain != 0;
+    return ok;
+  };
   using Raw = Two<double>::Raw;
   struct Own {
     double u, rs, x;
   };
   Dot2 a0, a1;
-  A.template sweep<ChainSum<double>>(sm, Two<double>{r, v}, [&](const Raw &e) { return fma(-alpha, e.b, e.a); },
+  const bool on = A.template sweep<ChainSum<double>>(sm, Two<double>{r, v}, begin, [&](const Raw &e) { return fma(-alpha, e.b, e.a); },
                                      [](const Raw &e, double) { return e; },
                                      [&](int32_t i) { return Own{ld<S>(u + i), ld<S>(rs + i), ld<S>(x + i)}; },
                                      [&](int32_t i, const ChainSum<double> &q, const Raw &e, const Own &o) {
@@ -281,6 +328,7 @@ __global__ void __launch_bounds__(kBlock) k_grid_bicg_c(Op A, const double *__re
                                        a0.add(ri, o.rs);
                                        a1.add(ri, ri);
                                      });
+  if (!on) return;
   DD d[2] = {a0.get(), a1.get()};
   block_partial_to<2>(d, ps.dst);
 }
@@ -303,6 +351,13 @@ hipError_t with(const GridRun &g, F &&f) {
   else
     g.points == 4 ? f(make<27, T, 4>(g)) : f(make<27, T, 2>(g));
   return hipGetLastError();
+}
+template <class F>
+void with_pass(const Pass &p, F &&f) {
+  if (p.count > 0)
+    f(p);
+  else
+    f(PassPlain{p.in, {p.dst[0], p.dst[1]}});
 }
 // f(op, whether the pass streams)
 template <class F>
@@ -343,11 +398,24 @@ GridRun grid_run(const GridStencil &a, int64_t vector_bytes, hipStream_t s) {
     hipLaunchKernelGGL((kernel), dim3(g.blocks), dim3(kBlock), 0, g.s, op, __VA_ARGS__);            \
   })
 
-#define GRID_LAUNCH_STREAM(kernel, ...)                                                             \
+// The same with the pass as its type says: pending partials or none.
+#define GRID_LAUNCH_PASS(T, pass, kernel, ...)                                                      \
+  return with<T>(g, [&](auto op) {                                                                  \
+    using Op = decltype(op);                                                                        \
+    with_pass(pass, [&](auto ps) {                                                                  \
+      using P = decltype(ps);                                                                       \
+      hipLaunchKernelGGL((kernel), dim3(g.blocks), dim3(kBlock), 0, g.s, op, __VA_ARGS__, ps);      \
+    });                                                                                             \
+  })
+
+#define GRID_LAUNCH_STREAM(pass, kernel, ...)                                                             \
   return with_stream(g, [&](auto op, auto stream) {                                                 \
     using Op = decltype(op);                                                                        \
     constexpr bool S = decltype(stream)::value;                                                     \
-    hipLaunchKernelGGL((kernel), dim3(g.blocks), dim3(kBlock), 0, g.s, op, __VA_ARGS__);            \
+    with_pass(pass, [&](auto ps) {                                                                  \
+      using P = decltype(ps);                                                                       \
+      hipLaunchKernelGGL((kernel), dim3(g.blocks), dim3(kBlock), 0, g.s, op, __VA_ARGS__, ps);      \
+    });                                                                                             \
   })
 
 hipError_t grid_spmv(const GridRun &g, const double *x, double *y) { GRID_LAUNCH(double, k_grid_spmv<Op>, x, y); }
@@ -357,33 +425,36 @@ hipError_t grid_residual(const GridRun &g, const double *b, const double *x, dou
 hipError_t grid_check(const GridRun &g, const double *b, const double *x, const PassPlain &ps) {
   GRID_LAUNCH(double, k_grid_check<Op>, b, x, ps);
 }
-hipError_t grid_jacobi(const GridRun &g, const double *b, const double *x, double *xn, const PassPlain &ps) {
-  GRID_LAUNCH_STREAM((k_grid_jacobi<Op, S>), b, x, xn, ps);
+hipError_t grid_jacobi(const GridRun &g, const double *b, const double *x, double *xn, const Pass &ps) {
+  GRID_LAUNCH_STREAM(ps, (k_grid_jacobi<Op, S, P>), b, x, xn);
 }
-hipError_t grid_cg_a(const GridRun &g, const double *r, const double *p, double *pn, const PassPlain &ps) {
-  GRID_LAUNCH_STREAM((k_grid_cg_a<Op, double, S>), r, p, pn, ps);
+hipError_t grid_cg_a(const GridRun &g, const double *r, const double *p, double *pn, const Pass &ps) {
+  GRID_LAUNCH_STREAM(ps, (k_grid_cg_a<Op, double, S, P>), r, p, pn);
 }
-hipError_t grid_cg_b(const GridRun &g, const double *pn, const double *p, double *r, double *x, const PassPlain &ps) {
-  GRID_LAUNCH_STREAM((k_grid_cg_b<Op, double, S>), pn, p, r, x, ps);
+hipError_t grid_cg_b(const GridRun &g, const double *pn, const double *p, double *r, double *x, bool defer,
+                     const Pass &ps) {
+  GRID_LAUNCH_STREAM(ps, (k_grid_cg_b<Op, double, S, P>), pn, p, r, x, defer);
 }
-hipError_t grid_cg_a(const GridRun &g, const float *r, const float *p, float *pn, const PassPlain &ps) {
-  GRID_LAUNCH(float, (k_grid_cg_a<Op, float, false>), r, p, pn, ps);
+hipError_t grid_cg_a(const GridRun &g, const float *r, const float *p, float *pn, const Pass &ps) {
+  GRID_LAUNCH_PASS(float, ps, (k_grid_cg_a<Op, float, false, P>), r, p, pn);
 }
-hipError_t grid_cg_b(const GridRun &g, const float *pn, const float *p, float *r, float *x, const PassPlain &ps) {
-  GRID_LAUNCH(float, (k_grid_cg_b<Op, float, false>), pn, p, r, x, ps);
+hipError_t grid_cg_b(const GridRun &g, const float *pn, const float *p, float *r, float *x, bool defer,
+                     const Pass &ps) {
+  GRID_LAUNCH_PASS(float, ps, (k_grid_cg_b<Op, float, false, P>), pn, p, r, x, defer);
 }
-hipError_t grid_cgnb_x(const GridRun &g, const double2_t *ra, double *w, const PassPlain &ps) {
-  GRID_LAUNCH(double, k_grid_cgnb_x<Op>, ra, w, ps);
+hipError_t grid_cgnb_x(const GridRun &g, const double2_t *ra, double *w, const Pass &ps) {
+  GRID_LAUNCH_PASS(double, ps, (k_grid_cgnb_x<Op, P>), ra, w);
 }
-hipError_t grid_bicg_a(const GridRun &g, const double *r, const double *u, double *rs, double *v, const PassPlain &ps) {
-  GRID_LAUNCH_STREAM((k_grid_bicg_a<Op, S>), r, u, rs, v, ps);
+hipError_t grid_bicg_a(const GridRun &g, const double *r, const double *u, double *rs, double *v, const FinBicgC &fin,
+                       const Pass &ps) {
+  GRID_LAUNCH_STREAM(ps, (k_grid_bicg_a<Op, S, P>), r, u, rs, v, fin);
 }
-hipError_t grid_bicg_b(const GridRun &g, const double *r, const double *v, const PassPlain &ps) {
-  GRID_LAUNCH(double, k_grid_bicg_b<Op>, r, v, ps);
+hipError_t grid_bicg_b(const GridRun &g, const double *r, const double *v, const Pass &ps) {
+  GRID_LAUNCH_PASS(double, ps, (k_grid_bicg_b<Op, P>), r, v);
 }
 hipError_t grid_bicg_c(const GridRun &g, const double *r, double *rn, double *u, const double *v, const double *rs,
-                       double *x, const PassPlain &ps) {
-  GRID_LAUNCH_STREAM((k_grid_bicg_c<Op, S>), r, rn, u, v, rs, x, ps);
+                       double *x, const Pass &ps) {
+  GRID_LAUNCH_STREAM(ps, (k_grid_bicg_c<Op, S, P>), r, rn, u, v, rs, x);
 }
 
 }  // namespace its

@@ -70,6 +70,8 @@ struct ChainSplit {
 
 // The sweep's hooks, for plane z (uniform) and in-plane row `off` of a point:
 //   load.at(nxy z, off)  what is loaded for a point, of any type
+//   begin()              called once the first plane's loads are on their way
+//                        and before anything else: false ends the sweep
 //   value(raw)           the vector's value there
 //   keep(raw, value)     what the body needs of the point's own load
 //   side(i)              what the body loads for its own row besides
@@ -87,9 +89,9 @@ struct GridOp {
 
   __device__ __forceinline__ double centre() const { return c[NPTS / 2]; }
 
-  template <class Chain, class Load, class Value, class Keep, class Side, class Body>
-  __device__ __forceinline__ void sweep(SweepSmem &sm, Load &&load, Value &&value, Keep &&keep, Side &&side,
-                                        Body &&body) const {
+  template <class Chain, class Load, class Begin, class Value, class Keep, class Side, class Body>
+  __device__ __forceinline__ bool sweep(SweepSmem &sm, Load &&load, Begin &&begin, Value &&value, Keep &&keep,
+                                        Side &&side, Body &&body) const {
     using Raw = decltype(load.at(0, 0u));
     using Extra = decltype(side(0));
     using Kept = decltype(keep(load.at(0, 0u), T(0)));
@@ -128,9 +130,6 @@ struct GridOp {
           hwr = (y + 1) * pitch + x + 1;
         }
       }
-      for (int k = t; k < 2 * (kPts + 1); k += kBlock) (&sm.v[0][0])[k] = T(0);
-      __syncthreads();
-
       const int32_t zs = max(z0 - 1, 0), ze = min(z1, nz - 1);
       Raw raw[R], rawh;
       Extra ex[R];
@@ -152,6 +151,9 @@ struct GridOp {
           if ((ok >> u) & 1u) body(zo + int32_t(off[u]), ch[u], own[u], ex[u]);
       };
       issue(zs);
+      for (int k = t; k < 2 * (kPts + 1); k += kBlock) (&sm.v[0][0])[k] = T(0);
+      if (b == sc.begin && !begin()) return false;
+      __syncthreads();
       if constexpr (NPTS == 7) {
         Chain ch[R];
         T prev[R];
@@ -234,8 +236,9 @@ struct GridOp {
         }
         if (z1 == nz) finish(nz - 1, lo, own);
       }
-      if (sc.begin + sc.stride < sc.end) __syncthreads();
+      if (b + sc.stride < sc.end) __syncthreads();
     }
+    return sc.begin < sc.end || begin();
   }
 };
 

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "fins.hpp"
 
 namespace its {
 
@@ -34,19 +35,23 @@ struct GridRun {
 GridRun grid_run(const GridStencil &a, int64_t vector_bytes, hipStream_t s);
 
 // Each launches one kernel of g.blocks blocks; the block partials go to
-// ps.dst.  The arithmetic of each is stated beside its kernel.
+// ps.dst.  The arithmetic of each is stated beside its kernel.  defer: an even
+// iteration of CG, which leaves x alone.
 hipError_t grid_spmv(const GridRun &g, const double *x, double *y);
 hipError_t grid_residual(const GridRun &g, const double *b, const double *x, double *r, double *zero, DD *dst);
 hipError_t grid_check(const GridRun &g, const double *b, const double *x, const PassPlain &ps);
-hipError_t grid_jacobi(const GridRun &g, const double *b, const double *x, double *xn, const PassPlain &ps);
-hipError_t grid_cg_a(const GridRun &g, const double *r, const double *p, double *pn, const PassPlain &ps);
-hipError_t grid_cg_b(const GridRun &g, const double *pn, const double *p, double *r, double *x, const PassPlain &ps);
-hipError_t grid_cg_a(const GridRun &g, const float *r, const float *p, float *pn, const PassPlain &ps);
-hipError_t grid_cg_b(const GridRun &g, const float *pn, const float *p, float *r, float *x, const PassPlain &ps);
-hipError_t grid_cgnb_x(const GridRun &g, const double2_t *ra, double *w, const PassPlain &ps);
-hipError_t grid_bicg_a(const GridRun &g, const double *r, const double *u, double *rs, double *v, const PassPlain &ps);
-hipError_t grid_bicg_b(const GridRun &g, const double *r, const double *v, const PassPlain &ps);
+hipError_t grid_jacobi(const GridRun &g, const double *b, const double *x, double *xn, const Pass &ps);
+hipError_t grid_cg_a(const GridRun &g, const double *r, const double *p, double *pn, const Pass &ps);
+hipError_t grid_cg_b(const GridRun &g, const double *pn, const double *p, double *r, double *x, bool defer,
+                     const Pass &ps);
+hipError_t grid_cg_a(const GridRun &g, const float *r, const float *p, float *pn, const Pass &ps);
+hipError_t grid_cg_b(const GridRun &g, const float *pn, const float *p, float *r, float *x, bool defer,
+                     const Pass &ps);
+hipError_t grid_cgnb_x(const GridRun &g, const double2_t *ra, double *w, const Pass &ps);
+hipError_t grid_bicg_a(const GridRun &g, const double *r, const double *u, double *rs, double *v, const FinBicgC &fin,
+                       const Pass &ps);
+hipError_t grid_bicg_b(const GridRun &g, const double *r, const double *v, const Pass &ps);
 hipError_t grid_bicg_c(const GridRun &g, const double *r, double *rn, double *u, const double *v, const double *rs,
-                       double *x, const PassPlain &ps);
+                       double *x, const Pass &ps);
 
 }  // namespace its

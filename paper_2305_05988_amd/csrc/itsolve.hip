@@ -451,7 +451,9 @@ its_status with_op32(const its_matrix *A, int dtype, F &&f) {
 // a finishing kernel between the two.  Per iteration, both ways: packed CG 40^3
 // 15.6 -> 12.3 us, 64^3 (1024 blocks) 16.5 -> 13.8; packed BiCGStab 64^3 29.7 ->
 // 25.9, Jacobi 9.4 -> 8.9.  With 2048 blocks and more the sum at the start of
-// every block costs what the kernel did or more (Jacobi 96^3 16.0 -> 21.3).
+// every block costs what the kernel did or more (Jacobi 96^3 16.0 -> 21.3).  The
+// plane sweeps, 512 to 1024 blocks whose first loads are already on their way
+// then, gain at every size: CG 96^3 22.3 -> 19.8 us, 256x240x200 2.4 %.
 constexpr int kFuseBlocks = 1024;
 
 // The passes of one batch of iterations, handing State and partials on.  The
@@ -789,13 +791,13 @@ its_status cg_grid(Run &run, const GridStencil &a, const WS &w, State *st, State
   Flow f(run, w, st);
   TRY(iterate(run, st, h, max_iter, m, [&](int64_t j, bool first, bool last) -> its_status {
     T *p = P[j & 1], *pn = P[(j & 1) ^ 1];
-    PassPlain ps;
+    Pass ps;
     if (first) f.start();
-    TRY(f.enter_plain<1>(FinCg2{}, 0, ps));
+    TRY(f.enter<1>(g.blocks, FinCg2{}, 0, ps));
     LAUNCH_GRID(run, 0, g, grid_cg_a(g, (const T *)r, (const T *)p, pn, ps));
     TRY(f.leave<1>(g.blocks, ps));
-    TRY(f.enter_plain<1>(FinCg1{}, 1, ps));
-    LAUNCH_GRID(run, 1, g, grid_cg_b(g, (const T *)pn, (const T *)p, r, x, ps));
+    TRY(f.enter<1>(g.blocks, FinCg1{}, 1, ps));
+    LAUNCH_GRID(run, 1, g, grid_cg_b(g, (const T *)pn, (const T *)p, r, x, (j & 1) == 0, ps));
     TRY(f.leave<1>(g.blocks, ps));
     return last ? f.end<1>(FinCg2{}) : ITS_OK;
   }));
@@ -912,12 +914,11 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
       if (A->grid.npts) {
         GridRun g = grid_run(A->grid, 40 * A->n, run.s);  // {r, A p}, p, w, x
         return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
-          PassPlain pp;
-          if (first) f.start();
-          TRY(f.enter_plain<1>(FinCgnbY{}, 0, pp));
-          LAUNCH_GRID(run, 0, g, grid_cgnb_x(g, ra, wv, pp));
-          TRY(f.leave<1>(g.blocks, pp));
           Pass ps;
+          if (first) f.start();
+          TRY(f.enter<1>(g.blocks, FinCgnbY{}, 0, ps));
+          LAUNCH_GRID(run, 0, g, grid_cgnb_x(g, ra, wv, ps));
+          TRY(f.leave<1>(g.blocks, ps));
           TRY(f.enter<1>(G, FinCgnbX{}, 1, ps));
           LAUNCH_PASS(run, 1, k_cgnb_y, (false), G, ps, n, x, ra, p, (const double *)wv);
           TRY(f.leave<1>(G, ps));
@@ -1099,15 +1100,15 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
       const FinBicgC fc{nullptr, rt2, paper};
       s = iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
         double *r = rr2[j & 1], *rn = rr2[(j & 1) ^ 1];
-        PassPlain ps;
+        Pass ps;
         if (first) f.start();
-        TRY(f.enter_plain<2>(fc, 0, ps));
-        LAUNCH_GRID(run, 0, g, grid_bicg_a(g, r, u, rs, v, ps));
+        TRY(f.enter<2>(g.blocks, fc, 0, ps));
+        LAUNCH_GRID(run, 0, g, grid_bicg_a(g, r, u, rs, v, fc, ps));
         TRY(f.leave<1>(g.blocks, ps));
-        TRY(f.enter_plain<1>(FinBicgA{}, 1, ps));
+        TRY(f.enter<1>(g.blocks, FinBicgA{}, 1, ps));
         LAUNCH_GRID(run, 1, g, grid_bicg_b(g, r, v, ps));
         TRY(f.leave<2>(g.blocks, ps));
-        TRY(f.enter_plain<2>(FinBicgB{}, 2, ps));
+        TRY(f.enter<2>(g.blocks, FinBicgB{}, 2, ps));
         LAUNCH_GRID(run, 2, g, grid_bicg_c(g, r, rn, u, v, rs, x, ps));
         TRY(f.leave<2>(g.blocks, ps));
         return last ? f.end<2>(fc) : ITS_OK;
@@ -1186,9 +1187,9 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
     Flow f(run, w, w.st);
     s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
       const int a = int(j & 1);
-      PassPlain ps;
+      Pass ps;
       if (first) f.start();
-      TRY(f.enter_plain<1>(FinJacobi{}, a, ps));
+      TRY(f.enter<1>(g.blocks, FinJacobi{}, a, ps));
       LAUNCH_GRID(run, 0, g, grid_jacobi(g, b, X[a], X[a ^ 1], ps));
       TRY(f.leave<1>(g.blocks, ps));
       return last ? f.end<1>(FinJacobi{}) : ITS_OK;

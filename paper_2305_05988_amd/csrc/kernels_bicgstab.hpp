@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "fins.hpp"
 #include "rowops.hpp"
 
 namespace its {
@@ -40,73 +41,6 @@ struct FinBicgInit {  // alpha_n = r.r'
   State *st;
   __device__ bool active() const { return true; }
   __device__ void operator()(DD (&v)[1]) const { st->alpha_n = dd_round(v[0]); }
-};
-
-// alpha_d = v.r', alpha = alpha_n / alpha_d; the restart (if any) is consumed.
-struct FinBicgA {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double ad = dd_round(v[0]);
-    st->plain = st->k == 0 || st->restart;
-    st->restart = 0;
-    if (ad == 0.0 || !finite(ad)) {
-      st->flag = kBreakdown;
-    } else {
-      st->alpha_d = ad;
-      st->alpha = st->alpha_n / ad;
-    }
-  }
-};
-
-// omega = (t.s) / (t.t), 0 if t.t = 0.
-struct FinBicgB {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&d)[2]) const {
-    const double ts = dd_round(d[0]), tt = dd_round(d[1]);
-    st->ts = ts;
-    st->tt = tt;
-    st->omega = (tt == 0.0) ? 0.0 : ts / tt;
-  }
-};
-
-// alpha_n' = r.r', beta = r.r; the restart test, then the convergence test
-// (in that order, as the restart count of the returned iterate includes a
-// restart decided in its last iteration).
-struct FinBicgC {
-  State *st;
-  double restart_tol2;
-  int32_t paper_mode;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&d)[2]) const {
-    const double om = st->omega;
-    const bool half = (om == 0.0);
-    const double an = dd_round(d[0]), beta = dd_round(d[1]);
-    const int64_t k = st->k + 1;
-    st->k = k;
-    st->rho = beta;
-    if (half) {
-      st->flag = (beta <= st->thr2) ? kConverged : kBreakdown;
-      return;
-    }
-    const bool want = paper_mode ? (__builtin_fabs(an) < restart_tol2)
-                                 : (an * an < restart_tol2 * beta);
-    if (want && beta > 0.0 && finite(beta)) {
-      st->restart = 1;
-      st->alpha_n = __builtin_sqrt(beta);
-      st->restarts += 1;
-    } else {
-      st->beta = an / (st->alpha_d * om);
-      st->alpha_n = an;
-    }
-    if (beta <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(beta))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
 };
 
 template <class Op, class P>

@@ -2,6 +2,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "fins.hpp"
 #include "rowops.hpp"
 
 namespace its {
@@ -24,39 +25,6 @@ namespace its {
 // roundings in the same order as updating x at each iteration.  A solve that
 // stops after an even iteration applies the pending update with k_cg_flush_x
 // (k_cg_flush_x32 for the FP32 inner solve).
-
-// alpha = rho / (p.q); p.q = 0 or non-finite is a breakdown.
-struct FinCg1 {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double pq = dd_round(v[0]);
-    if (pq == 0.0 || !finite(pq))
-      st->flag = kBreakdown;
-    else
-      st->alpha = st->rho / pq;
-  }
-};
-
-// rho' = r.r, one more iteration, beta = rho'/rho, convergence test.
-struct FinCg2 {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double rho_new = dd_round(v[0]);
-    const int64_t k = st->k + 1;
-    if (k & 1) st->alpha_x = st->alpha;  // iteration k - 1 (even) deferred its x update
-    st->k = k;
-    st->beta = rho_new / st->rho;
-    st->rho = rho_new;
-    if (rho_new <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(rho_new))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
-};
 
 template <class Op, class T, class P>
 __global__ void __launch_bounds__(kBlock) k_cg_pass1(Op A,

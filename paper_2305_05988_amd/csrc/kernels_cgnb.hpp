@@ -17,6 +17,7 @@
 #pragma once
 
 #include "common.hpp"
+#include "fins.hpp"
 #include "rowops.hpp"
 
 namespace its {
@@ -54,43 +55,6 @@ struct FinCgnbInit {  // alpha_d,0 and alpha_0
     } else {
       st->alpha_d = ad;
       st->alpha = st->rho / ad;
-    }
-  }
-};
-
-// alpha_n,j; beta and gamma for pass Y.
-struct FinCgnbX {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double an_new = dd_round(v[0]), an = st->rho;
-    st->alpha_n = an_new;
-    st->beta = an_new / an;
-    st->gamma = (an * an) / (st->alpha_d * an_new);
-  }
-};
-
-// alpha_d,j; one more iteration; the test on alpha_n,j (the residual of the
-// x_j just formed); alpha_j for the next pass X.
-struct FinCgnbY {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double ad = dd_round(v[0]), an = st->alpha_n;
-    const int64_t k = st->k + 1;
-    st->k = k;
-    st->rho = an;
-    if (an <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(an))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-    else if (ad == 0.0 || !finite(ad))
-      st->flag = kBreakdown;
-    else {
-      st->alpha_d = ad;
-      st->alpha = an / ad;
     }
   }
 };

@@ -2,34 +2,12 @@
 #pragma once
 
 #include "common.hpp"
+#include "fins.hpp"
 #include "csr.hpp"
 #include "sell.hpp"
 #include "stencil.hpp"
 
 namespace its {
-
-// ------------------------------------------------------------------ Jacobi
-// One fused sweep: the residual of x_k (full chain) and x_{k+1} = (b - off)/d.
-// The test applies to x_k, so a converged solve returns x_k from xo.
-// The sweep's residual belongs to x_k: test it; if it fails, x_{k+1} is the
-// new iterate.
-struct FinJacobi {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double rr = dd_round(v[0]);
-    const int64_t k = st->k;
-    st->rho = rr;
-    if (rr <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(rr))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-    else
-      st->k = k + 1;
-  }
-};
 
 template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_jacobi(Op A, const double *__restrict__ b,
@@ -78,43 +56,6 @@ __global__ void __launch_bounds__(kBlock) k_jacobi(Op A, const double *__restric
 // the separate pass: its LDS-tiled stencil SpMV costs less than the extra
 // chains in the sweeps.)
 enum : int32_t { kGsPlain = 0, kGsFinal = 1, kGsLagged = 2 };
-
-// The test after a lagged black sweep: r.r of the iterate = red part (dot 0,
-// from the red sweep that made it) + black part (dot 1).
-struct FinGs2 {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[2]) const {
-    const double rr = dd_round(dd_add(v[0], v[1]));
-    const int64_t k = st->k + 1;
-    st->k = k;
-    st->rho = rr;
-    if (rr <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(rr))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
-};
-
-// Residual of x_{k+1} after a symmetric iteration, and the test.
-struct FinGs {
-  State *st;
-  __device__ bool active() const { return st->flag == kRunning; }
-  __device__ void operator()(DD (&v)[1]) const {
-    const double rr = dd_round(v[0]);
-    const int64_t k = st->k + 1;
-    st->k = k;
-    st->rho = rr;
-    if (rr <= st->thr2)
-      st->flag = kConverged;
-    else if (!finite(rr))
-      st->flag = kBreakdown;
-    else if (k >= st->max_iter)
-      st->flag = kMaxIter;
-  }
-};
 
 // A half-sweep's start: the first of an iteration applies the pending test
 // (FinGs2 with two colours on CSR, FinGs elsewhere), the others have none.
