@@ -280,8 +280,9 @@ int64_t its_matrix_rows(const its_matrix *A);
 
 /* Brick plan of a matrix-free operator (the 7- and 27-point stencils of Section
    3.1 and the variable-coefficient operator) for the passes that march bricks:
-   those of small grids and of the persistent kernels (constant stencils on
-   grids of 786,432 points and more are swept in tiles of their own): plan (host,
+   those of small grids and of the persistent kernels (grids of 786,432 points
+   and more are swept in tiles of their own, with variable coefficients up to 6
+   million): plan (host,
    4 int32, out) = x tiles of 64 points, y tiles of 4 points, z chunks, and
    the z planes per chunk (the last chunk may hold fewer).  A block marches
    one (x tile, y tile, z chunk) brick plane by plane.  Depends only on the

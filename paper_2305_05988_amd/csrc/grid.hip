@@ -107,7 +107,6 @@ template <class Op, bool S, class P>
 __global__ void __launch_bounds__(kBlock) k_grid_jacobi(Op A, const double *__restrict__ b,
                                                         const double *__restrict__ x, double *__restrict__ xn, P ps) {
   __shared__ typename Op::SweepSmem sm;
-  const double diag = A.centre();
   State s;
   Dot2 a;
   const auto begin = [&] { return pass_begin<1>(ps, s, FinJacobi{}); };
@@ -115,7 +114,7 @@ __global__ void __launch_bounds__(kBlock) k_grid_jacobi(Op A, const double *__re
                                [&](int32_t i, const ChainSplit &q, None, double bi) {
                                  const double ri = bi - q.s;
                                  a.add(ri, ri);
-                                 xn[i] = (bi - q.off) / diag;  // the next sweep's x
+                                 xn[i] = (bi - q.off) / q.d;  // the next sweep's x
                                });
   if (!on) return;
   DD v[1] = {a.get()};
@@ -344,8 +343,15 @@ GridOp<NPTS, T, R> make(const GridRun &g) {
   return op;
 }
 
+
 template <class T, class F>
 hipError_t with(const GridRun &g, F &&f) {
+  if constexpr (std::is_same<T, double>::value) {
+    if (g.a->npts == 1) {
+      f(VarGridOp<2>{g.a->nx, g.a->ny, g.a->nz, g.a->n, g.a->k, g.plan});
+      return hipGetLastError();
+    }
+  }
   if (g.a->npts == 7)
     g.points == 4 ? f(make<7, T, 4>(g)) : f(make<7, T, 2>(g));
   else
@@ -377,15 +383,29 @@ bool grid_takes(int32_t nx, int32_t ny, int32_t nz) {
   return nxy * nz >= (int64_t(3) << 18) && nxy < (int64_t(1) << 28);
 }
 
+// Variable coefficients: CG 96^3 28.2 us an iteration by bricks and 27.4 by
+// planes, 131x118x107 46.1 and 39.3, 180^3 104 and 97, but 256^3 254 and 282
+// (two passes form the faces, and there the bricks' one pass and the stored A p
+// cost less); Jacobi 131x118x107 33.7 and 20.3, BiCGStab 93 and 67.
+bool grid_takes_var(int32_t nx, int32_t ny, int32_t nz) {
+  return grid_takes(nx, ny, nz) && int64_t(nx) * ny * nz < (int64_t(6) << 20);
+}
+
 // Two points per thread until four still make two blocks per CU: CG 96^3 22.8 us
 // an iteration with two, 24.3 with four; 256^3 179 with two, 164 with four.
 // 512 blocks of four points, all resident: 256^3 164 us against 174 with 1024.
 // Streaming from 256 MB of vectors on: CG 256^3 (512 MB) 164 us against 197
 // with allocating accesses, 27-point 192^3 (226 MB) 79.6 against 73.3.
+// Variable coefficients: two points per thread throughout (four do not leave
+// registers for two blocks on a CU); 512 blocks up to 3 million cells (128^3
+// 44.4 us against 49.5 with 1024), 1024 beyond (160^3 73.7 against 95.1).
 GridRun grid_run(const GridStencil &a, int64_t vector_bytes, hipStream_t s) {
+  const bool var = a.npts == 1;
+  if (var) vector_bytes += int64_t(8) * a.n;  // k
   GridRun g{&a, {}, 0, 0, vector_bytes > (int64_t(256) << 20), s};
-  g.points = a.n >= (1 << 21) ? 4 : 2;
-  g.plan = grid_plan(a.nx, a.ny, a.nz, g.points, g.points == 4 ? 512 : 1024);
+  g.points = !var && a.n >= (1 << 21) ? 4 : 2;
+  const bool few = var ? a.n < (3 << 20) : g.points == 4;
+  g.plan = grid_plan(a.nx, a.ny, a.nz, g.points, few ? 512 : 1024);
   const int64_t b = int64_t(g.plan.ntx) * g.plan.nty * g.plan.ncz;
   g.blocks = int(std::min<int64_t>(b, kFinishOne));
   if (g.blocks >= 64) g.blocks -= g.blocks % kXcds;

@@ -971,6 +971,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
   // the plane sweep's vectors in the same space: r, and p and p' in turn
   GridStencil grid = A->grid;
   std::memcpy(grid.lo, A->low[dt == ITS_F16], sizeof(grid.lo));
+  if (A->kind == kVar7) grid.npts = 0;  // refused below
   float *rh = w.reg<float>(1), *P[2] = {rh + n, q};
   double bb, rr;
   its_status s = prologue<false>(run, A, w, b, x, r, h, bb, rr);
@@ -1552,7 +1553,7 @@ its_status its_stencil_create(int32_t nx, int32_t ny, int32_t nz, int32_t npts, 
     A->low[1][o] = float(static_cast<_Float16>(coef[o]));
   }
   if (grid_takes(nx, ny, nz)) {
-    A->grid = GridStencil{npts, nx, ny, nz, int32_t(n), {}, {}};
+    A->grid = GridStencil{npts, nx, ny, nz, int32_t(n), {}, {}, nullptr};
     for (int o = 0; o < npts; ++o) A->grid.c[o] = coef[o];
   }
   *out = A;
@@ -1612,6 +1613,14 @@ its_status its_varcoef_create(int32_t nx, int32_t ny, int32_t nz, const double *
   A->ny = ny;
   A->nz = nz;
   A->kcoef = k;
+  if (grid_takes_var(nx, ny, nz)) {
+    A->grid.npts = 1;
+    A->grid.nx = nx;
+    A->grid.ny = ny;
+    A->grid.nz = nz;
+    A->grid.n = int32_t(n);
+    A->grid.k = k;
+  }
   *out = A;
   return ITS_OK;
 }
