@@ -574,10 +574,11 @@ its_status flag_to_status(int32_t f) {
   }
 }
 
-int batch_size(const its_options *o, int64_t n) {
-  if (o->check_every > 0) return o->check_every;
-  return n >= (int64_t(1) << 20) ? 8 : 32;
-}
+// 32 iterations between two reads of the State: a read idles the GPU for ~20 us,
+// an iteration too many costs ~5.  Against 8: 40 Jacobi sweeps 720 -> 676 us,
+// CG 131x118x107 (46 us an iteration) 38.1 -> 37.2 ms, 256^3 80.1 -> 79.5 ms; 64
+// loses where a solve has few hundred iterations (45x38x41 1.74 -> 2.06 ms).
+int batch_size(const its_options *o) { return o->check_every > 0 ? o->check_every : 32; }
 
 // Runs iterations j = j0, j0+1, ... until the device flag leaves kRunning or
 // max_iter iterations were launched; `step(j, first, last)` launches iteration
@@ -847,13 +848,13 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
     return ITS_OK;
   }
   if (flag == kRunning && grid) {
-    s = cg_grid(run, A->grid, w, w.st, h, o->max_iter, batch_size(o, n), x, r, P);
+    s = cg_grid(run, A->grid, w, w.st, h, o->max_iter, batch_size(o), x, r, P);
     if (s != ITS_OK) return s;
   } else if (flag == kRunning) {
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
       Flow f(run, w, w.st);
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
         Pass p;
         if (first) f.start();
         TRY(f.enter<1>(GA, FinCg2{}, 0, p));
@@ -913,7 +914,7 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
       Flow f(run, w, w.st);
       if (A->grid.npts) {
         GridRun g = grid_run(A->grid, 40 * A->n, run.s);  // {r, A p}, p, w, x
-        return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+        return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
           Pass ps;
           if (first) f.start();
           TRY(f.enter<1>(g.blocks, FinCgnbY{}, 0, ps));
@@ -925,7 +926,7 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
           return last ? f.end<1>(FinCgnbY{}) : ITS_OK;
         });
       }
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
         Pass ps;
         if (first) f.start();
         TRY(f.enter<1>(GA, FinCgnbY{}, 0, ps));
@@ -1011,7 +1012,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
     if (!(rho_i <= ithr2)) {
       LAUNCH(run, kClassOther, k_begin, 1, w.st2, (int32_t)kRunning, rho_i, ithr2, budget);
       if (grid.npts)
-        s = cg_grid(run, grid, w, w.st2, h, budget, batch_size(o, n), d, rh, P);
+        s = cg_grid(run, grid, w, w.st2, h, budget, batch_size(o), d, rh, P);
       else
       s = with_op32(A, dt, [&](auto op) -> its_status {
         // two rows per lane where it pays (measured): FP16 values, or
@@ -1023,7 +1024,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
         if constexpr (PairWalk<decltype(op)>::value)
           if (pairs) GA = op.grid_pairs(A->sell_wmax > 7);
         Flow f(run, w, w.st2);
-        return iterate(run, w.st2, h, budget, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+        return iterate(run, w.st2, h, budget, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
           Pass p;
           if (first) f.start();
           TRY(f.enter<1>(GA, FinCg2{}, 0, p));
@@ -1099,7 +1100,7 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
       GridRun g = grid_run(A->grid, 48 * A->n, run.s);  // r, its next, u, r', v, x
       Flow f(run, w, w.st);
       const FinBicgC fc{nullptr, rt2, paper};
-      s = iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+      s = iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
         double *r = rr2[j & 1], *rn = rr2[(j & 1) ^ 1];
         Pass ps;
         if (first) f.start();
@@ -1128,7 +1129,7 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
       }
       Flow f(run, w, w.st);
       const FinBicgC fc{nullptr, rt2, paper};
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
         Pass ps;
         if (first) f.start();
         TRY(f.enter<2>(GA, fc, 0, ps));
@@ -1186,7 +1187,7 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
   if (A->grid.npts) {
     GridRun g = grid_run(A->grid, 24 * A->n, run.s);  // x, its next, b
     Flow f(run, w, w.st);
-    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
       const int a = int(j & 1);
       Pass ps;
       if (first) f.start();
@@ -1199,7 +1200,7 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
     s = with_op64(A, [&](auto op) -> its_status {
     const int GA = op.grid();
     Flow f(run, w, w.st);
-    return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+    return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
       const int a = int(j & 1);
       Pass p;
       if (first) f.start();
@@ -1322,7 +1323,7 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
     // The red partials (dot 0) of iteration j - 1 and the black ones (dot 1)
     // of iteration j make the test that iteration j's red sweep applies before
     // it writes its own red partials: those alternate between two regions.
-    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
       if (first) f.start();
       const int red = int(j & 1);
       if (j == 0) {
@@ -1344,7 +1345,7 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
     if (A->grid.npts) g = grid_run(A->grid, 16 * A->n, run.s);  // x, b
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
-      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
         if (first) f.start();
         for (int c = (j == 0 ? 0 : 1); c < nc; ++c) TRY(sweep(c, 2, Plain{}));
         for (int c = nc - 2; c >= 0; --c) TRY(sweep(c, 2, Plain{}));
