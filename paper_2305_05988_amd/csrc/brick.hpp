@@ -49,7 +49,7 @@ inline int brick_grid(const BrickGeom &g) {
   int64_t b = int64_t(g.nbx) * g.nby * g.nbz;
   if (b < 1) b = 1;
   int grid = int(b < kMaxGrid ? b : kMaxGrid);
-  if (grid >= 64) grid -= grid % kXcds;
+  if (grid >= 64) grid = (grid + kXcds - 1) / kXcds * kXcds;  // as grid_for
   return grid;
 }
 

@@ -578,8 +578,10 @@ inline int grid_for(int64_t n, int max_blocks = kMaxGrid) {
   int64_t tiles = (n + kBlock - 1) / kBlock;
   if (tiles < 1) tiles = 1;
   if (tiles > kFinishOne && tiles <= 4 * kFinishOne) tiles = kFinishOne;
+  // up to the next multiple of 8 (XCDs), not down: a block without a tile costs
+  // nothing, a second tile for one block would be a second round of the pass
   int g = int(tiles < max_blocks ? tiles : max_blocks);
-  if (g >= 64) g -= g % kXcds;
+  if (g >= 64) g = g < max_blocks ? (g + kXcds - 1) / kXcds * kXcds : g / kXcds * kXcds;
   return g;
 }
 
