@@ -175,6 +175,10 @@ struct FinJacobi {
   }
 };
 
+// What a half-sweep of Gauss-Seidel with two colours does besides updating its
+// rows (kernels_relax.hpp).
+enum : int32_t { kGsPlain = 0, kGsFinal = 1, kGsLagged = 2 };
+
 // The test after a lagged black sweep: r.r of the iterate = red part (dot 0,
 // from the red sweep that made it) + black part (dot 1).
 struct FinGs2 {

@@ -114,11 +114,58 @@ __global__ void __launch_bounds__(kBlock) k_grid_jacobi(Op A, const double *__re
                                [&](int32_t i, const ChainSplit &q, None, double bi) {
                                  const double ri = bi - q.s;
                                  a.add(ri, ri);
-                                 xn[i] = (bi - q.off) / q.d;  // the next sweep's x
+                                 xn[i] = (bi - q.off) / A.diagonal(q);  // the next sweep's x
                                });
   if (!on) return;
   DD v[1] = {a.get()};
   block_partial_to<1>(v, ps.dst);
+}
+
+// A red-black Gauss-Seidel half-sweep over the rows of one colour (the parity
+// of x + y + z), in place, with the residual test riding on the sweeps as in
+// k_gs_rows_packed (kGsFinal, kGsLagged).  A row reads only rows of the other
+// colour, which no block writes.  xs: the old values of the black rows, row i at
+// i / 2 (two neighbours in a line, or the last point of a line and the first
+// of the next where they share a pair, have different colours).  Whole lines
+// are stored, the other colour's values as they were.
+template <class Op, int Mode, class P>
+__global__ void __launch_bounds__(kBlock) k_grid_gs(Op A, uint32_t colour, const double *__restrict__ b, double *x,
+                                                    double *__restrict__ xs, P ps) {
+  __shared__ typename Op::SweepSmem sm;
+  using Chain = std::conditional_t<Mode == kGsFinal, ChainTwice, ChainSplit>;
+  State s;
+  Dot2 a;
+  const auto begin = [&] { return pass_begin<2>(ps, s, FinGs2{}); };
+  const bool on = A.template sweep<Chain>(
+      sm, One<double>{x}, begin, Same{}, KeepValue{}, [&](int32_t i) { return b[i]; },
+      [&](int32_t i, const Chain &q, double xi, double bi, uint32_t odd, bool last) {
+        double xn = xi;
+        if (odd == colour) {
+          xn = (bi - q.off) / A.diagonal(q);
+          double ri = 0.0;
+          if constexpr (Mode == kGsLagged) {
+            ri = bi - q.s;
+            xs[i >> 1] = xi;
+          }
+          if constexpr (Mode == kGsFinal) ri = bi - q.with(A.c, xn, last);
+          if constexpr (Mode != kGsPlain) a.add(ri, ri);
+        }
+        x[i] = xn;
+      });
+  if (!on) return;
+  if constexpr (Mode != kGsPlain) {
+    DD v[1] = {a.get()};
+    block_partial_to<1>(v, ps.dst);
+  }
+}
+
+// The black rows of the tested iterate put back.
+__global__ void __launch_bounds__(kBlock) k_grid_gs_restore(int32_t n, int32_t nx, int32_t ny,
+                                                            const double *__restrict__ xs, double *__restrict__ x) {
+  for_rows(n, [&](int32_t i) {
+    const int32_t t = i / nx, ix = i - t * nx, iz = t / ny, iy = t - iz * ny;
+    if ((ix + iy + iz) & 1) x[i] = xs[i >> 1];
+  });
 }
 
 // CG in 7.5 vectors an iteration (the pair form of k_cg_pass1 and k_cg_pass2
@@ -477,6 +524,29 @@ hipError_t grid_bicg_b(const GridRun &g, const double *r, const double *v, const
 hipError_t grid_bicg_c(const GridRun &g, const double *r, double *rn, double *u, const double *v, const double *rs,
                        double *x, const Pass &ps) {
   GRID_LAUNCH_STREAM(ps, (k_grid_bicg_c<Op, S, P>), r, rn, u, v, rs, x);
+}
+
+hipError_t grid_gs(const GridRun &g, int mode, int colour, const double *b, double *x, double *xs, const Pass &ps) {
+  auto go = [&](auto op, auto m) {
+    using Op = decltype(op);
+    constexpr int M = decltype(m)::value;
+    with_pass(ps, [&](auto p) {
+      hipLaunchKernelGGL((k_grid_gs<Op, M, decltype(p)>), dim3(g.blocks), dim3(kBlock), 0, g.s, op, uint32_t(colour), b,
+                         x, xs, p);
+    });
+  };
+  auto modes = [&](auto op) {
+    if (mode == kGsPlain) go(op, std::integral_constant<int, kGsPlain>());
+    if (mode == kGsFinal) go(op, std::integral_constant<int, kGsFinal>());
+    if (mode == kGsLagged) go(op, std::integral_constant<int, kGsLagged>());
+  };
+  g.points == 4 ? modes(make<7, double, 4>(g)) : modes(make<7, double, 2>(g));
+  return hipGetLastError();
+}
+hipError_t grid_gs_restore(const GridRun &g, const double *xs, double *x) {
+  hipLaunchKernelGGL(k_grid_gs_restore, dim3(grid_for(g.a->n, kFinishOne)), dim3(kBlock), 0, g.s, g.a->n, g.a->nx,
+                     g.a->ny, xs, x);
+  return hipGetLastError();
 }
 
 }  // namespace its

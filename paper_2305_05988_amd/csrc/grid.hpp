@@ -51,12 +51,16 @@ inline GridPlan grid_plan(int32_t nx, int32_t ny, int32_t nz, int R, int blocks)
   return best;
 }
 
-// The plain chain of a row.
+// The plain chain of a row.  add: an entry below the diagonal; centre: the
+// diagonal; above: an entry above it (the 7-point sweeps number theirs: at x +
+// 1, y + 1 and z + 1).
 template <class T>
 struct ChainSum {
   T s = T(0);
   __device__ __forceinline__ void add(T a, T v) { s = fmaT(a, v, s); }
   __device__ __forceinline__ void centre(T a, T v) { s = fmaT(a, v, s); }
+  template <int Q>
+  __device__ __forceinline__ void above(T a, T v) { add(a, v); }
 };
 
 // The chain, the chain without the diagonal, and the diagonal.
@@ -70,6 +74,29 @@ struct ChainSplit {
     s = fma(a, v, s);
     d = a;
   }
+  template <int Q>
+  __device__ __forceinline__ void above(double a, double v) { add(a, v); }
+};
+
+// The chain without the diagonal, and what it takes to run the whole chain
+// again with another value of the row itself (7 points).
+struct ChainTwice {
+  double low = 0.0, off = 0.0, v[3];
+  __device__ __forceinline__ void add(double a, double x) {
+    low = fma(a, x, low);
+    off = fma(a, x, off);
+  }
+  __device__ __forceinline__ void centre(double, double) {}
+  template <int Q>
+  __device__ __forceinline__ void above(double a, double x) {
+    off = fma(a, x, off);
+    v[Q] = x;
+  }
+  // c: the stencil; last: the row has an entry at z + 1
+  __device__ __forceinline__ double with(const double (&c)[7], double x, bool last) const {
+    const double s = fma(c[5], v[1], fma(c[4], v[0], fma(c[3], x, low)));
+    return last ? fma(c[6], v[2], s) : s;
+  }
 };
 
 // A thread's points of a tile: in-plane row (0 where it has none), LDS index to
@@ -77,7 +104,7 @@ struct ChainSplit {
 template <int R>
 struct TilePoints {
   static constexpr int kPts = kBlock * R + kBlock;  // tile and ring
-  uint32_t off[R], ok = 0, hoff = 0;
+  uint32_t off[R], ok = 0, odd = 0, hoff = 0;  // odd: x + y
   int wr[R], rd[R], hwr = kPts;  // kPts: written by threads without a point
   __device__ __forceinline__ TilePoints(int32_t W, int32_t H, int32_t x0, int32_t y0, int32_t nx, int32_t ny,
                                         bool corners) {
@@ -92,6 +119,7 @@ struct TilePoints {
       rd[u] = in ? (y + 1) * pitch + x + 1 : pitch + 1;
       wr[u] = in ? rd[u] : kPts;
       ok |= uint32_t(in) << u;
+      odd |= uint32_t((x0 + x + y0 + y) & 1) << u;
     }
     if (t < 2 * pitch + 2 * H) {
       const int32_t q = t - 2 * pitch;
@@ -113,7 +141,18 @@ struct TilePoints {
 //   value(raw)           the vector's value there
 //   keep(raw, value)     what the body needs of the point's own load
 //   side(i)              what the body loads for its own row besides
-//   body(i, chain, kept, side)  for every row of the tile, in order of planes
+//   body(i, chain, kept, side)  for every row of the tile, in order of planes;
+//                        a body of six arguments also gets the parity of x + y
+//                        + z and whether the row has a row above it
+template <class Body, class Chain, class Kept, class Extra>
+__device__ __forceinline__ void call_body(Body &body, int32_t i, const Chain &ch, const Kept &own, const Extra &ex,
+                                          uint32_t odd, bool last) {
+  if constexpr (std::is_invocable_v<Body &, int32_t, const Chain &, const Kept &, const Extra &, uint32_t, bool>)
+    body(i, ch, own, ex, odd, last);
+  else
+    body(i, ch, own, ex);
+}
+
 template <int NPTS, class T, int R>
 struct GridOp {
   int32_t nx, ny, nz, n;
@@ -124,6 +163,11 @@ struct GridOp {
   struct SweepSmem {
     T v[2][kPts + 1];
   };
+
+  template <class Chain>
+  __device__ __forceinline__ T diagonal(const Chain &) const {
+    return c[NPTS / 2];
+  }
 
 
   template <class Chain, class Load, class Begin, class Value, class Keep, class Side, class Body>
@@ -166,7 +210,8 @@ struct GridOp {
         const int32_t zo = int32_t(nxy * z);
 #pragma unroll
         for (int u = 0; u < R; ++u)
-          if ((ok >> u) & 1u) body(zo + int32_t(off[u]), ch[u], own[u], ex[u]);
+          if ((ok >> u) & 1u)
+            call_body(body, zo + int32_t(off[u]), ch[u], own[u], ex[u], ((pt.odd >> u) ^ uint32_t(z)) & 1u, z < nz - 1);
       };
       issue(zs);
       for (int k = t; k < 2 * (kPts + 1); k += kBlock) (&sm.v[0][0])[k] = T(0);
@@ -189,7 +234,7 @@ struct GridOp {
           pl[hwr] = value(rawh);
           if (z > z0) {  // rows z - 1 are complete
 #pragma unroll
-            for (int u = 0; u < R; ++u) ch[u].add(c[6], nv[u]);
+            for (int u = 0; u < R; ++u) ch[u].template above<2>(c[6], nv[u]);
             finish(z - 1, ch, own);
           }
 #pragma unroll
@@ -206,8 +251,8 @@ struct GridOp {
               q.add(c[1], p[-pitch]);
               q.add(c[2], p[-1]);
               q.centre(c[3], nv[u]);
-              q.add(c[4], p[1]);
-              q.add(c[5], p[pitch]);
+              q.template above<0>(c[4], p[1]);
+              q.template above<1>(c[5], p[pitch]);
               ch[u] = q;
             }
           }
@@ -284,6 +329,8 @@ struct VarGridOp {
     double v[2][kPts + 1], k[2][kPts + 1];
     int wide;  // a k outside the range was met
   };
+
+  __device__ __forceinline__ double diagonal(const ChainSplit &q) const { return q.d; }
 
   __device__ static __forceinline__ bool plain(double k) {
     const uint32_t e = uint32_t(__builtin_bit_cast(uint64_t, k) >> 52);

@@ -56,5 +56,9 @@ hipError_t grid_bicg_a(const GridRun &g, const double *r, const double *u, doubl
 hipError_t grid_bicg_b(const GridRun &g, const double *r, const double *v, const Pass &ps);
 hipError_t grid_bicg_c(const GridRun &g, const double *r, double *rn, double *u, const double *v, const double *rs,
                        double *x, const Pass &ps);
+// Half-sweeps of red-black Gauss-Seidel (7 points; modes of kernels_relax.hpp;
+// xs: n / 2 rounded up values).
+hipError_t grid_gs(const GridRun &g, int mode, int colour, const double *b, double *x, double *xs, const Pass &ps);
+hipError_t grid_gs_restore(const GridRun &g, const double *xs, double *x);
 
 }  // namespace its

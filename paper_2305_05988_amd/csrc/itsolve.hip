@@ -94,6 +94,7 @@ struct its_matrix {
     PatArrays pat;
   };
   std::vector<ColorPack> cpack;
+  bool red_black = false;  // grid (7 points): the two colours are the parities of x + y + z
   // A^T (its_csr_transpose): a CSR handle that owns its arrays (own_*)
   its_matrix *tr = nullptr;
   int32_t *own_rp = nullptr, *own_col = nullptr;
@@ -123,6 +124,7 @@ static void free_color_packs(its_matrix *A) {
     c.pat.release();
   }
   A->cpack.clear();
+  A->red_black = false;
 }
 
 static void drop_graph(its_matrix *A);
@@ -1313,7 +1315,33 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
   using Plain = std::integral_constant<int, kGsPlain>;
   using Final = std::integral_constant<int, kGsFinal>;
   using Lagged = std::integral_constant<int, kGsLagged>;
-  if (flag == kRunning && nc == 2 && A->kind == kCsr) {
+  if (flag == kRunning && A->red_black) {
+    // the two colours' sweeps and tests as below, plane by plane
+    GridRun g = grid_run(A->grid, 24 * A->n, run.s);  // x, b, the saved rows
+    auto half = [&](int c, int mode, int region) -> its_status {
+      Pass p;
+      TRY(enter(g.blocks, mode != kGsPlain, region, p));
+      if (mode == kGsLagged) p.dst[0] = p.dst[1];  // the black partials are the test's dot 1
+      LAUNCH_GRID(run, 0, g, grid_gs(g, mode, c, b, x, xs, p));
+      return ITS_OK;
+    };
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+      if (first) f.start();
+      const int red = int(j & 1);
+      if (j == 0) {
+        TRY(half(0, kGsPlain, 0));
+        TRY(half(1, kGsPlain, 0));
+      } else {
+        TRY(half(1, kGsLagged, 2));
+        TRY(f.join(g.blocks, red ^ 1, 2));
+      }
+      TRY(half(0, kGsFinal, red));
+      return last ? f.end<2>(FinGs2{}) : ITS_OK;
+    }, /*eager_first=*/true);
+    if (s != ITS_OK) return s;
+    LAUNCH_GRID(run, kClassOther, g, grid_gs_restore(g, xs, x));
+    HIP_TRY(hipStreamSynchronize(run.s));
+  } else if (flag == kRunning && nc == 2 && A->kind == kCsr) {
     // Iteration 1 sweeps red, black, red; iteration j > 1 black, red.  The
     // test of iterate j rides on the sweeps: its red residual on iteration
     // j's last (red) sweep, its black residual on iteration j + 1's black
@@ -1554,6 +1582,7 @@ its_status its_stencil_create(int32_t nx, int32_t ny, int32_t nz, int32_t npts, 
     A->low[1][o] = float(static_cast<_Float16>(coef[o]));
   }
   if (grid_takes(nx, ny, nz)) {
+    A->red_black = npts == 7;
     A->grid = GridStencil{npts, nx, ny, nz, int32_t(n), {}, {}, nullptr};
     for (int o = 0; o < npts; ++o) A->grid.c[o] = coef[o];
   }
@@ -2012,6 +2041,21 @@ static its_status pack_colors(its_matrix *A, hipStream_t s) {
     packs.push_back(cp);
   }
   A->cpack = packs;
+  if (A->grid.npts == 7 && A->ncolors == 2) {
+    DevTmp bad;
+    uint32_t hbad = 1;
+    HIP_TRY(hipMalloc(&bad.p, sizeof(uint32_t)));
+    HIP_TRY(hipMemsetAsync(bad.p, 0, sizeof(uint32_t), s));
+    for (int32_t c = 0; c < 2; ++c) {
+      const int32_t beg = A->color_off[size_t(c)], cnt = A->color_off[size_t(c) + 1] - beg;
+      hipLaunchKernelGGL(k_colour_parity, dim3(grid_for(cnt)), dim3(kBlock), 0, s, cnt,
+                         (const int32_t *)(A->color_rows + beg), A->grid.nx, A->grid.ny, c, static_cast<uint32_t *>(bad.p));
+      HIP_TRY(hipGetLastError());
+    }
+    HIP_TRY(hipMemcpyAsync(&hbad, bad.p, sizeof(uint32_t), hipMemcpyDeviceToHost, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    A->red_black = hbad == 0;
+  }
   return ITS_OK;
 }
 
@@ -2342,6 +2386,7 @@ static its_status solve_impl(const its_matrix *Ac, const its_options *o, const d
     At.nz = A->nz;
     const int np = A->kind == kSten7 ? 7 : 27;
     At.grid = A->grid;
+    At.red_black = A->red_black;
     for (int q = 0; q < np; ++q) {
       At.coef[q] = At.grid.c[q] = A->coef[np - 1 - q];
       for (int l = 0; l < 2; ++l) At.low[l][q] = A->low[l][np - 1 - q];

@@ -55,7 +55,6 @@ __global__ void __launch_bounds__(kBlock) k_jacobi(Op A, const double *__restric
 // r.r equals the separate pass's bit for bit.  (The matrix-free sweeps keep
 // the separate pass: its LDS-tiled stencil SpMV costs less than the extra
 // chains in the sweeps.)
-enum : int32_t { kGsPlain = 0, kGsFinal = 1, kGsLagged = 2 };
 
 // A half-sweep's start: the first of an iteration applies the pending test
 // (FinGs2 with two colours on CSR, FinGs elsewhere), the others have none.

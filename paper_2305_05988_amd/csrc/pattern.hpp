@@ -413,4 +413,14 @@ __global__ void __launch_bounds__(kBlock) k_grid_match(int32_t n, int32_t nx, in
   }
 }
 
+// Counts into *bad the rows rows[0 .. count) of an nx*ny grid whose parity of
+// x + y + z is not `colour`.
+__global__ void __launch_bounds__(kBlock) k_colour_parity(int32_t count, const int32_t *__restrict__ rows, int32_t nx,
+                                                          int32_t ny, int32_t colour, uint32_t *bad) {
+  for_rows(count, [&](int32_t p) {
+    const int32_t i = rows[p], t = i / nx, ix = i - t * nx, iz = t / ny, iy = t - iz * ny;
+    if (((ix + iy + iz) & 1) != colour) atomicAdd(bad, 1u);
+  });
+}
+
 }  // namespace its

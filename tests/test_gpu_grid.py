@@ -173,3 +173,25 @@ def test_variable_coefficients(g, far):
             continue
         _check(A, b, ref, rr, method, 3)
 
+
+# odd and even lines; two and four points per thread; the colours swapped (no
+# plane sweep, the colours' own rows)
+@pytest.mark.parametrize("g", [GRIDS[0], GRIDS[1], GRIDS[6], GRIDS[9]])
+def test_red_black(g):
+    Acsr, _, b = _system(g, COEF[7])
+    colors = inputs.redblack_colors(*g)
+    ref = oracle.sgs(Acsr, colors, 2, b, rtol=0.0, max_iter=3)
+    S = its().StencilMatrix(*g, COEF[7])
+    A = _operator(Acsr, g, COEF[7], "packed")
+    A.set_colors(colors, 2)
+    for M in (S, A):
+        _check(M, b, *ref, "sgs", 3)
+        _check(M, b, *ref, "sgs", 3, graph=True)
+        # a solve that stops at a tolerance returns the tested iterate
+        rtol = 0.5 * (ref[1].rel_res + oracle.sgs(Acsr, colors, 2, b, rtol=0.0, max_iter=2)[1].rel_res)
+        x, info = its().solve(M, dev(b), method="sgs", rtol=rtol, max_iter=50)
+        assert info.status == "ok" and info.iters == 3 and np.array_equal(x.cpu().numpy(), ref[0])
+    if g == GRIDS[0]:
+        swapped = (1 - colors).astype(np.uint8)
+        A.set_colors(swapped, 2)
+        _check(A, b, *oracle.sgs(Acsr, swapped, 2, b, rtol=0.0, max_iter=2), "sgs", 2)
