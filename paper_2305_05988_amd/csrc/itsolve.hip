@@ -405,6 +405,24 @@ its_status with_op64(const its_matrix *A, F &&f) {
   }
 }
 
+// The operator of a persistent kernel: matrix-free stencils by rows on grids of
+// at most 131,072 points.
+template <class F>
+its_status with_persistent(const its_matrix *A, F &&f) {
+  if (A->n <= (int64_t(1) << 17) && (A->kind == kSten7 || A->kind == kSten27)) {
+    auto rows = [&](auto op) -> its_status {
+      op.nx = A->nx;
+      op.ny = A->ny;
+      op.nz = A->nz;
+      op.n = int32_t(A->n);
+      for (size_t q = 0; q < sizeof(op.c) / sizeof(op.c[0]); ++q) op.c[q] = A->coef[q];
+      return f(op);
+    };
+    return A->kind == kSten7 ? rows(StencilRows<7>()) : rows(StencilRows<27>());
+  }
+  return with_op64(A, f);
+}
+
 template <class F>
 its_status with_op32(const its_matrix *A, int dtype, F &&f) {
   switch (A->kind) {
@@ -839,7 +857,7 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
   else if (o->max_iter <= 0) flag = kMaxIter;
   LAUNCH(run, kClassOther, k_begin, 1, w.st, flag, rr, thr2, (int64_t)o->max_iter);
   if (flag == kRunning && o->persistent) {
-    s = with_op64(A, [&](auto op) -> its_status {
+    s = with_persistent(A, [&](auto op) -> its_status {
       return persist_launch(run, h, k_cg_persist<decltype(op)>, op.grid(), w, op, x, rp, q, b, w.st, w.R);
     });
     if (s != ITS_OK) return s;
@@ -911,8 +929,10 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
       LAUNCH(run, kClassOther, k_cgnb_init<decltype(op)>, GA, op, ra, p, w.R);
       FINISH(run, 1, w.R, GA, (FinCgnbInit{w.st}));
       if (o->persistent)
-        return persist_launch(run, h, k_cgnb_persist<decltype(op)>, GA, w, op, x, ra, w.reg<double2_t>(3), p, wv, b,
-                              w.st, w.R);
+        return with_persistent(A, [&](auto po) -> its_status {
+          return persist_launch(run, h, k_cgnb_persist<decltype(po)>, po.grid(), w, po, x, ra, w.reg<double2_t>(3), p, wv,
+                                b, w.st, w.R);
+        });
       Flow f(run, w, w.st);
       if (A->grid.npts) {
         GridRun g = grid_run(A->grid, 40 * A->n, run.s);  // {r, A p}, p, w, x
@@ -1123,11 +1143,13 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
       if (o->persistent) {
         // BiCGStab-B1's split-phase schedule (ITS_BICGSTAB_SPLIT=0: the same
         // updates after the waits, classical BiCGStab's blocking points)
-        if (env_int("ITS_BICGSTAB_SPLIT", 1) != 0)
-          return persist_launch(run, h, k_bicg_persist<decltype(op), true>, GA, w, op, x, ru, rs, p, rv, t, b,
+        return with_persistent(A, [&](auto po) -> its_status {
+          if (env_int("ITS_BICGSTAB_SPLIT", 1) != 0)
+            return persist_launch(run, h, k_bicg_persist<decltype(po), true>, po.grid(), w, po, x, ru, rs, p, rv, t, b,
+                                  w.st, w.R, rt2, paper);
+          return persist_launch(run, h, k_bicg_persist<decltype(po), false>, po.grid(), w, po, x, ru, rs, p, rv, t, b,
                                 w.st, w.R, rt2, paper);
-        return persist_launch(run, h, k_bicg_persist<decltype(op), false>, GA, w, op, x, ru, rs, p, rv, t, b,
-                              w.st, w.R, rt2, paper);
+        });
       }
       Flow f(run, w, w.st);
       const FinBicgC fc{nullptr, rt2, paper};

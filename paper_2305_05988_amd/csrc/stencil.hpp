@@ -140,6 +140,34 @@ struct StencilOp {
   }
 };
 
+// The same operator one row per thread in 1-D tiles, its neighbours gathered:
+// for the persistent kernels on small grids, whose bricks are one plane thin and
+// load three planes one after the other (32^3 CG 13.6 -> 10.4 us an iteration,
+// BiCGStab 23.6 -> 18.2; 48^3 17.8 -> 13.5).
+template <int NPTS>
+struct StencilRows : StencilOp<NPTS, double> {
+  struct Smem {};
+  int grid() const { return grid_for(this->n); }
+  template <class Load, class Value, class Body>
+  __device__ __forceinline__ void rows(Smem &, Load &&load, Value &&value, Body &&body) const {
+    for_tiles(this->n, [&](int32_t r0, int32_t r1) {
+      const int32_t i = r0 + int32_t(threadIdx.x);
+      auto entries = [&](auto &&consume) {
+        const int32_t row = min(i, r1 - 1);
+        int32_t ix, iy, iz;
+        this->coords(row, ix, iy, iz);
+        this->row_entries_at(row, ix, iy, iz, load, [&](int32_t j, double a, const auto &raw) { consume(j, a, value(raw)); });
+      };
+      auto own = [&]() { return value(load(i)); };
+      body(i, i < r1, entries, own);
+    });
+  }
+  template <class Body>
+  __device__ __forceinline__ void own_rows(Body &&body) const {
+    tiled_own_rows(*this, body);
+  }
+};
+
 // Operators of a 3-D grid get their brick plan on the host.
 template <class Op>
 inline void plan_op(Op &) {}

@@ -59,3 +59,17 @@ def test_both_sides(pack, n, method, graph):
         assert info.iters == rr.iters
         assert np.array_equal(x.cpu().numpy(), ref)
         assert abs(info.rel_res - rr.rel_res) <= 1e-12 * rr.rel_res
+
+
+# the persistent kernels of matrix-free stencils: rows up to 131,072 points,
+# bricks beyond; one row per thread up to 256 blocks (65,536 rows) and several
+@pytest.mark.parametrize("method", ["cg", "cgnb", "bicgstab"])
+@pytest.mark.parametrize("g", [(1, 1, 1), (64, 32, 32), (64, 33, 32), (64, 32, 64), (64, 33, 63)])
+@pytest.mark.parametrize("points", [7, 27])
+def test_persistent_stencils(points, g, method):
+    coef = {7: inputs.convdiff7() if method == "bicgstab" else inputs.POISSON7, 27: inputs.STENCIL27}[points]
+    Acsr = inputs.stencil_csr(*g, coef)
+    b = inputs.uniform_vector(Acsr[0].size - 1, 3)
+    ref, rr = getattr(oracle, method)(Acsr, b, rtol=0.0, max_iter=4)
+    x, info = its().solve(its().StencilMatrix(*g, coef), dev(b), method=method, rtol=0.0, max_iter=4, persistent=True)
+    assert info.iters == rr.iters and np.array_equal(x.cpu().numpy(), ref)
