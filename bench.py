@@ -479,7 +479,7 @@ def differentiation(its, inputs):
     V = 8 * n
     out["diff_varcoef_128"] = {
         "forward_iters": fi.iters, "forward_s": t_fwd, "forward_iters_per_s": fi.iters / t_fwd,
-        "forward_achieved_gbs": fi.iters / t_fwd * 11 * V / 1e9,
+        "forward_achieved_gbs": fi.iters / t_fwd * 9.5 * V / 1e9,
         "adjoint_iters": ai.iters, "backward_s": t_bwd, "autograd_forward_backward_s": t_auto,
         "loss": L.item(), "grad_theta_norm": theta.grad.norm().item(),
         "grad_b_norm": b.grad.norm().item(),
@@ -571,20 +571,20 @@ def kernel_suite(its, inputs, iters=10):
     del rp, col, val
     b = its.spmv(A, torch.from_numpy(inputs.uniform_vector(n, 1)).cuda())
     V, V32 = 8 * n, 4 * n
-    M, M32, M16 = packed_matrix_bytes(A, n), packed_matrix_bytes(A, n, "f32"), packed_matrix_bytes(A, n, "f16")
+    M, M32 = packed_matrix_bytes(A, n), packed_matrix_bytes(A, n, "f32")
     log(f"kernels: cg 256^3 ({iters} iterations)")
     run(A, b, method="cg", rtol=0.0, max_iter=iters)
     log(f"kernels: jacobi 256^3 ({iters} sweeps)")
     run(A, b, method="jacobi", rtol=0.0, max_iter=iters)
-    for lowp, Ml in (("f32", M32), ("f16", M16)):
+    for lowp in ("f32", "f16"):
         log(f"kernels: refinement ({lowp} values) 256^3 ({iters} inner iterations)")
         run(A, b, method="cg", rtol=1e-12, max_iter=iters, inner_dtype=lowp, inner_rtol=1e-30)
     out["poisson256_packed"] = {
-        "n": n, "grid_spmv": (n + 255) // 256,
-        "k_cg_pass1<SellOp<double": M + 3 * V, "k_cg_pass2<double, true": 6 * V,
-        "k_jacobi<SellOp<double": M + 3 * V,
-        "k_cg_pass1<SellOp<float": M32 + 3 * V32, "k_cg_pass1_pairs<SellOp<__half": M16 + 3 * V32,
-        "k_cg_pass2_f32x2": 6 * V32, "k_residual<SellOp<double": M + 3 * V}
+        "n": n,
+        "k_grid_cg_a<GridOp<7, double": M + 3 * V, "k_grid_cg_b<GridOp<7, double": int(4.5 * V),
+        "k_grid_jacobi<GridOp<7, double": M + 3 * V,
+        "k_grid_cg_a<GridOp<7, float": M32 + 3 * V32, "k_grid_cg_b<GridOp<7, float": int(4.5 * V32),
+        "k_grid_residual<GridOp<7, double": M + 3 * V}
     del A, b
     torch.cuda.empty_cache()
     # 256^3 matrix-free 7-point stencil
@@ -594,9 +594,8 @@ def kernel_suite(its, inputs, iters=10):
     run(S, b, method="cg", rtol=0.0, max_iter=iters)
     log(f"kernels: matrix-free red-black sgs 256^3 ({iters} iterations)")
     run(S, b, method="sgs", rtol=0.0, max_iter=iters)
-    out["poisson256_stencil"] = {"n": n, "k_cg_pass1<StencilOp<7, double": 3 * V,
-                                 "k_gs_stencil<7>": 3 * V // 2 + V // 2,
-                                 "k_gs_check<StencilOp<7, double": 2 * V}
+    out["poisson256_stencil"] = {"n": n, "k_grid_cg_a<GridOp<7, double": 3 * V,
+                                 "k_grid_gs<GridOp<7, double": 3 * V}
     del S, b
     torch.cuda.empty_cache()
     # 192^3 upwind convection-diffusion, packed CSR
@@ -608,8 +607,8 @@ def kernel_suite(its, inputs, iters=10):
     log(f"kernels: bicgstab 192^3 upwind ({iters} iterations)")
     run(C2, b2, method="bicgstab", rtol=0.0, max_iter=iters)
     M2, V2 = packed_matrix_bytes(C2, n2), 8 * n2
-    out["convdiff192_packed"] = {"n": n2, "k_bicg_a<": M2 + 6 * V2, "k_bicg_b<": M2 + 3 * V2,
-                                 "k_bicg_c": 9 * V2}
+    out["convdiff192_packed"] = {"n": n2, "k_grid_bicg_a<": M2 + 4 * V2, "k_grid_bicg_b<": M2 + 2 * V2,
+                                 "k_grid_bicg_c<": M2 + 8 * V2}
     del C2, b2
     torch.cuda.empty_cache()
     # 192^3 27-point, packed CSR with FP32 and FP16 value copies
@@ -624,11 +623,10 @@ def kernel_suite(its, inputs, iters=10):
         run(A3, b3, method="cg", rtol=1e-12, max_iter=iters, inner_dtype=lowp, inner_rtol=1e-30)
     V3, V3_32 = 8 * n2, 4 * n2
     out["stencil27_192_packed"] = {
-        "n": n2, "k_cg_pass1<SellOp<double": packed_matrix_bytes(A3, n2) + 3 * V3,
-        "k_cg_pass2<double, true": 6 * V3,
-        "k_cg_pass1_pairs<SellOp<float": packed_matrix_bytes(A3, n2, "f32") + 3 * V3_32,
-        "k_cg_pass1_pairs<SellOp<__half": packed_matrix_bytes(A3, n2, "f16") + 3 * V3_32,
-        "k_cg_pass2_f32x2": 6 * V3_32}
+        "n": n2, "k_grid_cg_a<GridOp<27, double": packed_matrix_bytes(A3, n2) + 3 * V3,
+        "k_grid_cg_b<GridOp<27, double": int(4.5 * V3),
+        "k_grid_cg_a<GridOp<27, float": packed_matrix_bytes(A3, n2, "f32") + 3 * V3_32,
+        "k_grid_cg_b<GridOp<27, float": int(4.5 * V3_32)}
     del A3, b3
     torch.cuda.empty_cache()
     return out
@@ -707,11 +705,11 @@ def extras(its, inputs, A, b, xs, n, nnz, N, args, ws, s_per_it):
     S = its.StencilMatrix(N, N, N, inputs.POISSON7)
     its.solve(S, b, method="cg", rtol=args.rtol, max_iter=20000)
     t, (xs_, info) = timed(lambda: its.solve(S, b, method="cg", rtol=args.rtol, max_iter=20000))
-    # matrix-free: pass 1 gathers the {r, p} pairs (2V) and writes q (V);
-    # pass 2 moves 6V on average (x every other iteration): 9V
+    # plane sweeps: pass 1 reads r and p and writes p' (3V), pass 2 moves 4.5V
+    # on average (x every other iteration): 7.5V
     ex["stencil_cg_256"] = {"iters": info.iters, "s": t, "iters_per_s": info.iters / t,
-                            "bytes_per_iter": 9 * V,
-                            "achieved_gbs": info.iters / t * 9 * V / 1e9}
+                            "bytes_per_iter": int(7.5 * V),
+                            "achieved_gbs": info.iters / t * 7.5 * V / 1e9}
     # Jacobi: 2000 capped sweeps on the CSR system
     its.solve(A, b, method="jacobi", rtol=args.rtol, max_iter=50)
     t, (xj, info) = timed(lambda: its.solve(A, b, method="jacobi", rtol=args.rtol, max_iter=500))
@@ -746,14 +744,16 @@ def extras(its, inputs, A, b, xs, n, nnz, N, args, ws, s_per_it):
     reps = 10
     t, (xb, info) = timed(lambda: its.solve(C, b2, method="bicgstab", rtol=args.rtol, max_iter=2000),
                           reps=reps)
-    # two SpMV passes over the matrix; the pair layout of the vectors moves
-    # 18V per iteration (one more than the fused minimum of 17V)
+    # plane sweeps: A reads r, u, r' and writes v (4V), B reads r and v (2V), C
+    # reads r, v, x, u, r' and writes x, r, u (8V).  Otherwise two SpMV passes
+    # over the matrix, and the pair layout of the vectors moves 18V
     M2 = packed_matrix_bytes(C, n2)
+    bicg_bytes = 14 * 8 * n2 if C.packed_slots and M2 <= 27 * 8 else 2 * M2 + 18 * 8 * n2
     ex["bicgstab_192_convdiff_csr"] = {"iters": info.iters, "restarts": info.restarts,
                                        "s_per_solve": t, "iters_per_s": info.iters / t,
                                        "solves_per_s": 1.0 / t,
-                                       "bytes_per_iter": 2 * M2 + 18 * 8 * n2,
-                                       "achieved_gbs": info.iters / t * (2 * M2 + 18 * 8 * n2) / 1e9,
+                                       "bytes_per_iter": bicg_bytes,
+                                       "achieved_gbs": info.iters / t * bicg_bytes / 1e9,
                                        "true_rel_res": info.true_rel_res}
     del C, x2, b2, xb
     ex["ir_27pt_192"] = ir_27pt(its, inputs, args)

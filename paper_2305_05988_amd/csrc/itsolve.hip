@@ -1035,35 +1035,36 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
       LAUNCH(run, kClassOther, k_begin, 1, w.st2, (int32_t)kRunning, rho_i, ithr2, budget);
       if (grid.npts)
         s = cg_grid(run, grid, w, w.st2, h, budget, batch_size(o), d, rh, P);
-      else
-      s = with_op32(A, dt, [&](auto op) -> its_status {
-        // two rows per lane where it pays (measured): FP16 values, or
-        // slices wider than one group of seven entries
-        bool pairs = false;
-        if constexpr (PairWalk<decltype(op)>::value)
-          pairs = sizeof(typename decltype(op)::value_type) == 2 || A->sell_wmax > 7;
-        int GA = op.grid();
-        if constexpr (PairWalk<decltype(op)>::value)
-          if (pairs) GA = op.grid_pairs(A->sell_wmax > 7);
-        Flow f(run, w, w.st2);
-        return iterate(run, w.st2, h, budget, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
-          Pass p;
-          if (first) f.start();
-          TRY(f.enter<1>(GA, FinCg2{}, 0, p));
-          bool done = false;
+      else {
+        s = with_op32(A, dt, [&](auto op) -> its_status {
+          // two rows per lane where it pays (measured): FP16 values, or
+          // slices wider than one group of seven entries
+          bool pairs = false;
           if constexpr (PairWalk<decltype(op)>::value)
-            if (pairs) {
-              LAUNCH_PASS(run, 0, k_cg_pass1_pairs, (decltype(op)), GA, p, op, (const float2_t *)rhp, q);
-              done = true;
-            }
-          if (!done) LAUNCH_PASS(run, 0, k_cg_pass1, (decltype(op), float), GA, p, op, (const float2_t *)rhp, q);
-          TRY(f.leave<1>(GA, p));
-          TRY(f.enter<1>(G2, FinCg1{}, 1, p));
-          LAUNCH_PASS(run, 1, k_cg_pass2_f32x2, (GathersPairs<decltype(op)>::value), G2, p, n, d, rhp, (const float *)q);
-          TRY(f.leave<1>(G2, p));
-          return last ? f.end<1>(FinCg2{}) : ITS_OK;
+            pairs = sizeof(typename decltype(op)::value_type) == 2 || A->sell_wmax > 7;
+          int GA = op.grid();
+          if constexpr (PairWalk<decltype(op)>::value)
+            if (pairs) GA = op.grid_pairs(A->sell_wmax > 7);
+          Flow f(run, w, w.st2);
+          return iterate(run, w.st2, h, budget, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
+            Pass p;
+            if (first) f.start();
+            TRY(f.enter<1>(GA, FinCg2{}, 0, p));
+            bool done = false;
+            if constexpr (PairWalk<decltype(op)>::value)
+              if (pairs) {
+                LAUNCH_PASS(run, 0, k_cg_pass1_pairs, (decltype(op)), GA, p, op, (const float2_t *)rhp, q);
+                done = true;
+              }
+            if (!done) LAUNCH_PASS(run, 0, k_cg_pass1, (decltype(op), float), GA, p, op, (const float2_t *)rhp, q);
+            TRY(f.leave<1>(GA, p));
+            TRY(f.enter<1>(G2, FinCg1{}, 1, p));
+            LAUNCH_PASS(run, 1, k_cg_pass2_f32x2, (GathersPairs<decltype(op)>::value), G2, p, n, d, rhp, (const float *)q);
+            TRY(f.leave<1>(G2, p));
+            return last ? f.end<1>(FinCg2{}) : ITS_OK;
+          });
         });
-      });
+      }
       if (s != ITS_OK) return s;
       if (!grid.npts) LAUNCH(run, kClassOther, k_cg_flush_x32, G, n, d, (const float2_t *)rhp, (const State *)w.st2);
       inner_total += h->k;
@@ -1137,38 +1138,39 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
         TRY(f.leave<2>(g.blocks, ps));
         return last ? f.end<2>(fc) : ITS_OK;
       });
-    } else
-    s = with_op64(A, [&](auto op) -> its_status {
-      const int GA = op.grid();
-      if (o->persistent) {
-        // BiCGStab-B1's split-phase schedule (ITS_BICGSTAB_SPLIT=0: the same
-        // updates after the waits, classical BiCGStab's blocking points)
-        return with_persistent(A, [&](auto po) -> its_status {
-          if (env_int("ITS_BICGSTAB_SPLIT", 1) != 0)
-            return persist_launch(run, h, k_bicg_persist<decltype(po), true>, po.grid(), w, po, x, ru, rs, p, rv, t, b,
+    } else {
+      s = with_op64(A, [&](auto op) -> its_status {
+        const int GA = op.grid();
+        if (o->persistent) {
+          // BiCGStab-B1's split-phase schedule (ITS_BICGSTAB_SPLIT=0: the same
+          // updates after the waits, classical BiCGStab's blocking points)
+          return with_persistent(A, [&](auto po) -> its_status {
+            if (env_int("ITS_BICGSTAB_SPLIT", 1) != 0)
+              return persist_launch(run, h, k_bicg_persist<decltype(po), true>, po.grid(), w, po, x, ru, rs, p, rv, t, b,
+                                    w.st, w.R, rt2, paper);
+            return persist_launch(run, h, k_bicg_persist<decltype(po), false>, po.grid(), w, po, x, ru, rs, p, rv, t, b,
                                   w.st, w.R, rt2, paper);
-          return persist_launch(run, h, k_bicg_persist<decltype(po), false>, po.grid(), w, po, x, ru, rs, p, rv, t, b,
-                                w.st, w.R, rt2, paper);
+          });
+        }
+        Flow f(run, w, w.st);
+        const FinBicgC fc{nullptr, rt2, paper};
+        return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
+          Pass ps;
+          if (first) f.start();
+          TRY(f.enter<2>(GA, fc, 0, ps));
+          LAUNCH_PASS(run, 0, k_bicg_a, (decltype(op)), GA, ps, op, (const double2_t *)ru, rs, p, rv, fc);
+          TRY(f.leave<1>(GA, ps));
+          TRY(f.enter<1>(GA, FinBicgA{}, 1, ps));
+          // backwards: it starts on the {r, v} pairs pass A wrote last
+          LAUNCH_OP(run, 1, k_bicg_b, true, GA, ps, op, (const double2_t *)rv, t);
+          TRY(f.leave<2>(GA, ps));
+          TRY(f.enter<2>(GC, FinBicgB{}, 2, ps));
+          LAUNCH_PASS(run, 2, k_bicg_c, (GathersPairs<decltype(op)>::value), GC, ps, n, x, ru, (const double *)rs, (const double *)p, (const double2_t *)rv, (const double *)t);
+          TRY(f.leave<2>(GC, ps));
+          return last ? f.end<2>(fc) : ITS_OK;
         });
-      }
-      Flow f(run, w, w.st);
-      const FinBicgC fc{nullptr, rt2, paper};
-      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
-        Pass ps;
-        if (first) f.start();
-        TRY(f.enter<2>(GA, fc, 0, ps));
-        LAUNCH_PASS(run, 0, k_bicg_a, (decltype(op)), GA, ps, op, (const double2_t *)ru, rs, p, rv, fc);
-        TRY(f.leave<1>(GA, ps));
-        TRY(f.enter<1>(GA, FinBicgA{}, 1, ps));
-        // backwards: it starts on the {r, v} pairs pass A wrote last
-        LAUNCH_OP(run, 1, k_bicg_b, true, GA, ps, op, (const double2_t *)rv, t);
-        TRY(f.leave<2>(GA, ps));
-        TRY(f.enter<2>(GC, FinBicgB{}, 2, ps));
-        LAUNCH_PASS(run, 2, k_bicg_c, (GathersPairs<decltype(op)>::value), GC, ps, n, x, ru, (const double *)rs, (const double *)p, (const double2_t *)rv, (const double *)t);
-        TRY(f.leave<2>(GC, ps));
-        return last ? f.end<2>(fc) : ITS_OK;
       });
-    });
+    }
     if (s != ITS_OK) return s;
   } else {
     s = poll(run, w.st, h);
@@ -1220,21 +1222,22 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
       TRY(f.leave<1>(g.blocks, ps));
       return last ? f.end<1>(FinJacobi{}) : ITS_OK;
     });
-  } else
+  } else {
     s = with_op64(A, [&](auto op) -> its_status {
-    const int GA = op.grid();
-    Flow f(run, w, w.st);
-    return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
-      const int a = int(j & 1);
-      Pass p;
-      if (first) f.start();
-      TRY(f.enter<1>(GA, FinJacobi{}, a, p));
-      // odd sweeps run backwards: each starts on the x values the previous one wrote last
-      LAUNCH_OP(run, 0, k_jacobi, a == 1, GA, p, op, b, (const double *)X[a], X[a ^ 1]);
-      TRY(f.leave<1>(GA, p));
-      return last ? f.end<1>(FinJacobi{}) : ITS_OK;
+      const int GA = op.grid();
+      Flow f(run, w, w.st);
+      return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+        const int a = int(j & 1);
+        Pass p;
+        if (first) f.start();
+        TRY(f.enter<1>(GA, FinJacobi{}, a, p));
+        // odd sweeps run backwards: each starts on the x values the previous one wrote last
+        LAUNCH_OP(run, 0, k_jacobi, a == 1, GA, p, op, b, (const double *)X[a], X[a ^ 1]);
+        TRY(f.leave<1>(GA, p));
+        return last ? f.end<1>(FinJacobi{}) : ITS_OK;
+      });
     });
-  });
+  }
   if (s != ITS_OK) return s;
   if (h->k & 1) HIP_TRY(hipMemcpyAsync(x, X[1], size_t(n) * 8, hipMemcpyDeviceToDevice, run.s));
   HIP_TRY(hipStreamSynchronize(run.s));

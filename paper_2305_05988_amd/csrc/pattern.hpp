@@ -28,6 +28,8 @@ namespace its {
 // 120x110x96 63 -> 28 us, red-black half-sweeps 192x160x170 76 -> 34 and 51 ->
 // 31 us.  Blocks walk several tiles (4096 blocks at most: 103 us for the 256^3
 // pass alone against 124 with 8192 and 137 with one tile per block).
+// (Constant stencils on grids of 360,448 points and more have since moved to the
+// plane sweep, grid.hpp; the figures are those of this walk.)
 constexpr int kPatMax = 32;            // positions per pattern
 constexpr int kPatTable = 1 << 15;     // hash slots of the search for patterns
 constexpr int kPatLimit = 1 << 13;     // most patterns a layout may have
