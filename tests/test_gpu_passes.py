@@ -35,15 +35,16 @@ def _line(n):
 ROWS = 256
 
 
-@pytest.mark.parametrize("graph", [False, True])
-@pytest.mark.parametrize("method", ["cg", "cgnb", "bicgstab", "jacobi", "sgs"])
 # one block; a grid on both sides of 1024 blocks; the update passes' 1024 blocks
-# behind a pass of more
-@pytest.mark.parametrize("n", [1, 255, 1024 * ROWS, 1024 * ROWS + 1, 2048 * ROWS + 77])
+# behind a pass of more; graphs at two sizes
+SIZES = [(n, False) for n in (1, 255, 1024 * ROWS, 1024 * ROWS + 1, 2048 * ROWS + 77)]
+SIZES += [(255, True), (1024 * ROWS + 1, True)]
+
+
+@pytest.mark.parametrize("n,graph", SIZES)
+@pytest.mark.parametrize("method", ["cg", "cgnb", "bicgstab", "jacobi", "sgs"])
 @pytest.mark.parametrize("pack", [False, True])
-def test_both_sides(pack, n, method, graph):
-    if graph and n not in (255, 1024 * ROWS + 1):  # graphs at two sizes
-        pytest.skip("graphs at two sizes")
+def test_both_sides(pack, method, n, graph):
     Acsr = _line(n)
     A = its().CSRMatrix.from_numpy(*Acsr, pack=pack, max_fill=4.0)
     b = inputs.uniform_vector(n, 3)
