@@ -174,8 +174,9 @@ its_status its_csr_set_lowp(its_matrix *A, const void *val_lo, int32_t dtype);
    have it, and each slice stores its pattern's number.  Constant-coefficient
    operators on structured grids pack this way, whatever their sides.  A matrix
    that is exactly a 7- or 27-point stencil with constant finite coefficients on
-   a grid of at least 360,448 points (the neighbours outside it omitted) is
-   then applied as that stencil; the results are the same bit for bit.
+   a grid of at least 360,448 points that is not a thin duct (the neighbours
+   outside it omitted) is then applied as that stencil; the results are the same
+   bit for bit.
    The packed copy (col, val and any low-precision values attached with
    its_csr_set_lowp, which must come first) is allocated and owned by the
    handle and freed by its_matrix_destroy or the next its_csr_pack; it is a
@@ -280,9 +281,9 @@ int64_t its_matrix_rows(const its_matrix *A);
 
 /* Brick plan of a matrix-free operator (the 7- and 27-point stencils of Section
    3.1 and the variable-coefficient operator) for the passes that march bricks:
-   those of small grids and of the persistent kernels (constant stencils from
-   360,448 points on, and variable coefficients from 786,432 to 6 million, are
-   swept in tiles of their own): plan (host,
+   those of small and of thin grids and of the persistent kernels (constant
+   stencils from 360,448 points on, and variable coefficients from 786,432 to 6
+   million, are otherwise swept in tiles of their own): plan (host,
    4 int32, out) = x tiles of 64 points, y tiles of 4 points, z chunks, and
    the z planes per chunk (the last chunk may hold fewer).  A block marches
    one (x tile, y tile, z chunk) brick plane by plane.  Depends only on the

@@ -1,6 +1,7 @@
 // The passes of constant stencils on large grids: kernels and launches.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <type_traits>
 
 #include "fins.hpp"
@@ -420,40 +421,13 @@ hipError_t with_stream(const GridRun &g, F &&f) {
 
 }  // namespace
 
-// From 360,448 points on; per iteration, packed rows (or bricks) and planes:
-// packed CG 64^3 13.2 and 16.1 us, 72^3 17.9 and 17.1, 88^3 22.4 and 19.4;
-// matrix-free BiCGStab 72^3 35.6 and 28.9; packed 27-point Jacobi 72^3 14.6 and
-// 10.4 (below, the chain of planes of a block costs more than the gathers).
-// In-plane rows are 28-bit so that their byte offsets fit 32 bits.
-bool grid_takes(int32_t nx, int32_t ny, int32_t nz) {
-  const int64_t nxy = int64_t(nx) * ny;
-  return nxy * nz >= (int64_t(11) << 15) && nxy < (int64_t(1) << 28);
-}
-
-// Variable coefficients from 786,432 cells to 6 million: CG 80^3 25.0 us an
-// iteration by bricks and 26.5 by planes, 131x118x107 46.1 and 38.2, 180^3 104
-// and 98, but 256^3 254 and 275 (two passes form the faces, and there the bricks'
-// one pass and the stored A p cost less); Jacobi 131x118x107 33.7 and 18.9,
-// BiCGStab 93 and 67.
-bool grid_takes_var(int32_t nx, int32_t ny, int32_t nz) {
-  const int64_t n = int64_t(nx) * ny * nz;
-  return grid_takes(nx, ny, nz) && n >= (int64_t(3) << 18) && n < (int64_t(6) << 20);
-}
-
-// Four points per thread in 512 blocks (two per CU, all resident) from 5 million
-// points on: CG 256^3 164 us an iteration, 174 with 1024 blocks, 179 with two
-// points; below, two points in 768 blocks: BiCGStab 160x144x150 78.3 us against
-// 82.4 with four, CG 150^3 42.2 against 43.1 with 1024 blocks.  Variable
-// coefficients: two points in 512 blocks (four do not leave registers for two
-// blocks on a CU; 128^3 42.9 us against 44.5 with 768).
 // Streaming from 256 MB of vectors on: CG 256^3 (512 MB) 164 us against 197
 // with allocating accesses, 27-point 192^3 (226 MB) 79.6 against 73.3.
 GridRun grid_run(const GridStencil &a, int64_t vector_bytes, hipStream_t s) {
-  const bool var = a.npts == 1;
-  if (var) vector_bytes += int64_t(8) * a.n;  // k
-  GridRun g{&a, {}, 0, 0, vector_bytes > (int64_t(256) << 20), s};
-  g.points = !var && a.n >= (5 << 20) ? 4 : 2;
-  g.plan = grid_plan(a.nx, a.ny, a.nz, g.points, var || g.points == 4 ? 512 : 768);
+  static_assert(kGridThreads == kBlock, "the plan's block size");
+  if (a.npts == 1) vector_bytes += int64_t(8) * a.n;  // k
+  const GridShape shape = grid_shape(a.npts, a.nx, a.ny, a.nz);
+  GridRun g{&a, shape.plan, shape.points, 0, vector_bytes > (int64_t(256) << 20), s};
   const int64_t b = int64_t(g.plan.ntx) * g.plan.nty * g.plan.ncz;
   // one round for all: up to the next multiple of 8 (XCDs), not down (CG
   // 192x160x170, 510 bricks: 72.7 us with 504 blocks, 57.3 with 512)

@@ -1,7 +1,6 @@
 // The plane sweep of constant stencils on large grids.
 #pragma once
 
-#include <algorithm>
 #include <type_traits>
 
 #include "grid_passes.hpp"
@@ -24,33 +23,6 @@ namespace its {
 //
 // W need not be a multiple of a wave: a 160-point line is cut into two tiles
 // of 80 with every lane at work.
-// Tiles that cover the grid with the least points loaded and thread slots
-// spent, the ring at most one point per thread; then z chunks for about
-// `blocks` blocks of at least 4 planes.
-inline GridPlan grid_plan(int32_t nx, int32_t ny, int32_t nz, int R, int blocks) {
-  GridPlan best{1, 1, 1, 1, 1, 1};
-  double cost = 1e300;
-  for (int32_t ntx = (nx + 109) / 110; ntx <= (nx + 109) / 110 + 6 && ntx <= nx; ++ntx) {
-    const int32_t W = (nx + ntx - 1) / ntx;
-    int32_t H = std::min(kBlock * R / W, 126 - W);
-    H = std::min(H, ny);
-    if (H < 1) continue;
-    const int32_t nty = (ny + H - 1) / H;
-    H = (ny + nty - 1) / nty;
-    const double c = double(ntx) * nty * (0.5 * kBlock * R + double(W + 4) * (H + 2));
-    if (c < cost) {
-      cost = c;
-      best = GridPlan{W, H, (nx + W - 1) / W, nty, 1, 1};
-    }
-  }
-  const int64_t tiles = int64_t(best.ntx) * best.nty;
-  int64_t chunks = std::max<int64_t>(1, blocks / tiles);
-  chunks = std::min<int64_t>(chunks, std::max(1, nz / 4));
-  best.zb = int32_t((nz + chunks - 1) / chunks);
-  best.ncz = (nz + best.zb - 1) / best.zb;
-  return best;
-}
-
 // The plain chain of a row.  add: an entry below the diagonal; centre: the
 // diagonal; above: an entry above it (the 7-point sweeps number theirs: at x +
 // 1, y + 1 and z + 1).

@@ -3,12 +3,9 @@
 
 #include "common.hpp"
 #include "fins.hpp"
+#include "grid_plan.hpp"
 
 namespace its {
-
-struct GridPlan {
-  int32_t W, H, ntx, nty, zb, ncz;  // tile, tiles in x and y, planes per chunk, chunks
-};
 
 // A constant stencil on nx*ny*nz with neighbours outside the grid omitted -- a
 // matrix-free operator, or a packed CSR matrix found to be one -- or the
@@ -20,10 +17,6 @@ struct GridStencil {
   float lo[27] = {};    // the same for the refinement's inner solve
   const double *k = nullptr;  // variable coefficients: one per cell
 };
-
-// Whether the plane sweep takes this grid (else the bricks or the packed rows do).
-bool grid_takes(int32_t nx, int32_t ny, int32_t nz);
-bool grid_takes_var(int32_t nx, int32_t ny, int32_t nz);  // variable coefficients
 
 // What every pass runs with.
 struct GridRun {

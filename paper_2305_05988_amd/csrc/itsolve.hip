@@ -1606,7 +1606,7 @@ its_status its_stencil_create(int32_t nx, int32_t ny, int32_t nz, int32_t npts, 
     A->low[0][o] = float(coef[o]);
     A->low[1][o] = float(static_cast<_Float16>(coef[o]));
   }
-  if (grid_takes(nx, ny, nz)) {
+  if (grid_takes(npts, nx, ny, nz, false)) {
     A->red_black = npts == 7;
     A->grid = GridStencil{npts, nx, ny, nz, int32_t(n), {}, {}, nullptr};
     for (int o = 0; o < npts; ++o) A->grid.c[o] = coef[o];
@@ -1668,7 +1668,7 @@ its_status its_varcoef_create(int32_t nx, int32_t ny, int32_t nz, const double *
   A->ny = ny;
   A->nz = nz;
   A->kcoef = k;
-  if (grid_takes_var(nx, ny, nz)) {
+  if (grid_takes(1, nx, ny, nz, false)) {
     A->grid.npts = 1;
     A->grid.nx = nx;
     A->grid.ny = ny;
@@ -2141,7 +2141,7 @@ static hipError_t find_grid(its_matrix *A, hipStream_t s) {
         if (np == 7 && std::abs(dk) + std::abs(dj) + std::abs(di) > 1) continue;
         if (d.d[q++] != dk * nxy + dj * nx + di) return hipSuccess;
       }
-  if (nz < 2 || !grid_takes(int32_t(nx), ny, nz)) return hipSuccess;
+  if (nz < 2 || !grid_takes(np, int32_t(nx), ny, nz, true)) return hipSuccess;
   DevTmp bad;
   uint32_t hbad = 1;
   e = hipMalloc(&bad.p, sizeof(uint32_t));
