@@ -10,6 +10,8 @@
 #include <cstdint>
 #include <type_traits>
 
+#include "dd.hpp"
+
 namespace its {
 
 constexpr int kBlock = 256;             // threads per block: 4 wave64
@@ -50,32 +52,6 @@ struct alignas(256) State {
 // Written-out roundings: the library is compiled with -ffp-contract=off, so
 // a*b+c is two roundings and fma() is one, exactly as written.
 
-struct DD {  // unevaluated sum hi + lo, |lo| <= ulp(hi)/2 when normalised
-  double hi, lo;
-};
-
-__device__ __forceinline__ DD two_sum(double a, double b) {
-  const double s = a + b;
-  const double bp = s - a;
-  const double e = (a - (s - bp)) + (b - bp);
-  return {s, e};
-}
-
-__device__ __forceinline__ DD fast_two_sum(double a, double b) {  // |a| >= |b|
-  const double s = a + b;
-  return {s, b - (s - a)};
-}
-
-// Accurate double-double addition (error ~ 2^-104 relative to |a|+|b|).
-__device__ __forceinline__ DD dd_add(DD a, DD b) {
-  DD s = two_sum(a.hi, b.hi);
-  const DD t = two_sum(a.lo, b.lo);
-  s.lo += t.hi;
-  s = fast_two_sum(s.hi, s.lo);
-  s.lo += t.lo;
-  return fast_two_sum(s.hi, s.lo);
-}
-
 // Per-thread compensated dot accumulator (Ogita-Rump-Oishi Dot2): the
 // product error comes from fma, the sum error from two_sum; both are summed
 // into c.  A float*float product is exact in double, so its error term is 0.
@@ -92,8 +68,6 @@ struct Dot2 {
   // dd_cascade / dd_add, which need no normalised input
   __device__ __forceinline__ DD get() const { return {s, c}; }
 };
-
-__device__ __forceinline__ double dd_round(DD v) { return v.hi + v.lo; }
 
 __device__ __forceinline__ bool finite(double v) { return __builtin_isfinite(v); }
 
@@ -198,17 +172,6 @@ __device__ __forceinline__ void for_tiles(int32_t n, Body &&body, bool rev = fal
 }
 
 // --------------------------------------------------------------- reductions
-
-// Cascaded sum of unevaluated pairs (the Sum2 step of Ogita-Rump-Oishi):
-// the high parts are added error-free, their error joins the low parts.
-// The result is the sum of the operands' values up to an error of about
-// 2^-106 times the sum of their magnitudes, the accuracy class of Dot2
-// itself, so a reduction of Dot2 partials through it keeps Dot2's bound; it
-// costs 8 additions instead of dd_add's 20.
-__device__ __forceinline__ DD dd_cascade(DD a, DD b) {
-  const DD s = two_sum(a.hi, b.hi);
-  return {s.hi, (a.lo + b.lo) + s.lo};
-}
 
 __device__ __forceinline__ DD wave_reduce(DD v) {
 #pragma unroll
@@ -327,23 +290,7 @@ __global__ void __launch_bounds__(kBlock) k_finish_group(PartialSlots from, Redu
 // 0.  Every thread of the block calls it.
 template <int ND>
 __device__ __forceinline__ void sum_in_block(const DD *const *src, int count, DD (&v)[ND]) {
-#pragma unroll
-  for (int d = 0; d < ND; ++d) v[d] = DD{0.0, 0.0};
-  // four partials per thread in flight at a time, added in the same order
-  constexpr int kU = 4;
-  for (int j0 = int(threadIdx.x); j0 < count; j0 += kU * kBlock) {
-    DD t[kU][ND];
-#pragma unroll
-    for (int u = 0; u < kU; ++u) {
-      const int j = j0 + u * kBlock;
-#pragma unroll
-      for (int d = 0; d < ND; ++d) t[u][d] = j < count ? src[d][j] : DD{0.0, 0.0};
-    }
-#pragma unroll
-    for (int u = 0; u < kU; ++u)
-#pragma unroll
-      for (int d = 0; d < ND; ++d) v[d] = dd_cascade(v[d], t[u][d]);
-  }
+  dd_sum<ND>(src, int(threadIdx.x), kBlock, count, v);
   block_reduce<ND>(v);
 }
 

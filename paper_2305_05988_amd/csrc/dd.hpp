@@ -1,0 +1,72 @@
+// Sums of unevaluated pairs of doubles (error-free transformations).  Plain
+// arithmetic behind HIP's qualifiers, so that a host compiler takes it as well.
+#pragma once
+
+namespace its {
+
+struct DD {  // unevaluated sum hi + lo, |lo| <= ulp(hi)/2 when normalised
+  double hi, lo;
+};
+
+__device__ __forceinline__ DD two_sum(double a, double b) {
+  const double s = a + b;
+  const double bp = s - a;
+  const double e = (a - (s - bp)) + (b - bp);
+  return {s, e};
+}
+
+__device__ __forceinline__ DD fast_two_sum(double a, double b) {  // |a| >= |b|
+  const double s = a + b;
+  return {s, b - (s - a)};
+}
+
+// Accurate double-double addition (of normalised pairs: relative error at most 3 * 2^-106).
+__device__ __forceinline__ DD dd_add(DD a, DD b) {
+  DD s = two_sum(a.hi, b.hi);
+  const DD t = two_sum(a.lo, b.lo);
+  s.lo += t.hi;
+  s = fast_two_sum(s.hi, s.lo);
+  s.lo += t.lo;
+  return fast_two_sum(s.hi, s.lo);
+}
+
+// Cascaded sum of unevaluated pairs (the Sum2 step of Ogita-Rump-Oishi):
+// the high parts are added error-free, their error joins the low parts.
+// The result is the sum of the operands' values up to an error of about
+// 2^-106 times the sum of their magnitudes, the accuracy class of Dot2
+// itself, so a reduction of Dot2 partials through it keeps Dot2's bound; it
+// costs 8 additions instead of dd_add's 20.
+__device__ __forceinline__ DD dd_cascade(DD a, DD b) {
+  const DD s = two_sum(a.hi, b.hi);
+  return {s.hi, (a.lo + b.lo) + s.lo};
+}
+
+__device__ __forceinline__ double dd_round(DD v) { return v.hi + v.lo; }
+
+// v[d] = the partials first, first + step, ... below count of src[d], added in
+// that order, four of them in flight at a time: the serial part of the sums over
+// a grid's blocks.  In the accurate addition, whose error follows the running
+// sum; a cascade's would follow the magnitudes of all partials added so far.
+template <int ND>
+__device__ __forceinline__ void dd_sum(const DD *const *src, int first, int step, int count, DD (&v)[ND]) {
+#pragma unroll
+  for (int d = 0; d < ND; ++d) v[d] = DD{0.0, 0.0};
+  constexpr int kU = 4;
+  for (int at = 0; at < count; at += kU * step) {  // at: the same for all first < step
+    DD t[kU][ND];
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      const int j = first + at + u * step;
+#pragma unroll
+      for (int d = 0; d < ND; ++d) t[u][d] = j < count ? src[d][j] : DD{0.0, 0.0};
+    }
+#pragma unroll
+    for (int u = 0; u < kU; ++u) {
+      if (at + u * step >= count) break;
+#pragma unroll
+      for (int d = 0; d < ND; ++d) v[d] = dd_add(v[d], t[u][d]);
+    }
+  }
+}
+
+}  // namespace its
