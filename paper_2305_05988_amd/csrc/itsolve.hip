@@ -22,6 +22,7 @@
 #include "grid_passes.hpp"
 #include "host.hpp"
 #include "kernels.hpp"
+#include "poll.hpp"
 
 using namespace its;
 
@@ -229,6 +230,7 @@ struct Run {
   Prof prof;
   its_matrix::GraphCache *gc = nullptr;  // null: launch each iteration eagerly
   std::vector<uint64_t> key;             // what the captured launches depend on
+  double rho0 = 0.0;                     // r.r before the next iteration loop
   template <class K, class... Args>
   hipError_t launch(int cls, K kernel, int grid, Args... args) {
     prof.begin(cls, s);
@@ -594,26 +596,39 @@ its_status flag_to_status(int32_t f) {
   }
 }
 
-// 32 iterations between two reads of the State: a read idles the GPU for ~20 us,
-// an iteration too many costs ~5.  Against 8: 40 Jacobi sweeps 720 -> 676 us,
-// CG 131x118x107 (46 us an iteration) 38.1 -> 37.2 ms, 256^3 80.1 -> 79.5 ms; 64
-// loses where a solve has few hundred iterations (45x38x41 1.74 -> 2.06 ms).
-int batch_size(const its_options *o) { return o->check_every > 0 ? o->check_every : 32; }
+Batches batch_size(const its_options *o, int64_t n) { return batches(o->check_every, n); }
+
+// The length of each batch of one loop, from what the reads of the State say.
+struct Pace {
+  Batches b;
+  double rho0;  // r.r before the loop
+  int now;
+
+  Pace(const Batches &b, double rho0) : b(b), rho0(rho0), now(b.least) {}
+  // of `left` iterations; with room to grow, no remainder below the least batch
+  int64_t todo(int64_t left) const {
+    if (b.least < b.most && left - now < b.least) return left;
+    return std::min<int64_t>(now, left);
+  }
+  void read(const State &s) { now = next_batch(b, rho0, s.rho, s.k, s.thr2); }
+};
 
 // Runs iterations j = j0, j0+1, ... until the device flag leaves kRunning or
 // max_iter iterations were launched; `step(j, first, last)` launches iteration
 // j, the first or last of its batch (the State is read after the last).
 // Graph form of the loop: iterations 0..m-1 (or 1..m with the first run
 // eagerly, for a step whose first iteration differs) are captured once on
-// the handle's stream and replayed, with one poll of the State per replay.
+// the handle's stream and replayed, with one poll of the State after as many
+// replays as make a batch.
 // m is even so that steps alternating buffers by the parity of j line up.
 // The limits live in the State, so the same graph serves every right-hand
 // side; the key holds every value the captured launches bake in.
 template <class Step>
-its_status iterate_graph(Run &run, const State *dev, State *host, int64_t max_iter, int m,
+its_status iterate_graph(Run &run, const State *dev, State *host, int64_t max_iter, const Batches &b,
                          bool eager_first, Step &&step) {
   its_matrix::GraphCache &G = *run.gc;
-  if (m & 1) ++m;
+  const int m = b.least + (b.least & 1);
+  Pace pace(b, run.rho0);
   if (!G.s) {
     HIP_TRY(hipStreamCreateWithFlags(&G.s, hipStreamNonBlocking));
     HIP_TRY(hipEventCreateWithFlags(&G.ev, hipEventDisableTiming));
@@ -656,22 +671,28 @@ its_status iterate_graph(Run &run, const State *dev, State *host, int64_t max_it
     G.key = key;
   }
   for (;;) {
-    HIP_TRY(hipGraphLaunch(G.exec, G.s));
-    j += m;
+    int64_t todo = pace.todo(max_iter - j);
+    do {
+      HIP_TRY(hipGraphLaunch(G.exec, G.s));
+      j += m;
+      todo -= m;
+    } while (todo > 0);
     HIP_TRY(hipMemcpyAsync(host, dev, sizeof(State), hipMemcpyDeviceToHost, G.s));
     HIP_TRY(hipStreamSynchronize(G.s));
     if (host->flag != kRunning) return ITS_OK;
+    pace.read(*host);
     if (j >= max_iter + m) return fail(ITS_E_HIP, "device state still running after max_iter");
   }
 }
 
 template <class Step>
-its_status iterate(Run &run, const State *dev, State *host, int64_t max_iter, int m, Step &&step,
+its_status iterate(Run &run, const State *dev, State *host, int64_t max_iter, const Batches &b, Step &&step,
                    bool eager_first = false) {
-  if (run.gc && run.prof.every == 0) return iterate_graph(run, dev, host, max_iter, m, eager_first, step);
+  if (run.gc && run.prof.every == 0) return iterate_graph(run, dev, host, max_iter, b, eager_first, step);
   int64_t j = 0;
+  Pace pace(b, run.rho0);
   for (;;) {
-    const int64_t todo = std::min<int64_t>(m, max_iter - j);
+    const int64_t todo = pace.todo(max_iter - j);
     for (int64_t t = 0; t < todo; ++t, ++j) {
       its_status st = step(j, t == 0, t == todo - 1);
       if (st != ITS_OK) return st;
@@ -679,6 +700,7 @@ its_status iterate(Run &run, const State *dev, State *host, int64_t max_iter, in
     its_status st = poll(run, dev, host);
     if (st != ITS_OK) return st;
     if (host->flag != kRunning) return ITS_OK;
+    pace.read(*host);
     if (j >= max_iter) return fail(ITS_E_HIP, "device state still running after max_iter");
   }
 }
@@ -733,6 +755,7 @@ its_status prologue(Run &run, const its_matrix *A, const WS &w, const double *b,
   if (s != ITS_OK) return s;
   bb = host->dot[0];
   rr = host->dot[1];
+  run.rho0 = rr;
   return ITS_OK;
 }
 
@@ -806,7 +829,7 @@ its_status persist_launch(Run &run, State *h, K kernel, int units, const WS &w, 
 // The iterations of CG by plane sweeps (grid.hip): T double, or float for the
 // refinement's inner solve.  P[0] holds zeros at the start.
 template <class T>
-its_status cg_grid(Run &run, const GridStencil &a, const WS &w, State *st, State *h, int64_t max_iter, int m, T *x,
+its_status cg_grid(Run &run, const GridStencil &a, const WS &w, State *st, State *h, int64_t max_iter, const Batches &m, T *x,
                    T *r, T *const (&P)[2]) {
   GridRun g = grid_run(a, int64_t(4 * sizeof(T)) * a.n, run.s);  // r, p, p', x
   Flow f(run, w, st);
@@ -868,13 +891,13 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
     return ITS_OK;
   }
   if (flag == kRunning && grid) {
-    s = cg_grid(run, A->grid, w, w.st, h, o->max_iter, batch_size(o), x, r, P);
+    s = cg_grid(run, A->grid, w, w.st, h, o->max_iter, batch_size(o, n), x, r, P);
     if (s != ITS_OK) return s;
   } else if (flag == kRunning) {
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
       Flow f(run, w, w.st);
-      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
         Pass p;
         if (first) f.start();
         TRY(f.enter<1>(GA, FinCg2{}, 0, p));
@@ -936,7 +959,7 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
       Flow f(run, w, w.st);
       if (A->grid.npts) {
         GridRun g = grid_run(A->grid, 40 * A->n, run.s);  // {r, A p}, p, w, x
-        return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
+        return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
           Pass ps;
           if (first) f.start();
           TRY(f.enter<1>(g.blocks, FinCgnbY{}, 0, ps));
@@ -948,7 +971,7 @@ its_status solve_cgnb(Run &run, const its_matrix *A, const its_options *o, const
           return last ? f.end<1>(FinCgnbY{}) : ITS_OK;
         });
       }
-      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
         Pass ps;
         if (first) f.start();
         TRY(f.enter<1>(GA, FinCgnbY{}, 0, ps));
@@ -1029,12 +1052,13 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
     s = poll(run, w.st2, h);
     if (s != ITS_OK) return s;
     const double rho_i = h->dot[1];
+    run.rho0 = rho_i;
     const double ithr2 = threshold2(o->inner_rtol, rho_i);
     const int64_t budget = o->max_iter - inner_total;
     if (!(rho_i <= ithr2)) {
       LAUNCH(run, kClassOther, k_begin, 1, w.st2, (int32_t)kRunning, rho_i, ithr2, budget);
       if (grid.npts)
-        s = cg_grid(run, grid, w, w.st2, h, budget, batch_size(o), d, rh, P);
+        s = cg_grid(run, grid, w, w.st2, h, budget, batch_size(o, n), d, rh, P);
       else {
         s = with_op32(A, dt, [&](auto op) -> its_status {
           // two rows per lane where it pays (measured): FP16 values, or
@@ -1046,7 +1070,7 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
           if constexpr (PairWalk<decltype(op)>::value)
             if (pairs) GA = op.grid_pairs(A->sell_wmax > 7);
           Flow f(run, w, w.st2);
-          return iterate(run, w.st2, h, budget, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
+          return iterate(run, w.st2, h, budget, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
             Pass p;
             if (first) f.start();
             TRY(f.enter<1>(GA, FinCg2{}, 0, p));
@@ -1123,7 +1147,7 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
       GridRun g = grid_run(A->grid, 48 * A->n, run.s);  // r, its next, u, r', v, x
       Flow f(run, w, w.st);
       const FinBicgC fc{nullptr, rt2, paper};
-      s = iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+      s = iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
         double *r = rr2[j & 1], *rn = rr2[(j & 1) ^ 1];
         Pass ps;
         if (first) f.start();
@@ -1154,7 +1178,7 @@ its_status solve_bicgstab(Run &run, const its_matrix *A, const its_options *o, c
         }
         Flow f(run, w, w.st);
         const FinBicgC fc{nullptr, rt2, paper};
-        return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t, bool first, bool last) -> its_status {
+        return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t, bool first, bool last) -> its_status {
           Pass ps;
           if (first) f.start();
           TRY(f.enter<2>(GA, fc, 0, ps));
@@ -1213,7 +1237,7 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
   if (A->grid.npts) {
     GridRun g = grid_run(A->grid, 24 * A->n, run.s);  // x, its next, b
     Flow f(run, w, w.st);
-    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
       const int a = int(j & 1);
       Pass ps;
       if (first) f.start();
@@ -1226,7 +1250,7 @@ its_status solve_jacobi(Run &run, its_matrix *A, const its_options *o, const dou
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
       Flow f(run, w, w.st);
-      return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
         const int a = int(j & 1);
         Pass p;
         if (first) f.start();
@@ -1350,7 +1374,7 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
       LAUNCH_GRID(run, 0, g, grid_gs(g, mode, c, b, x, xs, p));
       return ITS_OK;
     };
-    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
       if (first) f.start();
       const int red = int(j & 1);
       if (j == 0) {
@@ -1376,7 +1400,7 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
     // The red partials (dot 0) of iteration j - 1 and the black ones (dot 1)
     // of iteration j make the test that iteration j's red sweep applies before
     // it writes its own red partials: those alternate between two regions.
-    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+    s = iterate(run, w.st, h, steps_for(o->max_iter), batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
       if (first) f.start();
       const int red = int(j & 1);
       if (j == 0) {
@@ -1398,7 +1422,7 @@ its_status solve_sgs(Run &run, its_matrix *A, const its_options *o, const double
     if (A->grid.npts) g = grid_run(A->grid, 16 * A->n, run.s);  // x, b
     s = with_op64(A, [&](auto op) -> its_status {
       const int GA = op.grid();
-      return iterate(run, w.st, h, o->max_iter, batch_size(o), [&](int64_t j, bool first, bool last) -> its_status {
+      return iterate(run, w.st, h, o->max_iter, batch_size(o, n), [&](int64_t j, bool first, bool last) -> its_status {
         if (first) f.start();
         for (int c = (j == 0 ? 0 : 1); c < nc; ++c) TRY(sweep(c, 2, Plain{}));
         for (int c = nc - 2; c >= 0; --c) TRY(sweep(c, 2, Plain{}));
