@@ -16,21 +16,27 @@ struct GridPlan {
 // Tiles that cover the grid with the least points loaded and thread slots
 // spent, the ring at most one point per thread; then z chunks for about
 // `blocks` blocks of at least 4 planes.  R: points per thread.
-inline GridPlan grid_plan(int32_t nx, int32_t ny, int32_t nz, int R, int blocks) {
+// lines: tiles of whole 128-byte lines (16 points).
+inline GridPlan grid_plan(int32_t nx, int32_t ny, int32_t nz, int R, int blocks, bool lines) {
   GridPlan best{1, 1, 1, 1, 1, 1};
   double cost = 1e300;
-  for (int32_t ntx = (nx + 109) / 110; ntx <= (nx + 109) / 110 + 6 && ntx <= nx; ++ntx) {
-    const int32_t W = (nx + ntx - 1) / ntx;
+  auto consider = [&](int32_t W) {
     int32_t H = std::min(kGridThreads * R / W, 126 - W);
     H = std::min(H, ny);
-    if (H < 1) continue;
-    const int32_t nty = (ny + H - 1) / H;
+    if (H < 1) return;
+    const int32_t ntx = (nx + W - 1) / W, nty = (ny + H - 1) / H;
     H = (ny + nty - 1) / nty;
     const double c = double(ntx) * nty * (0.5 * kGridThreads * R + double(W + 4) * (H + 2));
     if (c < cost) {
       cost = c;
-      best = GridPlan{W, H, (nx + W - 1) / W, nty, 1, 1};
+      best = GridPlan{W, H, ntx, nty, 1, 1};
     }
+  };
+  if (lines) {
+    for (int32_t W = 96; W >= 48; W -= 16) consider(W);  // the wider of equals
+  } else {
+    const int32_t least = (nx + 109) / 110;
+    for (int32_t ntx = least; ntx <= least + 6 && ntx <= nx; ++ntx) consider((nx + ntx - 1) / ntx);
   }
   const int64_t tiles = int64_t(best.ntx) * best.nty;
   int64_t chunks = std::max<int64_t>(1, blocks / tiles);
@@ -61,13 +67,21 @@ struct GridShape {
 // coefficients: two points in 512 blocks (four do not leave registers for two
 // blocks on a CU; 128^3 42.9 us against 44.5 with 768).  Tiles that four points
 // per thread would leave half empty take two: CG 16x16x31250 136 us and 100.
+//
+// From 2^23 points on, where the vectors stream past the caches (grid_run), a
+// line of memory that two tiles share is moved twice and stored in two parts:
+// tiles of whole lines there, where the grid's own lines start at even points
+// and are long enough to cut.  CG 272^3 in tiles of 39 points 342 us an iteration
+// (bricks 250), of 48 220; 400^3 1024 (841) and 688, 250^3 231 (208) and 186; one
+// product of 800x800x100 291 (219) and 216.  Tiles of 32 lose to the ring.
 inline GridShape grid_shape(int npts, int32_t nx, int32_t ny, int32_t nz) {
   const int64_t n = int64_t(nx) * ny * nz;
-  const bool var = npts == 1;
+  const bool var = npts == 1, lines = !var && n >= (int64_t(1) << 23) && nx % 2 == 0 &&
+                                     (nx >= 96 || (nx >= 64 && nx % 8 == 0));
   GridShape s;
   s.points = !var && n >= (5 << 20) ? 4 : 2;
   for (;;) {
-    s.plan = grid_plan(nx, ny, nz, s.points, var || s.points == 4 ? 512 : 768);
+    s.plan = grid_plan(nx, ny, nz, s.points, var || s.points == 4 ? 512 : 768, lines);
     s.fill = grid_fill(nx, ny, s.plan, s.points);
     if (s.points == 2 || s.fill >= 0.5) return s;
     s.points = 2;
@@ -117,6 +131,17 @@ inline bool grid_takes(int npts, int32_t nx, int32_t ny, int32_t nz, bool packed
   }
   if (packed) return filled;
   return filled || s.fill >= (npts == 27 ? 1.0 : 1.2) * bricks;
+}
+
+// Whether matrix-free CG, which forms A p twice in the sweep and once in the
+// bricks, takes the sweep on a grid that it takes.  Not
+// on large grids whose lines start at any point or whose planes are too few tiles
+// for the chip: bricks and planes 401^3 905 and 1013 us an iteration, 350^3 594 and
+// 739, 1581x1582x8 248 and 266, 720x360x100 (270 bricks) 321 and 391.
+inline bool grid_takes_cg(int npts, int32_t nx, int32_t ny, int32_t nz) {
+  if (npts != 7 || int64_t(nx) * ny * nz < (int64_t(1) << 24)) return true;
+  const GridPlan g = grid_shape(npts, nx, ny, nz).plan;
+  return nx % 4 == 0 && int64_t(g.ntx) * g.nty * g.ncz >= 320;
 }
 
 }  // namespace its

@@ -860,7 +860,8 @@ its_status solve_cg(Run &run, const its_matrix *A, const its_options *o, const d
   double2_t *rp = w.reg<double2_t>(0);  // {r, p} pairs
   double *q = w.v64(1);
   // the plane sweep's vectors in the same space: r, and p and p' in turn
-  const bool grid = A->grid.npts != 0 && !o->persistent;
+  const bool grid = A->grid.npts != 0 && !o->persistent &&
+                    (A->kind == kCsr || grid_takes_cg(A->grid.npts, A->nx, A->ny, A->nz));
   double *r = w.v64(0), *P[2] = {r + n, w.v64(1)};
   double bb, rr;
   its_status s = grid ? prologue<false>(run, A, w, b, x, r, h, bb, rr, P[0])

@@ -49,6 +49,7 @@ extern "C" double shape(int npts, int nx, int ny, int nz, int *out) {
 extern "C" int takes(int npts, int nx, int ny, int nz, int packed) {
   return its::grid_takes(npts, nx, ny, nz, packed != 0);
 }
+extern "C" int takes_cg(int npts, int nx, int ny, int nz) { return its::grid_takes_cg(npts, nx, ny, nz); }
 """)
     lib.shape.restype = C.c_double
     return lib
@@ -62,3 +63,7 @@ def shape(npts, g):
 
 def takes(npts, g, packed=False):
     return bool(_lib().takes(npts, *g, int(packed)))
+
+
+def takes_cg(npts, g):
+    return bool(_lib().takes_cg(npts, *g))

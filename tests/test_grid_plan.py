@@ -47,6 +47,19 @@ def test_half_empty_tiles_of_four_points_take_two():
     assert grid_plan.shape(7, (256, 256, 256)).points == 4
 
 
+@pytest.mark.parametrize("g", [(272, 272, 272), (400, 400, 400), (250, 250, 250), (800, 800, 100), (912, 913, 24),
+                               (72, 72, 1800), (10000, 900, 1), (2300000, 4, 1)])
+@pytest.mark.parametrize("npts", [7, 27])
+def test_large_grids_are_cut_into_whole_lines(npts, g):
+    assert grid_plan.shape(npts, g).W % 16 == 0
+
+
+@pytest.mark.parametrize("g,takes", [((272, 272, 272), True), ((401, 401, 401), False), ((350, 350, 350), False),
+                                     ((720, 360, 100), False), ((256, 256, 256), True), ((201, 201, 201), True)])
+def test_matrix_free_cg_of_large_grids(g, takes):
+    assert grid_plan.takes_cg(7, g) == takes and grid_plan.takes_cg(27, g)
+
+
 def test_plans():
     """Tiles and chunks cover the grid; the tile, its ring and the LDS planes fit."""
     rng = random.Random(3)
