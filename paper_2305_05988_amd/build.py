@@ -7,6 +7,7 @@ instructions are disabled for all device code.
 import os
 import subprocess
 import sys
+import tempfile
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
@@ -24,19 +25,23 @@ FLAGS = [
 
 
 def build(verbose: bool = False) -> str:
-    """Compiles the sources side by side and links them."""
-    objects = [src[:-len(".hip")] + ".o" for src in SOURCES]
-    compiles = [[HIPCC] + FLAGS + ["-c", src, "-o", obj] for src, obj in zip(SOURCES, objects)]
-    link = [HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared"] + objects + ["-o", LIB + ".tmp"]
-    if verbose:
-        for cmd in compiles + [link]:
-            print(" ".join(cmd), flush=True)
-    running = [subprocess.Popen(cmd) for cmd in compiles]
-    for cmd, status in [(cmd, p.wait()) for cmd, p in zip(compiles, running)]:
-        if status != 0:
-            raise subprocess.CalledProcessError(status, cmd)
-    subprocess.run(link, check=True)
-    os.replace(LIB + ".tmp", LIB)
+    """Compiles the sources side by side and links them.  The objects and the
+    unfinished library have names of this call's own, so that builds at the same
+    time do not write each other's."""
+    tmp = f"{LIB}.tmp{os.getpid()}"
+    with tempfile.TemporaryDirectory() as folder:
+        objects = [os.path.join(folder, os.path.basename(src) + ".o") for src in SOURCES]
+        compiles = [[HIPCC] + FLAGS + ["-c", src, "-o", obj] for src, obj in zip(SOURCES, objects)]
+        link = [HIPCC, "--offload-arch=gfx950", "-fPIC", "-shared"] + objects + ["-o", tmp]
+        if verbose:
+            for cmd in compiles + [link]:
+                print(" ".join(cmd), flush=True)
+        running = [subprocess.Popen(cmd) for cmd in compiles]
+        for cmd, status in [(cmd, p.wait()) for cmd, p in zip(compiles, running)]:
+            if status != 0:
+                raise subprocess.CalledProcessError(status, cmd)
+        subprocess.run(link, check=True)
+    os.replace(tmp, LIB)
     return LIB
 
 
