@@ -1019,6 +1019,10 @@ its_status solve_ir(Run &run, const its_matrix *A, const its_options *o, const d
   GridStencil grid = A->grid;
   std::memcpy(grid.lo, A->low[dt == ITS_F16], sizeof(grid.lo));
   if (A->kind == kVar7) grid.npts = 0;  // refused below
+  // the sweep multiplies a coefficient by 0 where the neighbour lies outside the
+  // grid: one that overflows FP16 (or FP32) and that no row uses must not be there
+  for (float c : grid.lo)
+    if (!std::isfinite(c)) grid.npts = 0;
   float *rh = w.reg<float>(1), *P[2] = {rh + n, q};
   double bb, rr;
   its_status s = prologue<false>(run, A, w, b, x, r, h, bb, rr);
