@@ -2026,7 +2026,6 @@ static its_status pack_rows(const its_matrix *A, const int32_t *rows, int64_t co
       P.sp = nullptr;
       P.soff = nullptr;
       P.smask = nullptr;
-      P.col_slots = 0;
     } else {
       if (e == hipSuccess) e = hipMalloc(&P.val, size_t(total) * sizeof(double));
       if (e == hipSuccess && v32) e = hipMalloc(&P.val32, size_t(total) * sizeof(float));

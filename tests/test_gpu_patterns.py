@@ -135,13 +135,3 @@ def test_refinement(dtype):
     x, info = its().solve(A, dev(b), method="cg", inner_dtype=dtype, rtol=1e-10, max_iter=500)
     assert info.iters == rr.iters and info.inner_iters == rr.inner_iters
     assert np.array_equal(x.cpu().numpy(), ref)
-
-
-def test_pattern_form_stores_no_columns():
-    make, _ = CASES["holes: a slice's list is longer than its rows"]
-    Acsr = make()
-    A = its().CSRMatrix.from_numpy(*Acsr, validate=False, pack=True, max_fill=8.0)
-    assert _is_pattern(A) and A.packed_column_slots == 0
-    val = Acsr[2] * np.linspace(1.0, 2.0, Acsr[2].size)  # the same slices with values of their own
-    A = its().CSRMatrix.from_numpy(Acsr[0], Acsr[1], val, validate=False, pack=True, max_fill=8.0)
-    assert not _is_pattern(A) and A.packed_column_slots > 0
