@@ -219,8 +219,9 @@ its_status its_csr_value_grad(const its_matrix *A, const double *x, const double
 int64_t its_csr_packed_slots(const its_matrix *A);
 
 /* Slots of the packed layout that store a column index (those of the slices
-   that are not offset slices, see its_csr_pack); 0 if not packed or if
-   every slice is an offset slice. */
+   that are not offset slices, see its_csr_pack; where the pattern form is used,
+   which stores none, those that it stands for); 0 if not packed or if every
+   slice is an offset slice. */
 int64_t its_csr_packed_column_slots(const its_matrix *A);
 
 /* Bytes of the matrix that one pass over the packed layout reads with values

@@ -124,7 +124,8 @@ class CSRMatrix(_Matrix):
 
     @property
     def packed_column_slots(self) -> int:
-        """Packed slots that still store a column index (0: all offset slices)."""
+        """Packed slots that store a column index, or would without the pattern
+        form (0: all offset slices)."""
         return int(L.lib().its_csr_packed_column_slots(self._h))
 
     def packed_bytes(self, dtype="f64") -> int:
