@@ -1889,9 +1889,9 @@ static hipError_t scan_slices(const its_matrix *A, const int32_t *rows, int32_t 
   const int64_t ns = (int64_t(count) + kSlice - 1) / kSlice;
   const int grid = int(std::min<int64_t>((ns + kWaves - 1) / kWaves, 65536));
   struct Found {
+    unsigned long long col_slots, odd;
     unsigned long long key[kPatTable];
     unsigned int rep[kPatTable];
-    unsigned long long col_slots, odd;
   };
   DevTmp tmp, rep, number;
   PatArrays T;
@@ -1902,8 +1902,7 @@ static hipError_t scan_slices(const its_matrix *A, const int32_t *rows, int32_t 
     return e;
   }
   Found *F = static_cast<Found *>(tmp.p);
-  std::vector<char> raw(sizeof(Found));
-  Found *H = reinterpret_cast<Found *>(raw.data());
+  unsigned long long totals[2] = {0, 0};  // col_slots, odd
   e = hipMemsetAsync(F, 0, sizeof(Found), s);
   if (e == hipSuccess) e = hipMemsetAsync(F->rep, 0xff, sizeof(F->rep), s);
   if (e == hipSuccess) {
@@ -1911,18 +1910,24 @@ static hipError_t scan_slices(const its_matrix *A, const int32_t *rows, int32_t 
                        P.sp, P.soff, P.smask, T.pid, F->key, F->rep, &F->col_slots, &F->odd);
     e = hipGetLastError();
   }
-  if (e == hipSuccess) e = hipMemcpyAsync(H, F, sizeof(Found), hipMemcpyDeviceToHost, s);
+  if (e == hipSuccess) e = hipMemcpyAsync(totals, F, sizeof(totals), hipMemcpyDeviceToHost, s);
   if (e == hipSuccess) e = hipStreamSynchronize(s);
+  // patterns numbered in the order of their first slices
+  std::vector<std::pair<uint32_t, int32_t>> found;
+  if (e == hipSuccess && totals[1] == 0) {
+    std::vector<unsigned long long> key(kPatTable);
+    std::vector<unsigned int> first(kPatTable);
+    e = hipMemcpyAsync(key.data(), F->key, sizeof(F->key), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipMemcpyAsync(first.data(), F->rep, sizeof(F->rep), hipMemcpyDeviceToHost, s);
+    if (e == hipSuccess) e = hipStreamSynchronize(s);
+    for (int32_t q = 0; e == hipSuccess && q < kPatTable; ++q)
+      if (key[size_t(q)]) found.emplace_back(first[size_t(q)], q);
+  }
   if (e != hipSuccess) {
     T.release();
     return e;
   }
-  P.col_slots = int64_t(H->col_slots);
-  // patterns numbered in the order of their first slices
-  std::vector<std::pair<uint32_t, int32_t>> found;
-  if (H->odd == 0)
-    for (int32_t q = 0; q < kPatTable; ++q)
-      if (H->key[q]) found.emplace_back(H->rep[q], q);
+  P.col_slots = int64_t(totals[0]);
   if (found.empty() || found.size() > size_t(kPatLimit)) {
     T.release();
     return hipSuccess;

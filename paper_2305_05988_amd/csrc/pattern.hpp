@@ -189,10 +189,12 @@ __device__ __forceinline__ int32_t wave_min(int32_t v) {
 }
 
 // Row p of the layout is matrix row rows[p] (p when rows is null); every lane
-// of the wave calls it for the same slice.  val32 and val16 may be null.
+// of the wave calls it for the same slice.  val32 and val16 may be null.  tight:
+// only an offset slice is looked for, which has no more offsets than its longest
+// row has entries.
 __device__ __forceinline__ SlicePattern slice_pattern(int64_t s, int32_t count, const int32_t *rp, const int32_t *rows,
                                                       const int32_t *col, const double *val, const float *val32,
-                                                      const __half *val16) {
+                                                      const __half *val16, bool tight = false) {
   const int lane = threadIdx.x & 63;
   const int64_t p = s * kSlice + lane;
   int32_t i = 0, e = 0, end = 0;
@@ -202,12 +204,17 @@ __device__ __forceinline__ SlicePattern slice_pattern(int64_t s, int32_t count, 
     end = rp[i + 1];
   }
   SlicePattern r{0, 0, 0, 0, 0, 0, -wave_min(-(end - e)), true, true};
+  const int32_t most = tight ? min(kPatMax, r.wmax) : kPatMax;
+  if (r.wmax > most) {
+    r.ascending = false;
+    return r;
+  }
   for (;;) {
     const int32_t c = e < end ? col[e] : 0;
     const int32_t mine = e < end ? c - i : INT32_MAX;
     const int32_t d = wave_min(mine);
     if (d == INT32_MAX) break;
-    if (r.w == kPatMax) {
+    if (r.w == most) {
       r.ascending = false;
       break;
     }
@@ -248,12 +255,21 @@ __device__ __forceinline__ uint64_t mix64(uint64_t h) {  // the finaliser of Spl
   return h ^ (h >> 31);
 }
 
+__device__ __forceinline__ bool is_set(unsigned long long *flag) {
+  return __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+}
+// Sets a flag that many may set: only the first few write.
+__device__ __forceinline__ void set_once(unsigned long long *flag) {
+  if (!is_set(flag)) atomicAdd(flag, 1ull);
+}
+
 // One wave per slice.  Slices whose offsets make an offset slice (sell.hpp:
 // as many offsets as the longest row has entries) get their descriptors and
 // their flag in sp; the slots of the others are added to *col_slots.  The
 // slices that have a pattern enter its hash into the table (hkey, with the
-// lowest slice of each hash in hrep) and keep its slot in pid; *odd counts
-// those that have none (and the slices of a full table).
+// lowest slice of each hash in hrep) and keep its slot in pid; *odd becomes
+// nonzero where one has none (or the table is full), and then the rest enter
+// nothing: the layout keeps its values.
 __global__ void __launch_bounds__(kBlock) k_slice_scan(int32_t count, const int32_t *__restrict__ rp,
                                                        const int32_t *__restrict__ rows,
                                                        const int32_t *__restrict__ col, const double *val,
@@ -265,7 +281,9 @@ __global__ void __launch_bounds__(kBlock) k_slice_scan(int32_t count, const int3
   const int64_t ns = (int64_t(count) + kSlice - 1) / kSlice;
   const int lane = threadIdx.x & 63;
   for (int64_t s = int64_t(blockIdx.x) * kWaves + (threadIdx.x >> 6); s < ns; s += int64_t(gridDim.x) * kWaves) {
-    const SlicePattern r = slice_pattern(s, count, rp, rows, col, val, val32, val16);
+    // whether the layout keeps its values already (the same for the whole wave)
+    const bool lost = __builtin_amdgcn_readfirstlane(is_set(odd)) != 0;
+    const SlicePattern r = slice_pattern(s, count, rp, rows, col, val, val32, val16, lost);
     if (r.wmax > 0) {
       if (r.ascending && r.w == r.wmax) {
         const int64_t base = sp[s];
@@ -279,9 +297,10 @@ __global__ void __launch_bounds__(kBlock) k_slice_scan(int32_t count, const int3
       }
     }
     if (!r.ascending || !r.constant) {
-      if (lane == 0) atomicAdd(odd, 1ull);
+      if (lane == 0) set_once(odd);
       continue;
     }
+    if (lost) continue;
     uint64_t h = 0;
     if (lane < r.w) {
       h = mix64(uint64_t(lane + 1) * 0x9e3779b97f4a7c15ull ^ uint32_t(r.d));
@@ -304,7 +323,7 @@ __global__ void __launch_bounds__(kBlock) k_slice_scan(int32_t count, const int3
       }
     }
     if (at < 0) {
-      atomicAdd(odd, 1ull);
+      set_once(odd);
       continue;
     }
     if (__hip_atomic_load(hrep + at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > uint32_t(s))
@@ -342,8 +361,8 @@ __global__ void __launch_bounds__(kBlock) k_pattern_emit(int32_t patterns, int32
 }
 
 // Replaces each slice's hash slot by its pattern's number and compares the
-// slice with the pattern bit for bit: *odd counts the slices that differ
-// (two patterns with one hash).
+// slice with the pattern bit for bit: *odd becomes nonzero where one differs (two
+// patterns with one hash).
 __global__ void __launch_bounds__(kBlock) k_pattern_check(int32_t count, const int32_t *__restrict__ rp,
                                                           const int32_t *__restrict__ rows,
                                                           const int32_t *__restrict__ col, const double *val,
@@ -371,7 +390,7 @@ __global__ void __launch_bounds__(kBlock) k_pattern_check(int32_t count, const i
     const bool all = __all(same);
     if (lane == 0) {
       pid[s] = q;
-      if (!all) atomicAdd(odd, 1ull);
+      if (!all) set_once(odd);
     }
   }
 }
