@@ -41,6 +41,7 @@ KERNEL_SOURCES = ["paper_2305_05988_amd/csrc/common.hpp", "paper_2305_05988_amd/
                   "paper_2305_05988_amd/csrc/csr.hpp", "paper_2305_05988_amd/csrc/sell.hpp",
                   "paper_2305_05988_amd/csrc/pattern.hpp",
                   "paper_2305_05988_amd/csrc/kernels_cg.hpp",
+                  "paper_2305_05988_amd/csrc/dd.hpp", "paper_2305_05988_amd/csrc/grid_plan.hpp",
                   "paper_2305_05988_amd/csrc/grid.hpp", "paper_2305_05988_amd/csrc/grid.hip"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "cg_pass1_poisson256_traffic.txt")
 # Inside the timed region every PROFILE_EVERY-th launch of each kernel is

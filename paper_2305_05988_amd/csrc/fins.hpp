@@ -152,10 +152,7 @@ struct FinBicgC {
 
 // ----------------------------------------------- Jacobi and Gauss-Seidel
 
-// ------------------------------------------------------------------ Jacobi
-// One fused sweep: the residual of x_k (full chain) and x_{k+1} = (b - off)/d.
-// The test applies to x_k, so a converged solve returns x_k from xo.
-// The sweep's residual belongs to x_k: test it; if it fails, x_{k+1} is the
+// The Jacobi sweep's residual belongs to x_k: test it; if it fails, x_{k+1} is the
 // new iterate.
 struct FinJacobi {
   State *st;

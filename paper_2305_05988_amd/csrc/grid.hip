@@ -422,7 +422,9 @@ hipError_t with_stream(const GridRun &g, F &&f) {
 }  // namespace
 
 // Streaming from 256 MB of vectors on: CG 256^3 (512 MB) 164 us against 197
-// with allocating accesses, 27-point 192^3 (226 MB) 79.6 against 73.3.
+// with allocating accesses, 27-point 192^3 (226 MB) 79.6 against 73.3.  The
+// refinement's FP32 CG never streams: 272^3 124 us against 145 streaming, 288^3
+// 144 and 156, 400^3 405 and 421 (320^3 alone 201 and 177).
 GridRun grid_run(const GridStencil &a, int64_t vector_bytes, hipStream_t s) {
   static_assert(kGridThreads == kBlock, "the plan's block size");
   if (a.npts == 1) vector_bytes += int64_t(8) * a.n;  // k
@@ -430,7 +432,8 @@ GridRun grid_run(const GridStencil &a, int64_t vector_bytes, hipStream_t s) {
   GridRun g{&a, shape.plan, shape.points, 0, vector_bytes > (int64_t(256) << 20), s};
   const int64_t b = int64_t(g.plan.ntx) * g.plan.nty * g.plan.ncz;
   // one round for all: up to the next multiple of 8 (XCDs), not down (CG
-  // 192x160x170, 510 bricks: 72.7 us with 504 blocks, 57.3 with 512)
+  // 192x193x191, 507 bricks: 93 us with 504 blocks, 72 with 512; 272^3, 468: 297
+  // and 220)
   g.blocks = int(std::min<int64_t>(b < 64 ? b : (b + kXcds - 1) / kXcds * kXcds, kFinishOne));
   return g;
 }

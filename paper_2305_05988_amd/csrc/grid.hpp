@@ -14,15 +14,16 @@ namespace its {
 // two LDS planes for the neighbours in the plane, and a thread keeps its own
 // points' values in registers for the neighbours above and below.  A row's
 // chain is started when its plane arrives and finished when the next one does,
-// in the stored order: one barrier a plane, five LDS reads a row for 7 points,
-// and for 27 points nine, each value feeding the chains of three planes.
+// in the stored order: one barrier a plane, four LDS reads a row for 7 points, and
+// for 27 points eight, each value feeding the chains of three planes.
 //
 // Neighbours outside the grid are zeros in LDS that are never written, so the
 // chain takes a term c * 0 where the CSR row has no entry; c is finite, so the
 // term changes nothing.
 //
-// W need not be a multiple of a wave: a 160-point line is cut into two tiles
-// of 80 with every lane at work.
+// W need not be a multiple of a wave (grid_plan.hpp): a 160-point line is cut into
+// five tiles of 32, a 146-point line into two of 73, with every lane at work.
+
 // The plain chain of a row.  add: an entry below the diagonal; centre: the
 // diagonal; above: an entry above it (the 7-point sweeps number theirs: at x +
 // 1, y + 1 and z + 1).

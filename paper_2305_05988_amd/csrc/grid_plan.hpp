@@ -60,8 +60,9 @@ struct GridShape {
 
 // npts: 7, 27, or 1 for variable coefficients.
 //
-// Four points per thread in 512 blocks (two per CU, all resident) from 5 * 2^20
-// points on: CG 256^3 164 us an iteration, 174 with 1024 blocks, 179 with two
+// By the size of the grid alone, as measured on 7 points in FP64 (27 points and
+// the refinement's FP32 take the same).  Four points per thread in 512 blocks (two
+// per CU, all resident) from 5 * 2^20 points on: CG 256^3 164 us an iteration, 174 with 1024 blocks, 179 with two
 // points; below, two points in 768 blocks: BiCGStab 160x144x150 78.3 us against
 // 82.4 with four, CG 150^3 42.2 against 43.1 with 1024 blocks.  Variable
 // coefficients: two points in 512 blocks (four do not leave registers for two

@@ -9,6 +9,9 @@
 
 namespace its {
 
+// ------------------------------------------------------------------ Jacobi
+// One fused sweep: the residual of x_k (full chain) and x_{k+1} = (b - off)/d.
+// The test applies to x_k, so a converged solve returns x_k from xo.
 template <class Op, class P>
 __global__ void __launch_bounds__(kBlock) k_jacobi(Op A, const double *__restrict__ b,
                                                    const double *__restrict__ xo,

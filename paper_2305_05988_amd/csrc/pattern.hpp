@@ -23,14 +23,13 @@ namespace its {
 //
 // Bound by the gathers through L1 and L2 (seven 16-byte ones per row for the
 // 7-point CG pass), not by HBM.  Measured against the layout with a value per
-// entry: 256^3 7-point CG pass 233 -> 128 us (3.1 TB/s of its 3V), BiCGStab
-// 160x144x150 passes A 66 -> 48 and B 52 -> 27 us, 27-point Jacobi sweep
-// 120x110x96 63 -> 28 us, red-black half-sweeps 192x160x170 76 -> 34 and 51 ->
-// 31 us.  Blocks walk several tiles (4096 blocks at most: 103 us for the 256^3
-// pass alone against 124 with 8192 and 137 with one tile per block).
-// (Constant stencils on grids of 360,448 points and more have since moved to the
-// plane sweep, grid.hpp; the figures are those of this walk.)
+// entry, on a duct of 8x8x125000 points that the plane sweep (grid.hpp) leaves to
+// this walk: one product 91 -> 37 us, an iteration of CG 167 -> 117, of Jacobi
+// 118 -> 71 and of red-black Gauss-Seidel 191 -> 90.  Blocks walk several tiles: the
+// CG pass alone on 16.8 million rows takes 103 us with at most 4096 blocks, 124
+// with 8192 and 137 with one tile per block.
 constexpr int kPatMax = 32;            // positions per pattern
+static_assert(kPatMax == kMaxOffsetWidth, "the scan of a slice serves both forms");
 constexpr int kPatTable = 1 << 15;     // hash slots of the search for patterns
 constexpr int kPatLimit = 1 << 13;     // most patterns a layout may have
 

@@ -33,7 +33,7 @@ constexpr int kSlice = 64;  // rows per slice: one wave64
 // stencils in CSR form) pack entirely into offset slices, which removes the
 // 4-byte column index from every entry's traffic.
 constexpr int64_t kOffsetSlice = 1;
-constexpr int kMaxOffsetWidth = 32;
+constexpr int kMaxOffsetWidth = 32;  // positions of an offset slice
 __host__ __device__ __forceinline__ int64_t slice_base(int64_t v) { return v & ~int64_t(63); }
 
 __host__ __device__ __forceinline__ int64_t sell_slot(int64_t base, int32_t w, int32_t j,
