@@ -64,12 +64,11 @@ struct DDSum {
 // v[d] = the partials first, first + step, ... below count of src[d], added in
 // that order, four of them in flight at a time: the serial part of the sums over
 // a grid's blocks.  Its error follows the running sum; with dd_cascade, which
-// spares a finishing kernel of 4096 partials 0.36 us (773 iterations of CG
-// 131x118x107: 36.6 ms and 37.2), it would follow the magnitudes of all partials.
+// takes 8 operations instead of 20, it would follow the magnitudes of all partials.
 template <int ND>
 __device__ __forceinline__ void dd_sum(const DD *const *src, int first, int step, int count, DD (&v)[ND]) {
-  DDSum sum[ND];
   constexpr int kU = 4;
+  DDSum sum[ND];
   for (int at = 0; at < count; at += kU * step) {  // at: the same for all first < step
     DD t[kU][ND];
 #pragma unroll

@@ -238,15 +238,22 @@ struct Run {
     prof.end(s);
     return hipGetLastError();
   }
+  template <int ND, class Fin>
+  hipError_t finish_final(const PartialSlots &from, int count, Fin fin) {
+    prof.begin(kClassFinish, s);
+    launch_finish_final<ND>(from, count, fin, s);
+    prof.end(s);
+    return hipGetLastError();
+  }
   // The finishing kernel(s) of a reducing pass that ran with G blocks.
   template <int ND, class Fin>
   hipError_t finish(Reduce *R, int G, Fin fin) {
     const PartialSlots p1{{R->p1[0], R->p1[1]}}, p2{{R->p2[0], R->p2[1]}};
     const int nb = finish_grid(G);
-    if (nb == 0) return launch(kClassFinish, k_finish_final<ND, Fin>, 1, p1, G, fin);
+    if (nb == 0) return finish_final<ND>(p1, G, fin);
     hipError_t e = launch(kClassFinish, k_finish_group<ND>, nb, p1, R, G);
     if (e != hipSuccess) return e;
-    return launch(kClassFinish, k_finish_final<ND, Fin>, 1, p2, nb, fin);
+    return finish_final<ND>(p2, nb, fin);
   }
 };
 
@@ -506,7 +513,8 @@ struct Flow {
   template <int ND, class Fin>
   its_status apply(Fin fin) {
     fin.st = cur;
-    LAUNCH(*run, kClassFinish, (k_finish_final<ND, Fin>), 1, (PartialSlots{{src[0], src[1]}}), count, fin);
+    const hipError_t e = run->finish_final<ND>(PartialSlots{{src[0], src[1]}}, count, fin);
+    if (e != hipSuccess) return fail(ITS_E_HIP, std::string("launch: ") + hipGetErrorString(e));
     count = 0;
     return ITS_OK;
   }
@@ -2335,10 +2343,10 @@ its_status its_dot(int64_t n, const double *x, const double *y, double *result, 
   const PartialSlots p1{{R->p1[0], R->p1[1]}}, p2{{R->p2[0], R->p2[1]}};
   const int nb = finish_grid(G);
   if (nb == 0) {
-    hipLaunchKernelGGL((k_finish_final<1, FinDot>), dim3(1), dim3(kBlock), 0, s, p1, G, FinDot{st, 0});
+    launch_finish_final<1>(p1, G, FinDot{st, 0}, s);
   } else {
     hipLaunchKernelGGL(k_finish_group<1>, dim3(nb), dim3(kBlock), 0, s, p1, R, G);
-    hipLaunchKernelGGL((k_finish_final<1, FinDot>), dim3(1), dim3(kBlock), 0, s, p2, nb, FinDot{st, 0});
+    launch_finish_final<1>(p2, nb, FinDot{st, 0}, s);
   }
   HIP_TRY(hipGetLastError());
   double v = 0.0;
