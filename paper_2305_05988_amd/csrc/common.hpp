@@ -348,12 +348,12 @@ __global__ void __launch_bounds__(kBlock) k_pass_end(Pass p, Fin fin) {
   }
 }
 
-// Single block: reduce `count` partials and apply Fin to the totals.  1024 threads
-// for more than 2048 partials, 256 below: 773 iterations of CG 131x118x107 (4096
-// partials) 36.2 ms and 37.1, variable-coefficient CG 140x32x59 (1416) 19.6 us an
-// iteration and 18.8.
-constexpr int kFinishWide = 1024;  // threads
-constexpr int kFinishMany = 2048;  // partials
+// Single block: reduce `count` partials and apply Fin to the totals.  512 threads
+// for more than 1024 partials, 256 below: an iteration of CG 131x118x107 (4096
+// partials) 46.4 us, 46.6 with 1024 threads, 47.5 with 256; 56x73x182 (2912) 26.6,
+// 26.9 with 1024; variable-coefficient CG 140x32x59 (1416) 18.5 and 18.7.
+constexpr int kFinishWide = 512;   // threads
+constexpr int kFinishMany = 1024;  // partials
 
 template <int ND, class Fin, int Threads>
 __global__ void __launch_bounds__(Threads) k_finish_final(PartialSlots from, int count, Fin fin) {
