@@ -613,9 +613,9 @@ struct Pace {
   int now;
 
   Pace(const Batches &b, double rho0) : b(b), rho0(rho0), now(b.least) {}
-  // of `left` iterations; with room to grow, no remainder below the least batch
+  // of `left` iterations; with room to grow, a remainder below half a batch goes along
   int64_t todo(int64_t left) const {
-    if (b.least < b.most && left - now < b.least) return left;
+    if (b.least < b.most && left - now < now / 2) return left;
     return std::min<int64_t>(now, left);
   }
   void read(const State &s) { now = next_batch(b, rho0, s.rho, s.k, s.thr2); }
